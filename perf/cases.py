@@ -76,7 +76,8 @@ def draw(rng):
     """One more case: the models over their range of sizes and walker numbers,
     the compression styles, the initiator rule, and the ways to run them."""
     kind = rng.choice(["solver"] * 6 + ["replicas", "replicas", "spectral", "batch", "server", "resume"])
-    model = rng.choice([RING, MOM, LATTICE] if kind != "server" else [RING, MOM])
+    # the server runs the ring and momentum space; excited states are a real-space method here
+    model = rng.choice({"server": [RING, MOM], "spectral": [RING, LATTICE]}.get(kind, [RING, MOM, LATTICE]))
     top = {"solver": 7.0, "replicas": 6.5, "spectral": 5.0, "batch": 4.5, "server": 4.0, "resume": 6.0}[kind]
     target = float(round(10 ** rng.uniform(3.0, top)))
     # the basis must be able to hold the population
