@@ -1,4 +1,4 @@
-// fq_kernels.hpp -- the merge and spawn kernel templates of the FCIQMC step.
+// fq_kernels.hpp -- the merge, spawn and resident kernel templates of the FCIQMC step.
 //
 // Their instantiations (address words W, model variant, workgroup size,
 // compression style) are compiled in separate translation units, one per
@@ -6,6 +6,7 @@
 // FQ_INST_MODEL), so that they build in parallel; the host runtime declares
 // them with FQ_EXTERN_STEP_KERNELS and launches them through their handles.
 #pragma once
+#include "fq_resident.hpp"
 #include "fq_step.hpp"
 
 // The step kernels run over a set of instances: one, or a batch.  `insts` is
@@ -49,6 +50,34 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(FQ_SPAWN_WAV
     fq::spawn_bucket<W, MODEL, BS, EARLY>(I, b, mode, smem);
 }
 
+// Resident steps of small instances, 2^lg_grid workgroups of the grid for
+// each.  Up to 32 (the CUs of an XCD) they are placed on XCD i mod 8 for
+// instance i: workgroup 8 ((i / 8) 2^lg_grid + g) + i mod 8 of the grid is
+// its workgroup g.  Above, workgroup i 2^lg_grid + g is.  An instance takes
+// as many of them as it has buckets, and enough that none owns more than
+// RES_MAXK.  stop[i]: the step at which instance i ends this launch.
+struct ResStops {
+    fq::i64 step[fq::RES_MAXG];
+};
+__host__ __device__ __forceinline__ int res_log2_groups(int lg, int log2B)
+{
+    const int least = log2B - 6;  // RES_MAXK = 2^6
+    return lg < least ? least : lg > log2B ? log2B : lg;
+}
+template <int W, int MODEL, bool EARLY>
+__global__ __launch_bounds__(fq::RES_BS) void k_resident(const fq::Inst *const *insts, int n, int lg, int lg_grid,
+                                                         int max_items, fq::u64 patience, ResStops stops)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int x = (int)blockIdx.x, y = lg_grid <= 5 ? x >> 3 : x;
+    const int g = y & ((1 << lg_grid) - 1), i = lg_grid <= 5 ? ((y >> lg_grid) << 3) | (x & 7) : y >> lg_grid;
+    if (i >= n) return;
+    const fq::Inst &I = fq::const_inst(insts[i]);
+    const int own = res_log2_groups(lg, I.log2B);
+    if (g >> own) return;
+    fq::resident_steps<W, MODEL, EARLY>(I, I.res, g, own, stops.step[i], (fq::i64)max_items << own, patience, smem);
+}
+
 // explicit instantiations (EXT = extern: declaration only) of the merge and
 // spawn kernels of one (W, model variant) pair, all workgroup sizes and both
 // compression styles
@@ -64,7 +93,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(FQ_SPAWN_WAV
     EXT template __global__ void k_spawn<W_, M_, 1024, false>(const fq::Inst *const *, const fq::u32 *, int); \
     EXT template __global__ void k_spawn<W_, M_, 256, true>(const fq::Inst *const *, const fq::u32 *, int); \
     EXT template __global__ void k_spawn<W_, M_, 512, true>(const fq::Inst *const *, const fq::u32 *, int); \
-    EXT template __global__ void k_spawn<W_, M_, 1024, true>(const fq::Inst *const *, const fq::u32 *, int);
+    EXT template __global__ void k_spawn<W_, M_, 1024, true>(const fq::Inst *const *, const fq::u32 *, int); \
+    EXT template __global__ void k_resident<W_, M_, false>(const fq::Inst *const *, int, int, int, int, fq::u64, ResStops); \
+    EXT template __global__ void k_resident<W_, M_, true>(const fq::Inst *const *, int, int, int, int, fq::u64, ResStops);
 
 #define FQ_EXTERN_STEP_KERNELS                                                                \
     FQ_STEP_KERNEL_SET(extern, 1, 0) FQ_STEP_KERNEL_SET(extern, 1, 1) FQ_STEP_KERNEL_SET(extern, 1, 2)        \

@@ -6,7 +6,8 @@
 // table), k_spawn (one workgroup per bucket: spawn records of the new table
 // for the next step), k_part (second pass of the spawn partition, only when
 // there are more than 64 buckets) and k_finalize (one workgroup: exact
-// reduction of the per-bucket partial sums and the shift update).  The host
+// reduction of the per-bucket partial sums and the shift update).  Small
+// instances take many steps in one launch instead (k_resident).  The host
 // synchronises only at the end of a chunk of steps, to copy the statistics
 // rows and check the error word.
 #include <hip/hip_runtime.h>
@@ -81,12 +82,17 @@ __global__ __launch_bounds__(PartShape<W>::BS) void k_part(const Inst *const *in
                                                                    (int)(m & 0x3fffu));
 }
 
-// start of a chunk of steps: statistics rows are stored from row 0
-__global__ void k_begin_chunk(const Inst *const *insts, int n)
+// start of a chunk of steps: statistics rows are stored from row 0; the
+// exchange area of a resident launch starts at zero
+__global__ void k_begin_chunk(const Inst *const *insts, int n, int resident)
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         Ctrl *c = insts[i]->ctrl;
         c->ring_base = c->step + 1;
+        if (resident) {
+            ResSync *y = insts[i]->res;
+            y->arrived = y->gate = y->xccs = y->count = 0;
+        }
     }
 }
 
@@ -305,6 +311,23 @@ const void *step_kernel(int W, int var, int bs, bool spawn)
     return W == 1 ? step_kernel_w<1>(m, bs, spawn, e) : step_kernel_w<2>(m, bs, spawn, e);
 }
 
+template <int W> const void *resident_kernel_w(int m, bool e)
+{
+    switch (m) {
+    case 0: return e ? (const void *)k_resident<W, 0, true> : (const void *)k_resident<W, 0, false>;
+    case 1: return e ? (const void *)k_resident<W, 1, true> : (const void *)k_resident<W, 1, false>;
+    case 2: return e ? (const void *)k_resident<W, 2, true> : (const void *)k_resident<W, 2, false>;
+    default: return e ? (const void *)k_resident<W, 3, true> : (const void *)k_resident<W, 3, false>;
+    }
+}
+
+int res_lds_bytes(int W) { return W == 1 ? ResLds<1>::BYTES : ResLds<2>::BYTES; }
+
+const void *resident_kernel(int W, int var)
+{
+    return W == 1 ? resident_kernel_w<1>(var % 4, var >= 4) : resident_kernel_w<2>(var % 4, var >= 4);
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int ilog2(i64 x)
@@ -339,6 +362,8 @@ size_t lds_spawn_bytes(i64 cap_t) { return (size_t)cap_t * 12 + 160 * 8 + 2048 +
 
 constexpr size_t LDS_MAX = 160 * 1024;
 static_assert(sizeof(Ctrl) % 4 == 0, "Ctrl is copied in 32-bit words");
+constexpr size_t REF_TMP_BYTES = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP + 64;
+static_assert(sizeof(ResSync) <= REF_TMP_BYTES, "the exchange area of resident steps lies in the set-state staging");
 static_assert(sizeof(StepStats) == sizeof(fq_step_stats), "StepStats mirrors fq_step_stats");
 
 // A set of instances stepped together: one launch per kernel per step.
@@ -501,7 +526,7 @@ int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, R
     R.off_ref_h = take(sizeof(double) * REFCAP);
     R.off_ref_b = take(sizeof(int) * REFCAP);
     R.off_ref_off = take(sizeof(int) * (R.B + 1));
-    R.off_ref_tmp = take((sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP + 64);
+    R.off_ref_tmp = take(REF_TMP_BYTES);
     R.off_ring = take(sizeof(StepStats) * RING);
     R.off_part = take(sizeof(Part) * R.B);
     R.off_spart[0] = take(sizeof(SpawnPart) * R.B);
@@ -661,6 +686,8 @@ struct fq_handle {
     int have_state;
     i64 step;
     int parity;
+    i64 items, work;  // of the last step: entries and spawn records; entries and spawn attempts
+    bool items_known; // from a statistics row, else an estimate
     std::string err;
     int timing;
     double time_ms[NEV - 1];
@@ -835,6 +862,7 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
     I.n_a = R.init ? p->initiator_threshold : 0.0;
     I.coarse = q->ws + R.off_coarse;
     I.coarse_n = (int *)(q->ws + R.off_coarse_n);
+    I.res = (ResSync *)(q->ws + R.off_ref_tmp);
     I.spart[0] = (SpawnPart *)(q->ws + R.off_spart[0]);
     I.spart[1] = (SpawnPart *)(q->ws + R.off_spart[1]);
     q->d_inst = (Inst *)(q->ws + R.off_inst);
@@ -875,6 +903,8 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
     if (e != hipSuccess) { hip_fail(q, e, "fq_create: workspace initialisation"); delete q; return FQ_EHIP; }
     e = ensure_lds(km, lds_bytes(R.W, R.slots, R.init));
     if (e == hipSuccess) e = ensure_lds(ks, lds_spawn_bytes(R.cap_t));
+    if (e == hipSuccess)
+        e = ensure_lds(resident_kernel(R.W, variant(h->model, h->M, h->N, R.W, h->g, p->flags)), res_lds_bytes(R.W));
     if (e != hipSuccess) { hip_fail(q, e, "fq_create: hipFuncSetAttribute(step kernels)"); delete q; return FQ_EHIP; }
     Exec &X = q->X;
     X.W = R.W;
@@ -1082,6 +1112,9 @@ static int load_state(fq_handle *q, const u64 *sa, const double *sv, i64 n, doub
     q->have_state = 1;
     q->step = step;
     q->parity = 0;
+    // entries and attempts; an exact parent has fewer events than walkers
+    q->items = q->work = (i64)std::min(1e15, 2.0 * (double)n + cc.norm);
+    q->items_known = false;
     q->ref[0] = ref_addr[0];
     q->ref[1] = W == 2 ? ref_addr[1] : 0;
     q->yref = ref_val;
@@ -1108,6 +1141,91 @@ int fq_kernel_time(fq_handle *q, double *ms, int32_t n, int64_t *steps, int32_t 
     return FQ_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Resident steps (fq_resident.hpp) for a set of instances.
+struct ResPlan {
+    int lg = 0, lg_grid = 0;  // workgroups of an instance and per instance of the grid (log2)
+};
+
+// Entries and spawn attempts per workgroup that a plan aims at on one XCD;
+// entries and records per workgroup above which a launch ends, so that the
+// next one takes more workgroups.  A step of the 12/12 ring under early
+// compression at 1e4 walkers (1.7e4 entries and attempts): 11.9 us at 512 a
+// workgroup (G = 32), 12.3 at 1024, 19.8 at 2100, 36 with the step kernels.
+// Beyond one XCD the exchange costs more than the work of a workgroup: the
+// same ring at 1e5 walkers (1.4e5 items) takes 27.7 us with 64 workgroups,
+// 35 with 256, 43 with the step kernels.
+constexpr i64 RES_AIM = 512;
+i64 res_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
+// wall-clock ticks (100 MHz) a workgroup waits for the others: 5 ms
+constexpr u64 RES_PATIENCE = 500000;
+// steps of a launch of the step kernels while the size of a step is a guess
+constexpr i64 RES_GUESS_STEPS = 64;
+
+// Whether the instances can be stepped by resident workgroups: all of them
+// on the GPU at once (one per CU, RES_MAXG together), no more items than the
+// hashes of the largest instance's workgroups hold, and no diagnostics (the
+// step kernels record the dumps, the phase clocks and the kernel times).
+// Larger steps keep the step kernels: at RES_MAXG workgroups the barrier
+// takes 9 us and the LDS hashes hold 7.9e5 items, where a step of the four
+// kernels takes about 90 us.
+bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
+{
+    if (n < 1 || n > RES_MAXG) return false;
+    for (int i = 0; i < n; i++)
+        if (h[i]->timing || h[i]->R.B > RES_MAXB ||
+            (h[i]->p.flags & (FQ_FLAG_DUMP_SPAWNS | FQ_FLAG_DUMP_MERGED | FQ_FLAG_PHASE_TIMING)))
+            return false;
+    bool fits = false;
+    for (int lg = 0; lg <= 8; lg++) {
+        int grid = 0;
+        bool aim = true, most = true;
+        for (int i = 0; i < n; i++) {
+            const int own = res_log2_groups(lg, h[i]->R.log2B);
+            grid = std::max(grid, own);
+            aim = aim && h[i]->work <= (RES_AIM << own);
+            most = most && h[i]->items <= (res_most(h[i]->R.W) << own);
+        }
+        // one XCD holds 32 workgroups, all of them RES_MAXG
+        if (grid <= 5 ? (((n + 7) / 8) << grid) > 32 : (n << grid) > RES_MAXG) break;
+        P.lg = lg;
+        P.lg_grid = grid;
+        fits = most;
+        if (aim || (most && lg >= 5)) break;
+    }
+    return fits;
+}
+
+hipError_t launch_resident(const Exec &X, const ResPlan &P, const ResStops &stops, hipStream_t s)
+{
+    int n = X.n, lg = P.lg, lg_grid = P.lg_grid, most = (int)res_most(X.W);
+    const int grid = lg_grid <= 5 ? 8 * ((n + 7) / 8 << lg_grid) : n << lg_grid;
+    u64 patience = RES_PATIENCE;
+    ResStops st = stops;
+    void *args[] = {(void *)&X.insts, (void *)&n, (void *)&lg, (void *)&lg_grid, (void *)&most, (void *)&patience, (void *)&st};
+    return hipLaunchKernel(resident_kernel(X.W, X.var), dim3(grid), dim3(RES_BS), args,
+                           res_lds_bytes(X.W), s);
+}
+
+// size of the steps to come: the last row of a launch, or more than its
+// workgroups hold when a resident launch ended early
+void note_items(fq_handle *q, const fq_step_stats &r, bool ended_early, const ResPlan *P)
+{
+    // (early compression drops attempts before they become records: about
+    // one attempt per walker)
+    q->items = q->work = r.len + r.spawns;
+    if (q->p.flags & FQ_FLAG_EARLY_COMPRESSION) q->work = std::max(q->work, r.len + (i64)r.norm);
+    q->items_known = true;
+    if (ended_early && P) q->items = std::max(q->items, (res_most(q->R.W) << res_log2_groups(P->lg, q->R.log2B)) + 1);
+}
+
+}  // namespace
+
+extern "C" {
+
 int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream)
 {
     if (!q || n_steps < 0) return FQ_EINVAL;
@@ -1119,15 +1237,25 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
     }
     hipLaunchKernelGGL(k_set_stop, dim3(1), dim3(64), 0, s, q->X.insts, 1, (i64)n_steps);
     i64 done = 0;
+    bool again = true;  // resident steps are worth another launch
     while (done < n_steps) {
-        const i64 chunk = std::min<i64>(RING, n_steps - done);
-        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, q->X.insts, 1);
+        ResPlan plan;
+        const bool resident = again && plan_resident(&q, 1, plan);
+        i64 chunk = std::min<i64>(RING, n_steps - done);
+        if (!resident && !q->items_known) chunk = std::min<i64>(chunk, RES_GUESS_STEPS);
+        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, q->X.insts, 1, resident ? 1 : 0);
         if (q->timing && (i64)q->ev.size() < NEV * chunk) {
             size_t old = q->ev.size();
             q->ev.resize(NEV * chunk);
             for (size_t k = old; k < q->ev.size(); k++) HIPCHK(q, hipEventCreate(&q->ev[k]));
         }
-        for (i64 k = 0; k < chunk; k++) HIPCHK(q, exec_step(q->X, s, q->timing ? &q->ev[NEV * k] : nullptr));
+        if (resident) {
+            ResStops stops = {};
+            stops.step[0] = q->step + chunk;
+            HIPCHK(q, launch_resident(q->X, plan, stops, s));
+        } else {
+            for (i64 k = 0; k < chunk; k++) HIPCHK(q, exec_step(q->X, s, q->timing ? &q->ev[NEV * k] : nullptr));
+        }
         Ctrl c;
         int rc = read_ctrl(q, c, s);
         if (rc) return rc;
@@ -1141,9 +1269,15 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
             q->launches += chunk;
         }
         const i64 completed = c.step - q->step;
-        if (completed > 0 && stats_out) {
-            HIPCHK(q, hipMemcpy(stats_out + done, q->inst.ring, sizeof(StepStats) * completed, hipMemcpyDeviceToHost));
+        if (completed > 0) {
+            // the rows, or the last one to know the size of a step
+            fq_step_stats last;
+            const i64 from = stats_out ? 0 : completed - 1;
+            fq_step_stats *to = stats_out ? stats_out + done : &last;
+            HIPCHK(q, hipMemcpy(to, q->inst.ring + from, sizeof(StepStats) * (completed - from), hipMemcpyDeviceToHost));
+            note_items(q, to[completed - from - 1], completed < chunk, resident ? &plan : nullptr);
         }
+        again = !resident || completed > 0;
         done += std::max<i64>(completed, 0);
         q->step = c.step;
         q->parity = c.parity;
@@ -1152,7 +1286,7 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
                      (c.err_bucket >= 0 ? " (bucket " + std::to_string(c.err_bucket) + ")" : "");
             return fqe_status(c.error);
         }
-        if (completed != chunk) { q->err = "step count mismatch"; return FQ_EHIP; }
+        if (completed != chunk && !resident) { q->err = "step count mismatch"; return FQ_EHIP; }
         if (c.first_inexact) q->err = inexact_note(c.first_inexact);
     }
     return FQ_OK;
@@ -1406,6 +1540,84 @@ hipError_t launch_overlap(const OvRun &ov, hipStream_t s)
     return e;
 }
 
+// After a launch of a group: the control blocks, and for every instance its
+// completed steps, rows (appended at (*rows)[j] and advanced, if not null)
+// and error (the first one to *failed, err and rc).
+int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, const ResPlan *plan, const ResStops *stops,
+                  int *failed, std::string &err, int &rc)
+{
+    const Exec &X = G.X;
+    hipLaunchKernelGGL(k_gather_ctrl, dim3(std::min(X.n, 1024)), dim3(64), 0, s, X.insts, X.n, G.d_ctrl_out);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(G.ctrl.data(), G.d_ctrl_out, sizeof(Ctrl) * X.n, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+    for (int j = 0; j < X.n; j++) {
+        fq_handle *q = G.h[j];
+        const Ctrl &c = G.ctrl[j];
+        const i64 completed = c.step - q->step;
+        if (completed > 0) {
+            fq_step_stats last;
+            const bool all = rows && rows[j];
+            const i64 from = all ? 0 : completed - 1;
+            fq_step_stats *to = all ? rows[j] : &last;
+            e = hipMemcpy(to, q->inst.ring + from, sizeof(StepStats) * (completed - from), hipMemcpyDeviceToHost);
+            if (e != hipSuccess) { err = std::string("group rows: ") + hipGetErrorString(e); return FQ_EHIP; }
+            note_items(q, to[completed - from - 1], plan && c.step < std::min(c.stop_step, stops->step[j]), plan);
+            if (all) rows[j] += completed;
+        }
+        q->step = c.step;
+        q->parity = c.parity;
+        if (c.error && rc == FQ_OK) {
+            q->err = std::string(fqe_name(c.error)) + " at step " + std::to_string(c.step + 1) +
+                     (c.err_bucket >= 0 ? " (bucket " + std::to_string(c.err_bucket) + ")" : "");
+            err = q->err;
+            rc = fqe_status(c.error);
+            if (failed) *failed = j;
+        }
+    }
+    return FQ_OK;
+}
+
+// Resident steps of every instance of G up to `steps` more (or its stop
+// step), in as many launches as the growth of the instances takes.  The
+// steps left by an instance whose workgroups did not get onto the GPU
+// together, or outgrew them, are made by its own step kernels.
+int group_resident(Group &G, ResPlan plan, i64 steps, fq_step_stats **rows, hipStream_t s, int *failed,
+                   std::string &err, int &rc)
+{
+    const Exec &X = G.X;
+    ResStops stops = {};
+    for (int j = 0; j < X.n; j++) stops.step[j] = G.h[j]->step + steps;
+    for (;;) {
+        std::vector<i64> before(X.n);
+        for (int j = 0; j < X.n; j++) before[j] = G.h[j]->step;
+        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 1);
+        hipError_t e = launch_resident(X, plan, stops, s);
+        if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+        int hr = group_collect(G, rows, s, &plan, &stops, failed, err, rc);
+        if (hr) return hr;
+        bool left = false, stuck = false;
+        for (int j = 0; j < X.n; j++) {
+            const Ctrl &c = G.ctrl[j];
+            if (c.error || c.step >= std::min(c.stop_step, stops.step[j])) continue;
+            left = true;
+            stuck = stuck || c.step == before[j];
+        }
+        if (!left) return FQ_OK;
+        if (!stuck && plan_resident(G.h.data(), X.n, plan)) continue;
+        for (int j = 0; j < X.n; j++) {
+            const Ctrl &c = G.ctrl[j];
+            const i64 k = c.error ? 0 : std::min(c.stop_step, stops.step[j]) - c.step;
+            if (k <= 0) continue;
+            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0);
+            for (i64 i = 0; i < k && e == hipSuccess; i++) e = exec_step(G.h[j]->X, s, nullptr);
+            if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+        }
+        return group_collect(G, rows, s, nullptr, nullptr, failed, err, rc);
+    }
+}
+
 // Runs `steps` steps of every instance of G (an instance that has failed or
 // reached its stop step does no work).  When rows is given, the statistics
 // rows of grid position j are appended at (*rows)[j] (advanced), if not
@@ -1420,47 +1632,32 @@ int group_steps(Group &G, i64 steps, fq_step_stats **rows, hipStream_t s, int *f
     int rc = FQ_OK;
     while (launched < steps && rc == FQ_OK) {
         const i64 chunk = std::min<i64>(RING, steps - launched);
-        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n);
-        hipError_t e = hipGetLastError();
-        for (i64 k = 0; k < chunk && e == hipSuccess; k++) {
-            e = exec_step(X, s, nullptr, gs);
-            if (e == hipSuccess && ov) e = launch_overlap(*ov, s);
-        }
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_gather_ctrl, dim3(std::min(X.n, 1024)), dim3(64), 0, s, X.insts, X.n, G.d_ctrl_out);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess) e = hipMemcpyAsync(G.ctrl.data(), G.d_ctrl_out, sizeof(Ctrl) * X.n, hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
-        if (ov) {
-            i64 done = chunk;
-            for (int j = 0; j < X.n; j++) done = std::min<i64>(done, G.ctrl[j].step - G.h[j]->step);
-            if (done > 0) {
-                e = hipMemcpy(ov->out, ov->O.ring, sizeof(double) * ov->O.P * done, hipMemcpyDeviceToHost);
-                if (e != hipSuccess) { err = std::string("overlap rows: ") + hipGetErrorString(e); return FQ_EHIP; }
-                ov->out += ov->O.P * done;
+        ResPlan plan;
+        int hr;
+        if (!ov && !gs && plan_resident(G.h.data(), X.n, plan)) {
+            hr = group_resident(G, plan, chunk, rows, s, failed, err, rc);
+        } else {
+            std::vector<i64> before(X.n);
+            for (int j = 0; j < X.n; j++) before[j] = G.h[j]->step;
+            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 0);
+            hipError_t e = hipGetLastError();
+            for (i64 k = 0; k < chunk && e == hipSuccess; k++) {
+                e = exec_step(X, s, nullptr, gs);
+                if (e == hipSuccess && ov) e = launch_overlap(*ov, s);
+            }
+            if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+            hr = group_collect(G, rows, s, nullptr, nullptr, failed, err, rc);
+            if (ov && !hr) {
+                i64 done = chunk;
+                for (int j = 0; j < X.n; j++) done = std::min<i64>(done, G.ctrl[j].step - before[j]);
+                if (done > 0) {
+                    e = hipMemcpy(ov->out, ov->O.ring, sizeof(double) * ov->O.P * done, hipMemcpyDeviceToHost);
+                    if (e != hipSuccess) { err = std::string("overlap rows: ") + hipGetErrorString(e); return FQ_EHIP; }
+                    ov->out += ov->O.P * done;
+                }
             }
         }
-        for (int j = 0; j < X.n; j++) {
-            fq_handle *q = G.h[j];
-            const Ctrl &c = G.ctrl[j];
-            const i64 completed = c.step - q->step;
-            if (completed > 0 && rows && rows[j]) {
-                e = hipMemcpy(rows[j], q->inst.ring, sizeof(StepStats) * completed, hipMemcpyDeviceToHost);
-                if (e != hipSuccess) { err = std::string("group rows: ") + hipGetErrorString(e); return FQ_EHIP; }
-                rows[j] += completed;
-            }
-            q->step = c.step;
-            q->parity = c.parity;
-            if (c.error && rc == FQ_OK) {
-                q->err = std::string(fqe_name(c.error)) + " at step " + std::to_string(c.step + 1) +
-                         (c.err_bucket >= 0 ? " (bucket " + std::to_string(c.err_bucket) + ")" : "");
-                err = q->err;
-                rc = fqe_status(c.error);
-                if (failed) *failed = j;
-            }
-        }
+        if (hr) return hr;
         launched += chunk;
     }
     return rc;

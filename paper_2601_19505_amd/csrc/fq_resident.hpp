@@ -1,0 +1,840 @@
+// fq_resident.hpp -- many FCIQMC steps of a small instance in one launch.
+//
+// A step of a few thousand entries takes a few microseconds of work, but as
+// four launches it took 32 to 45 us: every kernel starts with cold
+// instruction and data caches, reads its descriptor, counts and data in
+// dependent round trips of about 1 us each, and fills its LDS tables anew.
+// Here G = 2^lg workgroups stay on the GPU and run step after step.
+// Workgroup g owns B/G consecutive hash buckets of the instance.  A step is:
+//   merge the own buckets in one LDS hash (the rules of merge_bucket), write
+//   the survivors to table[1-p] and keep them in LDS, spawn from there into
+//   the bucket slabs of every workgroup (slab[1-p]); then one barrier of the
+//   G workgroups, after which each of them sums the G partial norms and
+//   computes the same shift.
+// Tables, slabs, counts and statistics in device memory are after every step
+// what the step kernels would have left, up to the order of entries in a
+// bucket, so either path continues the other's state.
+//
+// The barrier needs all G workgroups on the GPU at once.  A gate ensures
+// that before anything is written: every workgroup counts itself in and
+// waits for the last one, which opens the gate; a workgroup that has waited
+// too long closes it instead (one compare-and-swap decides).  Behind a
+// closed gate every workgroup returns, the instance has made no step, and the
+// host steps it with the step kernels.  Behind an open gate every workgroup
+// is running, so each later barrier ends.
+//
+// The code is kept small (loops are rolled, every building block is inlined
+// once): a step runs through all of it once, and the instruction cache of
+// 64 KiB serves two CUs.  With 67 KB of unrolled code a step of 900 attempts
+// took 14.7 us, most of it instruction fetches.
+//
+// Exchange.  What another workgroup reads (records, counts, partial sums) is
+// read with agent-scope loads.  An instance of up to 32 workgroups is placed
+// on one XCD (workgroups go round robin to the 8 XCDs); when the gate finds
+// all of them on one, their common L2 is the meeting point, and a barrier
+// needs no cache maintenance.  Otherwise one wave writes the L2 back at each
+// barrier (agent release), once every wave has waited for its own stores.
+// Measured per step with 1024 records of 12 bytes from every workgroup to all
+// others: 1.4 to 1.6 us on one XCD at 2 to 16 workgroups, 2.2 at 32; on all
+// XCDs with the write back 2.2 to 3.3 us up to 32, 7 at 64, 11 at 128 and 21
+// at 256, of which the barrier alone is 3, 5 and 9.  Fences by every wave
+// instead of one: 6 to 115 us.
+#pragma once
+#include "fq_step.hpp"
+
+namespace fq {
+
+constexpr int RES_BS = 1024;      // threads of a workgroup: one workgroup per CU
+// slots of its LDS hash, by address words
+template <int W> struct ResSlots { static constexpr int N = W == 2 ? 2048 : 4096; };
+constexpr int RES_MAXG = 256;     // workgroups of all instances of a launch: the CUs
+constexpr int RES_MAXB = 1024;    // buckets of an instance: LDS counters of the spawn records
+constexpr int RES_MAXK = 64;      // buckets of a workgroup: one wave scans their counts
+
+// Partial sums of one workgroup for one step, and what it knows of the next.
+// Every workgroup reads the first four words of all parts, workgroup 0 the
+// rest as well.
+struct ResPart {
+    u64 norm[2];
+    u64 items;    // entries from bit 40; records of the spawn pass for the next step below
+    u64 state;    // bit 0: some sum was rounded first, bit 1: the step failed; from bit 8 the
+                  // most distinct addresses in a bucket; from bit 32 exact parents of the spawn pass
+    u64 hproj[2], vproj[2];
+};
+
+// Exchange area of one instance, zero before the launch.  The parts are
+// double buffered by step parity: a workgroup can be at most one barrier
+// ahead of the slowest reader.
+struct ResSync {
+    u32 arrived, gate, xccs, pad0[29];  // xccs: mask of the XCDs its workgroups run on
+    u32 count, pad1[31];
+    ResPart part[2][RES_MAXG];
+};
+
+// LDS: the hash; slot indices of its occupied slots (before them the marks
+// of the initiator rule) and of the survivors; attempt offsets of the
+// survivors; counters of the spawn records; then small tables.
+template <int W> struct ResLds {
+    static constexpr int N = ResSlots<W>::N;
+    static constexpr int LIST = N * (W == 2 ? 36 : 24), LIVE = LIST + 2 * N, OFF = LIVE + 2 * N, CNT = OFF + 4 * N,
+                         BASE = CNT + 4 * RES_MAXB, MISC = BASE + 4 * RES_MAXB, LUT = MISC + 64 * 8, TRI = LUT + 2048,
+                         RED = TRI + 2 * TRI_N, WORDS = RED + 8 * 20, BYTES = WORDS + 7 * 4 * RES_MAXK;
+    static_assert(BYTES + 512 <= 160 * 1024, "the LDS of one CU, with the kernel's own words");
+};
+
+template <class X> __device__ __forceinline__ X res_load(const X *p)
+{
+    return __hip_atomic_load(gmem(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// a spawn record that another workgroup wrote
+template <int W> __device__ __forceinline__ void res_load_rec(int rec, const char *base, i64 i, u64 &a0, u64 &a1, double &v)
+{
+    a1 = 0;
+    if (W == 2) {
+        const u64 *r = (const u64 *)base + 3 * i;
+        a0 = res_load(r);
+        a1 = res_load(r + 1);
+        v = bitsd(res_load(r + 2));
+    } else if (rec == 12) {
+        const u32 *r = (const u32 *)base + 3 * i;
+        a0 = res_load(r);
+        v = bitsd(((u64)res_load(r + 2) << 32) | res_load(r + 1));
+    } else {
+        const u64 *r = (const u64 *)base + 2 * i;
+        a0 = res_load(r);
+        v = bitsd(res_load(r + 1));
+    }
+}
+
+// Whether every workgroup of the instance is on the GPU, or else the instance
+// is not stepped here: the same answer in every workgroup.  `local`: they
+// share an XCD.
+__device__ __forceinline__ bool res_gate(ResSync *Y, int G, u64 patience, int &local)
+{
+    const u32 xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));  // hardware register 20 (XCC_ID), bits 0 .. 3
+    u32 zero = 0;
+    __hip_atomic_fetch_or(&Y->xccs, 1u << xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__hip_atomic_fetch_add(&Y->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (u32)G - 1)
+        __hip_atomic_compare_exchange_strong(&Y->gate, &zero, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    const u64 t0 = wall_clock64();
+    u32 s;
+    while ((s = __hip_atomic_load(&Y->gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+        if (wall_clock64() - t0 > patience) {
+            zero = 0;
+            __hip_atomic_compare_exchange_strong(&Y->gate, &zero, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    const u32 m = __hip_atomic_load(&Y->xccs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    local = (m & (m - 1)) == 0;
+    return s == 1;
+}
+
+// Barrier number `round` (from 1) of the G workgroups of an instance: what
+// any of them stored before it, all of them read behind it with agent-scope
+// loads.
+__device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, bool local)
+{
+    if (G == 1) {
+        __syncthreads();
+        return;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached the L2
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (!local) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        __hip_atomic_fetch_add(&Y->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (__hip_atomic_load(&Y->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (u32)G * round) {}
+    }
+    __syncthreads();
+}
+
+// Exclusive scan of x over the workgroup; tmp: 16 words.  One barrier.
+__device__ __forceinline__ u64 res_scan(u64 x, u64 *tmp, u64 &total)
+{
+    static_assert(RES_BS / 64 == 16, "one lane of a row per wave");
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 in = wave_scan(x);
+    if (lane == 63) tmp[wid] = in;
+    __syncthreads();
+    const u64 w = row_scan(tmp[lane & 15]);
+    total = lane_value(w, 15);
+    return in - x + (wid ? lane_value(w, wid - 1) : 0);
+}
+
+// The A attempts of the nS survivors (hash slots list[i], attempts before
+// survivor i in off[i]) for step spawn_step, straight into the bucket slabs
+// of parity out_par.  The step kernel cuts the attempts of a bucket into
+// units of four of one parent, to save instructions; here a few hundred
+// attempts meet 1024 threads, and the length of the chain counts: the
+// attempts of all parents, exact and stochastic, are enumerated flat, one per
+// thread and round, each with its own parent search (four ways at a time)
+// and Philox block.  cnt[t], base[t]: records of the round for bucket t
+// (cnt starts at 0) and their place in its slab, from own[t] (all records so
+// far) when this workgroup is alone, else from one global atomic.  misc[60]
+// counts the records of early compression.
+template <int W, int MODEL, bool EARLY>
+__device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, const int out_par, const bool alone,
+                                               const u32 spawn_step, const int nS, const i64 A,
+                                               const unsigned short *list, const u32 *off, int *cnt, int *base,
+                                               int *own, const unsigned char *lut, const unsigned short *tri)
+{
+    typedef typename AddrOf<W>::T T;
+    constexpr int BS = RES_BS;
+    const int tid = threadIdx.x;
+    const bool narrow = MODEL == 1 || (W == 1 && I.mc.nb <= 32);
+    int top = 1;
+    while (4 * top < nS) top *= 4;
+#pragma unroll 1
+    for (i64 from = 0; from < A; from += BS) {
+        T d = AddrOf<W>::make(0, 0);
+        double v = 0.0;
+        int t = -1, rank = 0;  // bucket, rank in the round
+        bool ni = false;
+        // (wave 0 takes the last attempts: it has the row to write)
+        const i64 x = from + ((tid + BS - 64) & (BS - 1));
+        if (x < A) {
+            // the last survivor whose first attempt is at or before x
+            int w = 0;
+#pragma unroll 1
+            for (int stp = top; stp > 0; stp >>= 2) {
+                const int i1 = w + stp, i2 = i1 + stp, i3 = i2 + stp;
+                const u32 o1 = off[min(i1, nS - 1)], o2 = off[min(i2, nS - 1)], o3 = off[min(i3, nS - 1)];
+                w = i3 < nS && o3 <= (u32)x ? i3 : i2 < nS && o2 <= (u32)x ? i2 : i1 < nS && o1 <= (u32)x ? i1 : w;
+            }
+            const u32 k = (u32)x - off[w], n = (w + 1 < nS ? off[w + 1] : (u32)A) - off[w];
+            const int s = list[w];
+            const u64 a0 = L.k0[s], a1 = W == 2 ? L.k1[s] : 0;
+            const double c = bitsd(L.lo[s]);
+            const T a = AddrOf<W>::make(a0, a1);
+            double h;
+            if constexpr (MODEL == 0 || MODEL == 3) {
+                const int m = (MODEL == 0 ? 2 : I.mc.ndir) * (narrow ? popc(run_starts((u32)a0)) : popc(run_starts(a)));
+                const bool exact = fabs(c) >= I.t_rel * (double)m;
+                int e = (int)k;
+                if (!exact) e = (int)pick(rword(draw(I.seed, a0, a1, spawn_step, 0u, k >> 2), (int)(k & 3u)), (u32)m);
+                // in 32-bit words when the address fits them
+                auto entry = [&](auto y) {
+                    const auto st = run_starts(y);
+                    if constexpr (MODEL == 0) {
+                        return real_entry(I.mc, y, st, popc(st), e, h);
+                    } else {
+                        int kd;
+                        const auto z = lat_entry(I.mc, y, st, popc(st), e, h, kd, lut);
+                        h = h * gmem(I.mc.gz)[I.mc.N + kd];
+                        return z;
+                    }
+                };
+                if (narrow) d = AddrOf<W>::make((u64)entry((u32)a0), 0);
+                else d = entry(a);
+                v = (-(I.dtau * h)) * c;
+                if (!exact) v = v * ((double)m / (double)n);
+            } else {
+                const i64 m = narrow ? mom_col_size<u32>(I.mc, (u32)a0) : mom_col_size(I.mc, a);
+                if (fabs(c) >= I.t_rel * (double)m) {
+                    if (narrow) d = AddrOf<W>::make((u64)mom_column_entry<u32>(I.mc, (u32)a0, (int)k, h, lut), 0);
+                    else d = mom_column_entry(I.mc, a, (int)k, h, lut);
+                    v = (-(I.dtau * h)) * c;
+                } else {
+                    const R4 rr = draw(I.seed, a0, a1, spawn_step, 0u, k >> 1);
+                    const u32 x0 = (k & 1u) ? rr.z : rr.x, x1 = (k & 1u) ? rr.w : rr.y;
+                    int R, P;
+                    if constexpr (MODEL == 1 && W == 1) {
+                        const MomCtx32 y = mom_ctx32(I.mc, (u32)a0);
+                        P = y.P;
+                        d = AddrOf<W>::make((u64)mom_draw31(I.mc, y, x0, x1, h, R, lut, tri), 0);
+                    } else {
+                        const MomCtx<T> y = mom_ctx<T>(I.mc, a);
+                        P = y.P;
+                        d = mom_draw<T>(I.mc, y, x0, x1, h, R, lut);
+                    }
+                    v = ((-(I.dtau * h)) * c) * ((double)((i64)P * R) / (double)n);
+                }
+            }
+            ni = !(fabs(c) > I.n_a);
+            if (EARLY && fabs(v) < I.theta)
+                v = compress1(v, I.theta, draw(I.seed, a0, a1, spawn_step, 4u + (k >> 28), k & 0x0fffffffu).x);
+            if (!EARLY || v != 0.0) {
+                t = (int)bucket_index(d, I.log2B, I.mc.nb <= 32);
+                rank = atomicAdd(&cnt[t], 1);
+            }
+        }
+        __syncthreads();
+        for (int b = tid; b < I.B; b += BS) {
+            const int c = cnt[b];
+            if (c) {
+                if (alone) {
+                    base[b] = own[b];
+                    own[b] += c;
+                } else {
+                    base[b] = gatomic_add(&I.slab_n[out_par][b], c);
+                }
+                cnt[b] = 0;
+                if (EARLY) atomicAdd((unsigned long long *)&L.misc[60], (unsigned long long)c);
+            }
+        }
+        __syncthreads();
+        if (t >= 0) {
+            const i64 pos = (i64)base[t] + rank;
+            const u64 fl = ni ? I.iflag : 0ull;
+            const T df = AddrOf<W>::make(W == 1 ? word0(d) | fl : word0(d), W == 2 ? word1(d) | fl : 0ull);
+            if (pos < I.cap_s) store_rec<W>(I.rec, I.slab[out_par], (i64)t * I.cap_s + pos, df, v);
+            else fail(I, L, FQE_CAP_SLAB, t);
+        }
+    }
+}
+
+// Steps of instance I up to last_step by workgroup g of G = 2^lg (every
+// workgroup of the instance makes the same number).  Stops early at the
+// instance's stop step, at an error, and after a step that leaves more than
+// max_items entries and records to merge.
+template <int W, int MODEL, bool EARLY>
+__device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const int g, const int lg,
+                                               const i64 last_step, const i64 max_items, const u64 patience,
+                                               char *smem)
+{
+    typedef typename AddrOf<W>::T T;
+    typedef ResLds<W> M;
+    constexpr int BS = RES_BS, SLOTS = ResSlots<W>::N;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = 1 << lg;
+    const int K = I.B >> lg;   // buckets of this workgroup, at most RES_MAXK
+    const int bA = g * K;
+    Ctrl *ctrl = I.ctrl;
+
+    __shared__ int s_go, s_fail, s_full, s_len, s_load, s_inx, s_list, s_ex, s_local;
+    __shared__ double s_state[2];  // shift and norm after the step
+    __shared__ i64 s_sp;
+    Lds L;
+    L.k0 = (u64 *)smem;
+    L.k1 = L.k0 + SLOTS;
+    L.lo = L.k0 + SLOTS * W;
+    L.hi = L.lo + SLOTS;
+    L.state = (u32 *)(L.hi + SLOTS);
+    L.misc = (i64 *)(smem + M::MISC);
+    L.occ = (unsigned char *)(smem + M::LIST);
+    L.failed = &s_fail;
+    L.full = &s_full;
+    unsigned short *list = (unsigned short *)(smem + M::LIST), *live = (unsigned short *)(smem + M::LIVE);
+    u32 *off = (u32 *)(smem + M::OFF);
+    int *cnt = (int *)(smem + M::CNT), *base = (int *)(smem + M::BASE);
+    unsigned char *lut = (unsigned char *)(smem + M::LUT);
+    unsigned short *tri = (unsigned short *)(smem + M::TRI);
+    // 128-bit sums of the workgroup, ||c||_1, y.Hc, y.c, as 32-bit limbs in
+    // 64-bit words (adds without a carry); from word 12 the sums of a row
+    u64 *red = (u64 *)(smem + M::RED);
+    int *pt = (int *)(smem + M::WORDS), *ps = pt + 2 * RES_MAXK;  // own buckets: prefix sums of the entries, the records
+    int *keep = ps + 2 * RES_MAXK, *used = keep + RES_MAXK;  // survivors, distinct addresses
+    int *own = used + RES_MAXK;                   // G = 1: records written, per bucket (B <= RES_MAXK then)
+    const bool init = I.iflag != 0;
+    const bool narrow = MODEL == 1 || (W == 1 && I.mc.nb <= 32);
+
+    // the state before this launch, read before the gate: no workgroup
+    // changes it until all of them have passed
+    i64 n = ctrl->step;
+    int p = ctrl->parity;
+    double S = ctrl->shift, N0 = ctrl->norm;
+    const i64 stop = min(ctrl->stop_step, last_step);
+    const i64 ring_base = ctrl->ring_base;
+    if (tid == 0) s_go = !halted(ctrl);
+    __syncthreads();
+    if (!s_go) return;
+    if (G > 1) {
+        __syncthreads();
+        if (tid == 0) s_go = res_gate(Y, G, patience, s_local);
+        __syncthreads();
+        if (!s_go) return;
+    }
+    if (n >= stop) return;
+    const bool local = G == 1 || s_local;
+    for (int i = tid; i < 2048; i += BS) lut[i] = select_lut_entry(i);
+    if (MODEL == 1 || MODEL == 2) tri_fill(tri, tid, BS);
+    for (int t = tid; t < I.B; t += BS) cnt[t] = 0;
+    // the reference entries of the own buckets, one per thread from the last
+    // thread down, if there are no more than threads
+    const int ref0 = I.ref_off[bA], nref = I.ref_off[bA + K] - ref0;
+    const bool ref_held = nref <= BS;
+    u64 f0 = 0, f1 = 0;
+    double fh = 0.0;
+    if (ref_held && BS - 1 - tid < nref) {
+        f0 = gmem(I.ref_a[0])[ref0 + BS - 1 - tid];
+        if (W == 2) f1 = gmem(I.ref_a[1])[ref0 + BS - 1 - tid];
+        fh = gmem(I.ref_h)[ref0 + BS - 1 - tid];
+    }
+    // workgroup 0 writes the rows: counts of the spawn pass before the first step
+    i64 row_ex = 0, row_st = 0, row_sp = 0;
+    u32 row_inx = 0;
+    i64 first_inx = 0;
+    int max_load = 0;
+    if (g == 0 && wid == 0) {
+        for (int b = lane; b < I.B; b += 64) {
+            const SpawnPart x = I.spart[(n + 1) & 1][b];
+            row_ex += x.exact;
+            row_st += x.inexact;
+            row_sp += x.spawns;
+        }
+        row_ex = (i64)lane_value(wave_scan((u64)row_ex), 63);
+        row_st = (i64)lane_value(wave_scan((u64)row_st), 63);
+        row_sp = (i64)lane_value(wave_scan((u64)row_sp), 63);
+        row_inx = ctrl->inexact_in;
+        first_inx = ctrl->first_inexact;
+    }
+
+    u32 round = 0;
+    int slots = 0;           // of the hash: from the distinct addresses of the step before
+    bool concluded = true;   // no step waits for its shift
+    bool held = false;       // the survivors are in registers, at most one per thread: hc = 0 or (h0, h1), hc
+    u64 h0 = 0, h1 = 0;
+    double hc = 0.0;
+    bool row_due = false;    // wave 0 of workgroup 0: the row of step n is to be written
+    auto write_row = [&]() {
+        const bool flagged = red[18] || row_inx;
+        // one conversion: y.Hc in lane 0, y.c in the others
+        const double e = from_fixed(red[lane == 0 ? 12 : 14], red[lane == 0 ? 13 : 15]);
+        const double hp = lane_value(e, 0), vp = lane_value(e, 1);
+        const i64 len = (i64)(red[17] >> 40), row = n - ring_base;
+        if (lane == 0 && row >= 0 && row < I.ring_cap) {
+            StepStats &R = I.ring[row];
+            R.step = n;
+            R.len = len;
+            R.exact_steps = row_ex;
+            R.inexact_steps = row_st;
+            R.spawns = row_sp;
+            R.shift = S;
+            R.norm = N0;
+            R.hproj = hp;
+            R.vproj = vp;
+            R.flags = flagged ? ROW_INEXACT : 0;
+        }
+        row_inx = 0;
+        if (flagged && first_inx == 0) first_inx = n;
+        row_ex = (i64)red[16];
+        row_st = len - row_ex;
+        row_sp = (i64)(red[17] & (((u64)1 << 40) - 1));
+        row_due = false;
+    };
+    s_go = 2;
+    for (;;) {
+        // ------------------------------------------------ 0. what the other workgroups left
+        // wave 0: the parts of the step that waits for its shift, summed over
+        // the workgroups lane, lane + 64, ..
+        u64 nl = 0, nh = 0, both = 0, state = 0;
+        const bool split = !concluded;
+        const ResPart *part = Y->part[(n + 1) & 1];
+        if (split && wid == 0) {
+#pragma unroll 1
+            for (int k = lane; k < G; k += 64) {
+                const u64 x0 = res_load(&part[k].norm[0]), x1 = res_load(&part[k].norm[1]),
+                          x2 = res_load(&part[k].items), x3 = res_load(&part[k].state);
+                add128(nl, nh, x0, x1);
+                both += x2;
+                // flags joined, largest load, sum of exact parents
+                state = (state & 3) | (x3 & 3) | (max(state & 0xffffff00u, x3 & 0xffffff00u)) |
+                        (((state >> 32) + (x3 >> 32)) << 32);
+            }
+        }
+        // wave 1: the counts of the own buckets
+        const int p1 = concluded ? p : 1 - p;  // parity of the state to advance
+        if (wid == 1) {
+            int x = 0, y = 0;
+            if (lane < K) {
+                x = res_load(&I.tab_n[p1][bA + lane]);
+                y = min(res_load(&I.slab_n[p1][bA + lane]), (int)I.cap_s);
+            }
+            const u64 xy = wave_scan(((u64)x << 32) | (u32)y);
+            if (lane < K) {
+                pt[lane + 1] = (int)(xy >> 32);
+                ps[lane + 1] = (int)(u32)xy;
+                keep[lane] = used[lane] = own[lane] = 0;
+            }
+            if (lane < 12) red[lane] = 0;
+            if (lane == 0) {
+                pt[0] = ps[0] = 0;
+                s_fail = s_full = 0;
+                s_len = s_load = s_inx = s_ex = 0;
+                s_sp = 0;
+            }
+        }
+        int inx = 0, np = 0, distinct = 0;
+        // Batches of consecutive buckets whose entries and records together
+        // fit the hash; a bucket larger than that is a batch alone (its
+        // distinct addresses usually fit).  The first batch is cleared for
+        // while the counts arrive, and merged again if it does not fit.
+        for (int k0 = 0, k1 = 0, redo = 0; k0 < K;) {
+            const bool all = k0 > 0 || redo;
+            if (all || slots == 0) slots = SLOTS;
+            if (all || wid > 1) {
+#pragma unroll 1
+                for (int s = all ? tid : tid - 128; s < slots; s += all ? BS : BS - 128) {
+                    L.k0[s] = EMPTY;
+                    if (W == 2) { L.k1[s] = EMPTY; L.state[s] = 0u; }
+                    L.lo[s] = 0;
+                    L.hi[s] = 0;
+                }
+            }
+            if (tid == 64) s_list = s_full = 0;
+            __syncthreads();
+            k1 = K;
+            if (pt[K] - pt[k0] + ps[K] - ps[k0] > SLOTS) {
+                k1 = k0 + 1;
+                while (k1 < K && pt[k1 + 1] - pt[k0] + ps[k1 + 1] - ps[k0] <= SLOTS) k1++;
+            }
+            L.mask = slots - 1;
+            // ------------------------------------------------ 1. merge
+            // The records first; meanwhile wave 0, which takes no items,
+            // concludes the step before, whose shift scales the survivors:
+            // s_go = 0 that step failed, 1 it was the last, 2 go on.  With
+            // the initiator rule the survivors come first.
+            const bool waits = split && !concluded;
+            if (waits && wid == 0) {
+                const int last = G <= 16 ? 15 : 63;
+                if (G > 1) {
+                    row_scan128(nl, nh);
+                    both = row_scan(both);
+                    if (G > 16) {
+                        add128(nl, nh, dpp0<0x142, 0xa>(nl), dpp0<0x142, 0xa>(nh));
+                        add128(nl, nh, dpp0<0x143, 0xc>(nl), dpp0<0x143, 0xc>(nh));
+                        both += dpp0<0x142, 0xa>(both);
+                        both += dpp0<0x143, 0xc>(both);
+                    }
+                }
+                const int from = G > 1 ? last : 0;
+                nl = lane_value(nl, from);
+                nh = lane_value(nh, from);
+                both = lane_value(both, from);
+                const double N1 = from_fixed(nl, nh);
+                // lanes 0 and 1 take one logarithm each
+                const double ln = N1 > 0.0 ? det_log(N1 / (lane == 0 ? N0 : I.target)) : 0.0;
+                const double l0 = lane_value(ln, 0), l1 = lane_value(ln, 1);
+                double S1 = S;
+                if (N1 > 0.0) S1 = (S - I.zeta / I.dtau * l0) - I.xi / I.dtau * l1;
+                const bool error = __any(state & 2), diverged = !(N1 < 17592186044416.0) || !(S1 == S1);
+                const i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
+                if (lane == 0) {
+                    s_go = error || diverged ? 0 : (items > max_items || n + 1 >= stop) ? 1 : 2;
+                    s_state[0] = S1;
+                    s_state[1] = N1;
+                    if (g == 0 && !error && diverged) set_error(ctrl, FQE_DIVERGED, -1);
+                }
+            }
+#pragma unroll 1
+            for (int ph = 0; ph < 3; ph++) {
+                // 0: records, 1: table, 2: records with the initiator rule
+                if (ph == 1) {
+                    if (waits) {
+                        __syncthreads();
+                        concluded = true;
+                        if (s_go) {
+                            n++;
+                            p = p1;
+                            S = lane_value(s_state[0], 0);
+                            N0 = lane_value(s_state[1], 0);
+                        }
+                        if (s_go && g == 0 && wid == 0) {
+                            // the sums of its row, written further down
+                            u64 hl = 0, hh = 0, vl = 0, vh = 0;
+#pragma unroll 1
+                            for (int k = lane; k < G; k += 64) {
+                                const u64 x0 = res_load(&part[k].hproj[0]), x1 = res_load(&part[k].hproj[1]),
+                                          x2 = res_load(&part[k].vproj[0]), x3 = res_load(&part[k].vproj[1]);
+                                add128(hl, hh, x0, x1);
+                                add128(vl, vh, x2, x3);
+                            }
+                            wave_scan128(hl, hh);
+                            wave_scan128(vl, vh);
+                            const u64 x = wave_scan(state >> 32);
+                            const bool flagged = __any(state & 1);
+                            if (lane == 63) {
+                                red[12] = hl; red[13] = hh; red[14] = vl; red[15] = vh;
+                                red[16] = x; red[17] = both; red[18] = flagged;
+                            }
+                            max_load = max(max_load, (int)((state >> 8) & 0xffffff));
+                            row_due = true;
+                        }
+                        if (s_go != 2) break;
+                    }
+                } else {
+                    if (init != (ph == 2)) continue;
+                    if (init) {
+                        __syncthreads();
+                        for (int s = tid; s < slots; s += BS)
+                            L.occ[s] = (W == 1 ? L.k0[s] != EMPTY : L.state[s] == 2u) ? 1 : 0;
+                        __syncthreads();
+                    }
+                }
+                const bool table = ph == 1, regs = table && held;
+                if (wid == 0) continue;
+                const int *pre = table ? pt : ps;
+                const int end = pre[k1];
+                int i = pre[k0] + tid - 64;
+                bool have = regs ? hc != 0.0 : i < end;
+#pragma unroll 1
+                while (have) {
+                    u64 a0, a1 = 0;
+                    double v;
+                    bool ok = true, ni = false;
+                    int k = k0;
+                    if (regs) {
+                        a0 = h0;
+                        if (W == 2) a1 = h1;
+                        v = hc;
+                    } else {
+                        for (int hi = k1; hi - k > 1;) {
+                            const int mid = (k + hi) >> 1;
+                            if (pre[mid] <= i) k = mid;
+                            else hi = mid;
+                        }
+                        const int j = i - pre[k];
+                        const i64 b = bA + k;
+                        if (table) {
+                            const i64 e = b * I.cap_t + j;
+                            a0 = gmem(I.tab_a[p][0])[e];
+                            if (W == 2) a1 = gmem(I.tab_a[p][1])[e];
+                            v = gmem(I.tab_v[p])[e];
+                        } else {
+                            res_load_rec<W>(I.rec, I.slab[p1] + b * I.cap_s * (i64)I.rec, j, a0, a1, v);
+                            ni = ((W == 1 ? a0 : a1) & I.iflag) != 0;
+                            ok = !ni;
+                            if (W == 1) a0 &= ~I.iflag;
+                            else a1 &= ~I.iflag;
+                        }
+                    }
+                    if (table) {
+                        const T a = AddrOf<W>::make(a0, a1);
+                        double hii;
+                        if (MODEL == 0 || MODEL == 3)
+                            hii = narrow ? real_diag_runs<u32>(I.mc, (u32)a0) : real_diag_runs(I.mc, a);
+                        else hii = narrow ? mom_diag_modes<u32>(I.mc, (u32)a0) : mom_diag_modes(I.mc, a);
+                        const double gd = 1.0 + I.dtau * (S - hii);
+                        v = v * gd;
+                        if (EARLY && fabs(v) < I.theta)
+                            v = compress1(v, I.theta, draw(I.seed, a0, a1, (u32)(n + 1), 2u, 0u).x);
+                        ok = v != 0.0 || init;
+                    }
+                    lds_add_n<W, 1>(L, I, &a0, &a1, &v, &ok, bA + k, np, inx);
+                    if (init && ph == 2) lds_add_occupied<W, 1>(L, I, &a0, &a1, &v, &ni, bA + k, inx);
+                    i += BS - 64;
+                    have = !regs && i < end;
+                }
+            }
+            if (s_go != 2) break;
+            __syncthreads();
+            if (s_full && slots < SLOTS) {
+                // more addresses than expected: again with the whole hash
+                redo = 1;
+                __syncthreads();
+                continue;
+            }
+            redo = 0;
+            if (s_full && tid == 0) fail(I, L, FQE_CAP_LDS, bA + k0);
+            // ------------------------------------------------ 2. occupied slots
+            // an index of them, so that the sums, draws and conversions run
+            // on full waves
+#pragma unroll 1
+            for (int s = tid; s < slots; s += BS) {
+                const bool occ = W == 1 ? L.k0[s] != EMPTY : L.state[s] == 2u;
+                const u64 m = __ballot(occ);
+                int at = 0;
+                if (lane == 0 && m) at = atomicAdd(&s_list, __popcll(m));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
+                if (occ) list[at] = (unsigned short)s;
+            }
+            __syncthreads();
+            // ------------------------------------------------ 3. compress, survivors and their attempts
+            const u32 step1 = (u32)(n + 1);
+            const int nU = s_list, kb = k1 - k0;
+            distinct += nU;
+            held = k0 == 0 && k1 == K && nU <= BS - 64;
+            u64 sum = 0;  // survivors from bit 48, attempts below
+            u64 nlo = 0, nhi = 0;
+            int odd = 0;
+            hc = 0.0;
+#pragma unroll 1
+            for (int j0 = -64; j0 + 64 < nU; j0 += BS - 64, odd ^= 16) {
+                const bool occ = wid > 0 && j0 + tid < nU;
+                int s = 0, bl = 0, pos = 0;
+                u64 a0 = 0, a1 = 0;
+                double c = 0.0;
+                u32 att = 0;
+                if (occ) {
+                    s = list[j0 + tid];
+                    a0 = L.k0[s];
+                    if (W == 2) a1 = L.k1[s];
+                    c = from_fixed(L.lo[s], L.hi[s]);
+                    if (!EARLY && c != 0.0 && fabs(c) < I.theta)
+                        c = compress1(c, I.theta, draw(I.seed, a0, a1, step1, 1u, 0u).x);
+                    L.lo[s] = dbits(c);
+                    if (kb > 1) bl = (int)bucket_index(AddrOf<W>::make(a0, a1), I.log2B, I.mc.nb <= 32) - (bA + k0);
+                }
+                const bool alive = c != 0.0;
+                bool exact = false;
+                if (alive) {
+                    int bad = 0;
+                    spawn_info<W, MODEL>(I, AddrOf<W>::make(a0, a1), c, att, exact, bad);
+                    if (bad) fail(I, L, FQE_ATTEMPTS, bA + k0 + bl);
+                    u64 lo, hi;
+                    int ovf = 0;
+                    to_fixed(fabs(c), lo, hi, ovf, inx);
+                    add128(nlo, nhi, lo, hi);
+                }
+                {
+                    const u64 em = __ballot(exact);
+                    if (lane == 0 && em) atomicAdd(&s_ex, __popcll(em));
+                }
+                // rank inside the bucket: one LDS atomic per wave for a few
+                // buckets, else one per lane
+                if (kb <= 4) {
+#pragma unroll 1
+                    for (int b = 0; b < kb; b++) {
+                        const u64 um = __ballot(occ && bl == b), lm = __ballot(alive && bl == b);
+                        int at = 0;
+                        if (lane == 0) {
+                            if (um) atomicAdd(&used[k0 + b], __popcll(um));
+                            if (lm) at = atomicAdd(&keep[k0 + b], __popcll(lm));
+                        }
+                        at = __builtin_amdgcn_readfirstlane(at);
+                        if (alive && bl == b) pos = at + __popcll(lm & ((1ull << lane) - 1));
+                    }
+                } else {
+                    if (occ) atomicAdd(&used[k0 + bl], 1);
+                    if (alive) pos = atomicAdd(&keep[k0 + bl], 1);
+                }
+                if (alive && pos < I.cap_t) {
+                    const i64 e = (i64)(bA + k0 + bl) * I.cap_t + pos;
+                    gmem(I.tab_a[1 - p][0])[e] = a0;
+                    if (W == 2) gmem(I.tab_a[1 - p][1])[e] = a1;
+                    gmem(I.tab_v[1 - p])[e] = c;
+                }
+                u64 total;
+                const u64 at = sum + res_scan(alive ? ((u64)1 << 48) + att : 0, (u64 *)L.misc + odd, total);
+                sum += total;
+                if (alive) {
+                    live[at >> 48] = (unsigned short)s;
+                    off[at >> 48] = (u32)at;
+                }
+                h0 = a0;
+                h1 = a1;
+                hc = c;
+            }
+            if (tid == 0) L.misc[60] = 0;
+            __syncthreads();
+            const int nS = (int)(sum >> 48);
+            const i64 A = (i64)(sum & (((u64)1 << 48) - 1));
+            // ------------------------------------------------ 4. projected energy
+            u64 hlo = 0, hhi = 0, vlo = 0, vhi = 0;
+            {
+                const int e0 = I.ref_off[bA + k0], e1 = I.ref_off[bA + k1];
+#pragma unroll 1
+                for (int e = ref_held ? ref0 + BS - 1 - tid : e0 + tid; e < e1; e += BS) {
+                    if (e >= e0) {
+                        const u64 a0 = ref_held ? f0 : gmem(I.ref_a[0])[e];
+                        const u64 a1 = W == 1 ? 0 : ref_held ? f1 : gmem(I.ref_a[1])[e];
+                        const double rh = ref_held ? fh : gmem(I.ref_h)[e];
+                        const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
+                        const double cv = s >= 0 ? bitsd(L.lo[s]) : 0.0;
+#pragma unroll 1
+                        for (int r = 0; r < (e == I.ref_self ? 2 : 1); r++) {
+                            u64 lo, hi;
+                            int ovf = 0;
+                            to_fixed(r ? I.yref * cv : I.yref * (rh * cv), lo, hi, ovf, inx);
+                            if (r) add128(vlo, vhi, lo, hi);
+                            else add128(hlo, hhi, lo, hi);
+                        }
+                    }
+                    if (ref_held) break;
+                }
+            }
+            // the wave's sums, limb by limb
+            auto limbs = [&](u64 *w, u64 &lo, u64 &hi) {
+                wave_scan128(lo, hi);
+                if (lane == 63) {
+                    atomicAdd(&w[0], lo & 0xffffffffull);
+                    atomicAdd(&w[1], lo >> 32);
+                    atomicAdd(&w[2], hi & 0xffffffffull);
+                    atomicAdd(&w[3], hi >> 32);
+                }
+            };
+            if (__any((nlo | nhi) != 0)) limbs(red, nlo, nhi);
+            if (__any((hlo | hhi | vlo | vhi) != 0)) {
+                limbs(red + 4, hlo, hhi);
+                limbs(red + 8, vlo, vhi);
+            }
+            // capacities as the step kernels hold them
+            if (tid >= k0 && tid < k1) {
+                const int u = used[tid];
+                if (keep[tid] > I.cap_t) fail(I, L, FQE_CAP_TABLE, bA + tid);
+                if (u > I.slots) fail(I, L, FQE_CAP_LDS, bA + tid);
+                atomicMax(&s_load, u);
+                I.tab_n[1 - p][bA + tid] = keep[tid];
+            }
+            // ------------------------------------------------ 5. spawn for step n+2
+            if (row_due) write_row();
+            if (A < ((i64)1 << 32)) {
+                resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own, lut,
+                                                tri);
+            } else if (tid == 0) {
+                fail(I, L, FQE_CAP_SLAB, bA + k0);
+            }
+            if (tid == 0) {
+                s_len += nS;
+                s_sp += EARLY ? L.misc[60] : A;
+            }
+            k0 = k1;
+            if (k0 < K) __syncthreads();
+        }
+        if (s_go != 2) break;
+
+        // ---------------------------------------------------- 6. partial sums, barrier
+        if (__any(inx) && lane == 0) s_inx = 1;
+        // the next hash: at most 5/8 full if the addresses are no more
+        slots = 8 * distinct <= 5 * BS ? BS : 8 * distinct <= 10 * BS ? 2 * BS : SLOTS;
+        __syncthreads();
+        if (wid == 0) {
+            ResPart &x = Y->part[(n + 1) & 1][g];
+            if (lane < 3) {
+                const u64 *w = red + 4 * lane;
+                u64 *to = lane == 0 ? x.norm : lane == 1 ? x.hproj : x.vproj;
+                u64 c = w[0];
+                u64 lo = c & 0xffffffffull;
+                c = (c >> 32) + w[1];
+                lo |= c << 32;
+                c = (c >> 32) + w[2];
+                to[0] = lo;
+                to[1] = (c & 0xffffffffull) | (((c >> 32) + w[3]) << 32);
+            }
+            if (lane == 63) {
+                x.items = ((u64)s_len << 40) + (u64)s_sp;
+                x.state = (s_inx ? 1 : 0) | (s_fail ? 2 : 0) | ((u64)s_load << 8) | ((u64)s_ex << 32);
+            }
+        }
+        if (wid == 1 && lane < K) {
+            __hip_atomic_store(gmem(&I.slab_n[p][bA + lane]), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // consumed
+            if (G == 1)
+                __hip_atomic_store(gmem(&I.slab_n[1 - p][lane]), own[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            SpawnPart x{0, 0, 0, 0};
+            if (lane == 0) x = SpawnPart{s_ex, s_len - s_ex, s_sp, 0};
+            I.spart[(n + 2) & 1][bA + lane] = x;
+        }
+        res_barrier(Y, G, ++round, local);
+        concluded = false;
+    }
+    // the last completed step
+    if (g == 0 && wid == 0) {
+        if (row_due) write_row();
+#pragma unroll 1
+        for (int o = 32; o > 0; o >>= 1) max_load = max(max_load, __shfl_xor(max_load, o, 64));
+        if (lane == 0) {
+            ctrl->step = n;
+            ctrl->parity = p;
+            ctrl->shift = S;
+            ctrl->norm = N0;
+            ctrl->inexact_in = row_inx;
+            ctrl->first_inexact = first_inx;
+            if ((u32)max_load > ctrl->max_load) ctrl->max_load = (u32)max_load;
+        }
+    }
+}
+
+}  // namespace fq

@@ -121,6 +121,7 @@ struct Inst {
     double n_a;
     char *coarse;
     int *coarse_n;
+    struct ResSync *res;  // exchange area of resident steps (shares the memory of the set-state staging)
 };
 
 // Kernels never write a descriptor, so a workgroup reads its descriptor in
@@ -267,7 +268,21 @@ struct Lds {
     i64 *misc;      // scan scratch and block accumulators
     unsigned char *occ;  // initiator rule: 1 where the slot holds an address of c^(n)
     int mask;
+    // resident steps: set when this workgroup reports an error, and when the
+    // hash is full (which the caller then handles)
+    int *failed = nullptr, *full = nullptr;
 };
+
+__device__ __forceinline__ void fail(const Inst &I, const Lds &L, int code, int bucket)
+{
+    set_error(I.ctrl, code, bucket);
+    if (L.failed) *L.failed = 1;
+}
+__device__ __forceinline__ void hash_full(const Inst &I, const Lds &L, int bucket)
+{
+    if (L.full) *L.full = 1;
+    else set_error(I.ctrl, FQE_CAP_LDS, bucket);
+}
 
 // find or insert the slot of address (a0, a1); returns -1 when full
 template <int W> __device__ __forceinline__ int lds_slot(const Lds &L, u64 a0, u64 a1, u64 h, int &np)
@@ -355,7 +370,7 @@ __device__ __forceinline__ void lds_add_n(const Lds &L, const Inst &I, const u64
         if (go[e]) {
             int ovf = 0;
             to_fixed(v[e], lo[e], hi[e], ovf, inx);
-            if (ovf) { set_error(I.ctrl, FQE_DIVERGED, b); go[e] = false; }
+            if (ovf) { fail(I, L, FQE_DIVERGED, b); go[e] = false; }
         }
     }
     if (W == 1) {
@@ -374,7 +389,7 @@ __device__ __forceinline__ void lds_add_n(const Lds &L, const Inst &I, const u64
             if (go[e] && old[e] != EMPTY && old[e] != a0[e]) {
                 // collision: continue the linear probe from the next slot
                 s[e] = lds_slot<W>(L, a0[e], 0ull, (u64)(s[e] + 1), np);
-                if (s[e] < 0) { set_error(I.ctrl, FQE_CAP_LDS, b); go[e] = false; }
+                if (s[e] < 0) { hash_full(I, L, b); go[e] = false; }
             }
         }
     } else {
@@ -408,7 +423,7 @@ __device__ __forceinline__ void lds_add_n(const Lds &L, const Inst &I, const u64
                 const bool hit = st[e] == 2u && L.k0[s[e]] == a0[e] && L.k1[s[e]] == a1[e];
                 if (!hit) {
                     s[e] = lds_slot<W>(L, a0[e], a1[e], (u64)(s[e] + (st[e] == 2u ? 1 : 0)), np);
-                    if (s[e] < 0) { set_error(I.ctrl, FQE_CAP_LDS, b); go[e] = false; }
+                    if (s[e] < 0) { hash_full(I, L, b); go[e] = false; }
                 }
             }
         }
@@ -443,7 +458,7 @@ __device__ __forceinline__ void lds_add_occupied(const Lds &L, const Inst &I, co
         u64 lo = 0, hi = 0;
         int ovf = 0;
         to_fixed(v[e], lo, hi, ovf, inx);
-        if (ovf) { set_error(I.ctrl, FQE_DIVERGED, b); continue; }
+        if (ovf) { fail(I, L, FQE_DIVERGED, b); continue; }
         const u64 old = atomicAdd((unsigned long long *)&L.lo[s], (unsigned long long)lo);
         const u64 h = hi + ((old + lo) < old ? 1ull : 0ull);
         if (h) atomicAdd((unsigned long long *)&L.hi[s], (unsigned long long)h);
