@@ -295,8 +295,8 @@ class Solver:
         if cap is None:
             cap = self.table_capacity + 1024
         for _ in range(2):
-            a = np.zeros((cap, self.W), np.uint64)
-            v = np.zeros(cap, np.float64)
+            a = np.empty((cap, self.W), np.uint64)
+            v = np.empty(cap, np.float64)
             n = C.c_int64(0)
             sh = C.c_double(0)
             st = C.c_int64(0)
@@ -306,7 +306,8 @@ class Solver:
                 cap = n.value
                 continue
             self._check(rc, "fq_get_state")
-            return a[:n.value].copy(), v[:n.value].copy(), sh.value, st.value
+            # pages beyond the entries were never touched: no copy into smaller arrays
+            return a[:n.value], v[:n.value], sh.value, st.value
         raise FqError(-2, "fq_get_state: state changed size")
 
     def spawn_dump(self, cap=None):

@@ -143,46 +143,93 @@ __global__ void k_fill_i32(int *p, int n, int v)
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = v;
 }
 
-// insert host-staged entries into table[parity] and accumulate the norm
+// What the insertion of a state finds (in the staging scratch, zero before)
+struct InsertNote {
+    u64 norm[2];      // exact 1-norm
+    u32 inexact;      // some value was rounded to the fixed-point grid
+    u32 overflow;     // a bucket is full
+    u32 out_of_range; // a value is too large for the grid
+    u32 refused;      // an address or value is invalid, or an address occurs twice
+};
+
+// insert staged entries (ew words per address) into table[par], whose counts
+// are zero, checking each: N bosons in N + M - 1 bits, a finite value that is
+// not zero
 template <int W>
-__global__ __launch_bounds__(256) void k_insert(const Inst *Ip, const u64 *sa, const double *sv, i64 n)
+__global__ __launch_bounds__(256) void k_insert(const Inst *Ip, int par, const u64 *sa, const double *sv, i64 n, int ew,
+                                                InsertNote *note)
 {
-    const Inst &I = *Ip;
-    Ctrl *ctrl = I.ctrl;
-    const int p = ctrl->parity;
+    const Inst &I = const_inst(Ip);
     __shared__ u64 acc[2];
     if (threadIdx.x == 0) acc[0] = acc[1] = 0;
     __syncthreads();
     u64 nlo = 0, nhi = 0;
     int inx = 0;
     for (i64 i = blockIdx.x * (i64)blockDim.x + threadIdx.x; i < n; i += (i64)gridDim.x * blockDim.x) {
-        u64 a0 = sa[i * W], a1 = W == 2 ? sa[i * W + 1] : 0;
-        double v = sv[i];
-        u32 b = bucket_index(AddrOf<W>::make(a0, a1), I.log2B, I.mc.nb <= 32);
-        int pos = atomicAdd(&I.tab_n[p][b], 1);
-        if (pos >= I.cap_t) { set_error(ctrl, FQE_CAP_TABLE, (int)b); continue; }
-        i64 o = (i64)b * I.cap_t + pos;
-        I.tab_a[p][0][o] = a0;
-        if (W == 2) I.tab_a[p][1][o] = a1;
-        I.tab_v[p][o] = v;
+        const u64 a0 = sa[i * ew], a1 = ew == 2 ? sa[i * ew + 1] : 0;
+        const double v = sv[i];
+        const U128 a{a0, a1}, out = a & ~mask_below<U128>(I.mc.nb);
+        if (!is_zero(out) || popc(a) != I.mc.N || !(fabs(v) < __builtin_inf()) || v == 0.0) {
+            note->refused = 1;
+            continue;
+        }
+        const u32 b = bucket_index(AddrOf<W>::make(a0, a1), I.log2B, I.mc.nb <= 32);
+        const int pos = atomicAdd(&I.tab_n[par][b], 1);
+        if (pos >= I.cap_t) { note->overflow = 1; continue; }
+        const i64 o = (i64)b * I.cap_t + pos;
+        I.tab_a[par][0][o] = a0;
+        if (W == 2) I.tab_a[par][1][o] = a1;
+        I.tab_v[par][o] = v;
         u64 lo, hi;
         int ovf = 0;
         to_fixed(fabs(v), lo, hi, ovf, inx);
-        if (ovf) set_error(ctrl, FQE_DIVERGED, (int)b);
+        if (ovf) note->out_of_range = 1;
         add128(nlo, nhi, lo, hi);
     }
-    if (inx) atomicOr(&ctrl->inexact_in, 1u);
+    if (inx) atomicOr(&note->inexact, 1u);
     if (nlo | nhi) lds_acc128(&acc[0], &acc[1], nlo, nhi);
     __syncthreads();
-    if (threadIdx.x == 0 && (acc[0] | acc[1])) glb_acc128(ctrl->acc_norm, acc[0], acc[1]);
+    if (threadIdx.x == 0 && (acc[0] | acc[1])) glb_acc128(note->norm, acc[0], acc[1]);
 }
 
-// finish set_state: norm of the inserted vector -> ctrl->norm
-__global__ void k_take_norm(const Inst *Ip)
+// whether an address occurs twice in a bucket of table[par] (one workgroup
+// per bucket, an LDS hash with a counter per slot)
+constexpr int TWICE_BS = 256;
+size_t twice_lds(int W, int slots) { return (size_t)slots * (W == 2 ? 24 : 12); }
+template <int W> __global__ __launch_bounds__(TWICE_BS) void k_twice(const Inst *Ip, int par, int slots, InsertNote *note)
+{
+    extern __shared__ __align__(16) char smem[];
+    const Inst &I = const_inst(Ip);
+    Lds L;
+    L.k0 = (u64 *)smem;
+    L.k1 = L.k0 + slots;
+    L.state = (u32 *)(L.k0 + W * slots);
+    u32 *seen = L.state + (W == 2 ? slots : 0);
+    L.mask = slots - 1;
+    const int b = blockIdx.x, tid = threadIdx.x, n = min((i64)I.tab_n[par][b], I.cap_t);
+    for (int s = tid; s < slots; s += TWICE_BS) {
+        L.k0[s] = EMPTY;
+        if (W == 2) { L.k1[s] = EMPTY; L.state[s] = 0u; }
+        seen[s] = 0;
+    }
+    __syncthreads();
+    int np = 0;
+    for (int i = tid; i < n; i += TWICE_BS) {
+        const i64 e = (i64)b * I.cap_t + i;
+        const u64 a0 = I.tab_a[par][0][e], a1 = W == 2 ? I.tab_a[par][1][e] : 0;
+        const int s = lds_slot<W>(L, a0, a1, slot_hash(a0, a1), np);
+        if (s < 0 || atomicAdd(&seen[s], 1u) != 0) note->refused = 1;
+    }
+}
+
+// set_state: the inserted vector becomes the state, its norm ctrl->norm
+__global__ void k_take_norm(const Inst *Ip, const InsertNote *note)
 {
     Ctrl *c = Ip->ctrl;
-    c->norm = from_fixed(c->acc_norm[0], c->acc_norm[1]);
-    c->acc_norm[0] = c->acc_norm[1] = 0;
+    c->norm = from_fixed(note->norm[0], note->norm[1]);
+    c->inexact_in = note->inexact;
+    if (note->out_of_range) set_error(c, FQE_DIVERGED, -1);
+    if (note->overflow) set_error(c, FQE_CAP_TABLE, -1);
 }
 
 // row of the reference address over its column's destinations: entry 0 is
@@ -362,7 +409,11 @@ size_t lds_spawn_bytes(i64 cap_t) { return (size_t)cap_t * 12 + 160 * 8 + 2048 +
 
 constexpr size_t LDS_MAX = 160 * 1024;
 static_assert(sizeof(Ctrl) % 4 == 0, "Ctrl is copied in 32-bit words");
-constexpr size_t REF_TMP_BYTES = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP + 64;
+// staging of set_state: a reference column (words, values, buckets), its
+// length, and the note of the insertion
+constexpr size_t REF_TMP_COLUMN = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP;
+constexpr size_t REF_TMP_NOTE = REF_TMP_COLUMN + 16, REF_TMP_BYTES = REF_TMP_COLUMN + 64;
+static_assert(REF_TMP_NOTE + sizeof(InsertNote) <= REF_TMP_BYTES, "the note fits behind the column");
 static_assert(sizeof(ResSync) <= REF_TMP_BYTES, "the exchange area of resident steps lies in the set-state staging");
 static_assert(sizeof(StepStats) == sizeof(fq_step_stats), "StepStats mirrors fq_step_stats");
 
@@ -714,8 +765,12 @@ static int hip_fail(fq_handle *q, hipError_t e, const char *what)
     } while (0)
 
 static int read_ctrl(fq_handle *q, Ctrl &c, hipStream_t s);
-static int load_state(fq_handle *q, const u64 *sa, const double *sv, i64 n, double shift, i64 step,
-                      const uint64_t *ref_addr, double ref_val, hipStream_t s);
+static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals, i64 n);
+static int next_parity(const fq_handle *q);
+static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, bool check, InsertNote &note,
+                          hipStream_t s);
+static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_t *ref_addr, double ref_val,
+                      hipStream_t s);
 
 // text of fq_last_error after a successful run in which some sum was not
 // exactly rounded (its rows carry FQ_ROW_INEXACT)
@@ -1001,7 +1056,43 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
     hipStream_t s = (hipStream_t)stream;
     const Resolved &R = q->R;
     const int W = R.W;
-    // host-side validation: addresses well formed and distinct, values finite
+    if (!valid_address(ref_addr, W, q->h.M, q->h.N)) {
+        // an invalid entry is reported before an invalid reference
+        int rc = check_entries(q, addrs, vals, n);
+        if (rc == FQ_OK) q->err = "invalid reference address";
+        return FQ_EINVAL;
+    }
+    if ((size_t)n * (8 * W + 8) > R.slab_bytes || n > (i64)R.B * R.cap_t) {
+        int rc = check_entries(q, addrs, vals, n);
+        if (rc) return rc;
+        q->err = "state larger than the workspace capacity";
+        return FQ_ECAPACITY;
+    }
+    // stage the entries in the slab that holds no pending spawns, then build
+    // the state from them
+    char *stage = q->inst.slab[next_parity(q)];
+    u64 *sa = (u64 *)stage;
+    double *sv = (double *)(stage + sizeof(u64) * W * n);
+    HIPCHK(q, hipMemcpyAsync(sa, addrs, sizeof(u64) * W * n, hipMemcpyHostToDevice, s));
+    HIPCHK(q, hipMemcpyAsync(sv, vals, sizeof(double) * n, hipMemcpyHostToDevice, s));
+    InsertNote note;
+    int rc = insert_entries(q, sa, sv, n, true, note, s);
+    if (rc) return rc;
+    if (note.refused || note.overflow) {
+        // the host names the entry, or finds the entries sound (a bucket is full)
+        rc = check_entries(q, addrs, vals, n);
+        if (rc) return rc;
+    }
+    return load_state(q, n, shift, step, ref_addr, ref_val, s);
+}
+
+// Host check of a state's entries: addresses well formed and distinct, values
+// finite and not zero; names the first entry that is not.  The device checks
+// the same (k_insert, k_twice); sorting the addresses here took 25 of the 30
+// ms that a checkpoint of 5e5 entries and its continuation took.
+static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals, i64 n)
+{
+    const int W = q->R.W;
     std::vector<std::pair<uint64_t, uint64_t>> keys((size_t)n);
     for (i64 i = 0; i < n; i++) {
         if (!valid_address(addrs + i * W, W, q->h.M, q->h.N) || !std::isfinite(vals[i]) || vals[i] == 0.0) {
@@ -1013,46 +1104,65 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
     std::sort(keys.begin(), keys.end());
     for (size_t i = 1; i < keys.size(); i++)
         if (keys[i] == keys[i - 1]) { q->err = "duplicate address in state"; return FQ_EINVAL; }
-    if (!valid_address(ref_addr, W, q->h.M, q->h.N)) { q->err = "invalid reference address"; return FQ_EINVAL; }
-    if ((size_t)n * (8 * W + 8) > R.slab_bytes || n > (i64)R.B * R.cap_t) {
-        q->err = "state larger than the workspace capacity";
-        return FQ_ECAPACITY;
-    }
-    // stage entries in the parity-1 slab, then build the instance from them
-    u64 *sa = (u64 *)q->inst.slab[1];
-    double *sv = (double *)(q->inst.slab[1] + sizeof(u64) * W * n);
-    HIPCHK(q, hipMemcpyAsync(sa, addrs, sizeof(u64) * W * n, hipMemcpyHostToDevice, s));
-    HIPCHK(q, hipMemcpyAsync(sv, vals, sizeof(double) * n, hipMemcpyHostToDevice, s));
-    return load_state(q, sa, sv, n, shift, step, ref_addr, ref_val, s);
+    return FQ_OK;
 }
 
-// State c^(step) from device arrays (n entries staged in the parity-1 slab
-// region or elsewhere outside the tables), shift, reference vector: insert
-// into table[0], reference column, spawns of c^(step) for step+1.
-static int load_state(fq_handle *q, const u64 *sa, const double *sv, i64 n, double shift, i64 step,
-                      const uint64_t *ref_addr, double ref_val, hipStream_t s)
+// The parity of a state being set: the table and slab that the current state
+// (its table, and its spawns for the next step) does not use.
+static int next_parity(const fq_handle *q) { return q->have_state ? 1 - q->parity : 0; }
+
+// Inserts n staged entries (device arrays) into the table of next_parity; the
+// current state stays as it is.  check: look for addresses that occur twice.
+static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, bool check, InsertNote &note,
+                          hipStream_t s)
 {
     const Resolved &R = q->R;
-    const int W = R.W;
+    const int W = R.W, par = next_parity(q);
+    InsertNote *d_note = (InsertNote *)(q->ws + R.off_ref_tmp + REF_TMP_NOTE);
+    HIPCHK(q, hipMemsetAsync(q->inst.tab_n[par], 0, sizeof(int) * R.B, s));
+    HIPCHK(q, hipMemsetAsync(d_note, 0, sizeof(InsertNote), s));
+    const int grid = (int)std::min<i64>((n + 255) / 256, 4096);
+    const Inst *I = q->d_inst;
+    if (W == 1) hipLaunchKernelGGL(k_insert<1>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, W, d_note);
+    else hipLaunchKernelGGL(k_insert<2>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, W, d_note);
+    HIPCHK(q, hipGetLastError());
+    if (check) {
+        // slots for at most cap_t entries of a bucket: the next power of two,
+        // and twice that where the LDS allows
+        int slots = 256;
+        while (slots < R.cap_t) slots *= 2;
+        if (twice_lds(W, 2 * slots) <= 64 * 1024) slots *= 2;
+        const void *kf = W == 1 ? (const void *)k_twice<1> : (const void *)k_twice<2>;
+        HIPCHK(q, ensure_lds(kf, twice_lds(W, slots)));
+        int p = par;
+        void *args[] = {(void *)&I, (void *)&p, (void *)&slots, (void *)&d_note};
+        HIPCHK(q, hipLaunchKernel(kf, dim3(R.B), dim3(TWICE_BS), args, twice_lds(W, slots), s));
+    }
+    HIPCHK(q, hipMemcpyAsync(&note, d_note, sizeof note, hipMemcpyDeviceToHost, s));
+    HIPCHK(q, hipStreamSynchronize(s));
+    return FQ_OK;
+}
+
+// The n entries inserted into the table of next_parity become the state
+// c^(step): shift, reference column, spawns for step+1.
+static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_t *ref_addr, double ref_val,
+                      hipStream_t s)
+{
+    const Resolved &R = q->R;
+    const int W = R.W, par = next_parity(q);
     // fresh control block
     Ctrl c;
     memset(&c, 0, sizeof c);
     c.step = step;
-    c.parity = 0;
+    c.parity = par;
     c.shift = shift;
     c.ring_base = step + 1;
     c.stop_step = INT64_MAX;
     HIPCHK(q, hipMemcpyAsync(q->d_ctrl, &c, sizeof c, hipMemcpyHostToDevice, s));
-    for (int k = 0; k < 2; k++) {
-        HIPCHK(q, hipMemsetAsync(q->inst.tab_n[k], 0, sizeof(int) * R.B, s));
-        HIPCHK(q, hipMemsetAsync(q->inst.slab_n[k], 0, sizeof(int) * R.B, s));
-    }
+    for (int k = 0; k < 2; k++) HIPCHK(q, hipMemsetAsync(q->inst.slab_n[k], 0, sizeof(int) * R.B, s));
     HIPCHK(q, hipMemsetAsync(q->inst.coarse_n, 0, sizeof(int) << (R.log2G + R.log2SUB), s));
-    int grid = (int)std::min<i64>((n + 255) / 256, 4096);
-    if (W == 1) hipLaunchKernelGGL(k_insert<1>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, (const u64 *)sa, (const double *)sv, (i64)n);
-    else hipLaunchKernelGGL(k_insert<2>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, (const u64 *)sa, (const double *)sv, (i64)n);
-    HIPCHK(q, hipGetLastError());
-    hipLaunchKernelGGL(k_take_norm, dim3(1), dim3(1), 0, s, (const Inst *)q->d_inst);
+    hipLaunchKernelGGL(k_take_norm, dim3(1), dim3(1), 0, s, (const Inst *)q->d_inst,
+                       (const InsertNote *)(q->ws + R.off_ref_tmp + REF_TMP_NOTE));
     // reference column (on the device), sorted by bucket on the host
     u64 *ra = (u64 *)(q->ws + R.off_ref_tmp);
     double *rh = (double *)(ra + 2 * REFCAP);
@@ -1111,7 +1221,7 @@ static int load_state(fq_handle *q, const u64 *sa, const double *sv, i64 n, doub
     }
     q->have_state = 1;
     q->step = step;
-    q->parity = 0;
+    q->parity = par;
     // entries and attempts; an exact parent has fewer events than walkers
     q->items = q->work = (i64)std::min(1e15, 2.0 * (double)n + cc.norm);
     q->items_known = false;
@@ -1396,7 +1506,7 @@ int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream)
         dst->err = "copy_state: destination slab too small to stage the source table";
         return FQ_ECAPACITY;
     }
-    char *buf = dst->inst.slab[1];
+    char *buf = dst->inst.slab[next_parity(dst)];
     unsigned long long *cnt = (unsigned long long *)buf;
     u64 *oa = (u64 *)(buf + 256);
     double *ov = (double *)(oa + (size_t)W * nmax);
@@ -1412,7 +1522,10 @@ int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream)
         dst->err = "copy_state: state does not fit the destination";
         return FQ_ECAPACITY;
     }
-    return load_state(dst, oa, ov, (i64)tot, c.shift, c.step, src->ref, src->yref, s);
+    InsertNote note;
+    rc = insert_entries(dst, oa, ov, (i64)tot, false, note, s);
+    if (rc) return rc;
+    return load_state(dst, (i64)tot, c.shift, c.step, src->ref, src->yref, s);
 }
 
 int fq_autotune(fq_handle *src, const fq_layout *cand, int32_t n, int32_t trial_steps, void *scratch,
