@@ -20,6 +20,7 @@
 #include <vector>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <unordered_map>
 
@@ -82,13 +83,15 @@ __global__ __launch_bounds__(PartShape<W>::BS) void k_part(const Inst *const *in
                                                                    (int)(m & 0x3fffu));
 }
 
-// start of a chunk of steps: statistics rows are stored from row 0; the
-// exchange area of a resident launch starts at zero
-__global__ void k_begin_chunk(const Inst *const *insts, int n, int resident)
+// Start of a chunk of steps: statistics rows are stored from row 0, and the
+// exchange area of a resident launch starts at zero.  stop >= 0: every
+// instance stops after that many more steps.
+__global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64 stop)
 {
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         Ctrl *c = insts[i]->ctrl;
         c->ring_base = c->step + 1;
+        if (stop >= 0) c->stop_step = c->step + stop;
         if (resident) {
             ResSync *y = insts[i]->res;
             y->arrived = y->gate = y->xccs = y->count = 0;
@@ -96,22 +99,21 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident)
     }
 }
 
-// every instance stops after `steps` more steps
-__global__ void k_set_stop(const Inst *const *insts, int n, i64 steps)
-{
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        Ctrl *c = insts[i]->ctrl;
-        c->stop_step = c->step + steps;
-    }
-}
-
-// copy the control blocks of n instances into one array
-__global__ void k_gather_ctrl(const Inst *const *insts, int n, Ctrl *out)
+// End of a chunk: the control blocks of n instances into one array, and the
+// rows of the chunk, at most `stride` of each instance, into another (none:
+// stride 0).  Both lie in pinned host memory: one launch and one wait take
+// the place of a copy for every instance.
+__global__ __launch_bounds__(256) void k_report(const Inst *const *insts, int n, Ctrl *ctrls, StepStats *rows, i64 stride)
 {
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
-        const u32 *src = (const u32 *)insts[i]->ctrl;
-        u32 *dst = (u32 *)(out + i);
+        const Inst &I = *insts[i];
+        const u32 *src = (const u32 *)I.ctrl;
+        u32 *dst = (u32 *)(ctrls + i);
         for (int k = threadIdx.x; k < (int)(sizeof(Ctrl) / 4); k += blockDim.x) dst[k] = src[k];
+        const i64 made = min(stride, min(I.ring_cap, I.ctrl->step + 1 - I.ctrl->ring_base));
+        const u64 *from = (const u64 *)I.ring;
+        u64 *to = (u64 *)(rows + i * stride);
+        for (i64 k = threadIdx.x; k < made * (i64)(sizeof(StepStats) / 8); k += blockDim.x) to[k] = from[k];
     }
 }
 
@@ -408,7 +410,31 @@ size_t lds_bytes(int W, int slots, bool init)
 size_t lds_spawn_bytes(i64 cap_t) { return (size_t)cap_t * 12 + 160 * 8 + 2048 + sizeof(int) * SPAWN_COARSE + 2 * TRI_N; }
 
 constexpr size_t LDS_MAX = 160 * 1024;
-static_assert(sizeof(Ctrl) % 4 == 0, "Ctrl is copied in 32-bit words");
+static_assert(sizeof(Ctrl) % 8 == 0 && sizeof(StepStats) % 8 == 0, "k_report copies words");
+
+// Pinned host memory that a handle or a group of instances reports into; it
+// grows to what a call needs, up to PINNED_MOST, and is freed with its owner.
+constexpr size_t PINNED_MOST = (size_t)8 << 20;
+struct Pinned {
+    char *p = nullptr;
+    size_t bytes = 0;
+    Pinned() = default;
+    Pinned(const Pinned &) = delete;
+    Pinned &operator=(const Pinned &) = delete;
+    ~Pinned() { if (p) (void)hipHostFree(p); }
+    hipError_t reserve(size_t need)
+    {
+        if (need <= bytes) return hipSuccess;
+        if (p) (void)hipHostFree(p);
+        p = nullptr;
+        bytes = 0;
+        need = std::max<size_t>(need, 64 << 10);
+        hipError_t e = hipHostMalloc((void **)&p, need, hipHostMallocDefault);
+        if (e == hipSuccess) bytes = need;
+        else p = nullptr;
+        return e;
+    }
+};
 // staging of set_state: a reference column (words, values, buckets), its
 // length, and the note of the insertion
 constexpr size_t REF_TMP_COLUMN = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP;
@@ -744,8 +770,7 @@ struct fq_handle {
     double time_ms[NEV - 1];
     i64 launches;
     std::vector<hipEvent_t> ev;
-    std::vector<StepStats> ring_host;
-    std::vector<int> ref_bucket_host;
+    Pinned pinned;
 };
 
 static thread_local std::string g_err;  // errors of calls that have no handle yet
@@ -975,7 +1000,6 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
     X.pmap = (const u32 *)(q->ws + R.off_pmap);
     X.pgrid = (int)pm.size();
     X.wide_groups = R.two_pass && R.log2B - R.log2G > 8;
-    q->ring_host.resize(RING);
     *out = q;
     return FQ_OK;
 }
@@ -1345,7 +1369,6 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(1), 0, s, &q->d_ctrl->dump_spawn_n, (i64)0);
         hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(1), 0, s, &q->d_ctrl->dump_merged_n, (i64)0);
     }
-    hipLaunchKernelGGL(k_set_stop, dim3(1), dim3(64), 0, s, q->X.insts, 1, (i64)n_steps);
     i64 done = 0;
     bool again = true;  // resident steps are worth another launch
     while (done < n_steps) {
@@ -1353,7 +1376,7 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         const bool resident = again && plan_resident(&q, 1, plan);
         i64 chunk = std::min<i64>(RING, n_steps - done);
         if (!resident && !q->items_known) chunk = std::min<i64>(chunk, RES_GUESS_STEPS);
-        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, q->X.insts, 1, resident ? 1 : 0);
+        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, q->X.insts, 1, resident ? 1 : 0, n_steps - done);
         if (q->timing && (i64)q->ev.size() < NEV * chunk) {
             size_t old = q->ev.size();
             q->ev.resize(NEV * chunk);
@@ -1366,9 +1389,14 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         } else {
             for (i64 k = 0; k < chunk; k++) HIPCHK(q, exec_step(q->X, s, q->timing ? &q->ev[NEV * k] : nullptr));
         }
-        Ctrl c;
-        int rc = read_ctrl(q, c, s);
-        if (rc) return rc;
+        HIPCHK(q, q->pinned.reserve(256 + sizeof(StepStats) * chunk));
+        const Ctrl &c = *(const Ctrl *)q->pinned.p;
+        const fq_step_stats *made = (const fq_step_stats *)(q->pinned.p + 256);
+        static_assert(sizeof(Ctrl) <= 256, "the rows come behind the control block");
+        hipLaunchKernelGGL(k_report, dim3(1), dim3(256), 0, s, q->X.insts, 1, (Ctrl *)q->pinned.p,
+                           (StepStats *)(q->pinned.p + 256), chunk);
+        HIPCHK(q, hipGetLastError());
+        HIPCHK(q, hipStreamSynchronize(s));
         if (q->timing) {
             for (i64 k = 0; k < chunk; k++)
                 for (int j = 0; j < NEV - 1; j++) {
@@ -1380,12 +1408,8 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         }
         const i64 completed = c.step - q->step;
         if (completed > 0) {
-            // the rows, or the last one to know the size of a step
-            fq_step_stats last;
-            const i64 from = stats_out ? 0 : completed - 1;
-            fq_step_stats *to = stats_out ? stats_out + done : &last;
-            HIPCHK(q, hipMemcpy(to, q->inst.ring + from, sizeof(StepStats) * (completed - from), hipMemcpyDeviceToHost));
-            note_items(q, to[completed - from - 1], completed < chunk, resident ? &plan : nullptr);
+            if (stats_out) memcpy(stats_out + done, made, sizeof(StepStats) * completed);
+            note_items(q, made[completed - 1], completed < chunk, resident ? &plan : nullptr);
         }
         again = !resident || completed > 0;
         done += std::max<i64>(completed, 0);
@@ -1566,7 +1590,7 @@ namespace {
 struct Group {
     std::vector<fq_handle *> h;  // in grid order
     Exec X;
-    Ctrl *d_ctrl_out = nullptr;
+    std::unique_ptr<Pinned> pinned = std::make_unique<Pinned>();
     std::vector<Ctrl> ctrl;
 };
 
@@ -1604,7 +1628,6 @@ int group_build(Group &G, std::vector<fq_handle *> hs, char *hdr, std::string &e
     o += align256(sizeof(u32) * map.size());
     u32 *d_pmap = (u32 *)o;
     o += align256(sizeof(u32) * pmap.size());
-    G.d_ctrl_out = (Ctrl *)o;
     hipError_t e = hipMemcpy(d_ip, ip.data(), sizeof(Inst *) * n, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(d_map, map.data(), sizeof(u32) * map.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && !pmap.empty())
@@ -1653,18 +1676,30 @@ hipError_t launch_overlap(const OvRun &ov, hipStream_t s)
     return e;
 }
 
-// After a launch of a group: the control blocks, and for every instance its
+size_t group_report_head(int n) { return (sizeof(Ctrl) * n + 255) & ~(size_t)255; }
+size_t group_report_bytes(int n, i64 steps) { return group_report_head(n) + sizeof(StepStats) * n * steps; }
+
+// After a launch of a group of at most `chunk` steps: the control blocks, and for every instance its
 // completed steps, rows (appended at (*rows)[j] and advanced, if not null)
 // and error (the first one to *failed, err and rc).
-int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, const ResPlan *plan, const ResStops *stops,
+int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, const ResPlan *plan, const ResStops *stops,
                   int *failed, std::string &err, int &rc)
 {
     const Exec &X = G.X;
-    hipLaunchKernelGGL(k_gather_ctrl, dim3(std::min(X.n, 1024)), dim3(64), 0, s, X.insts, X.n, G.d_ctrl_out);
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(G.ctrl.data(), G.d_ctrl_out, sizeof(Ctrl) * X.n, hipMemcpyDeviceToHost, s);
+    // rows through the pinned memory where they fit it, else a copy for every
+    // instance; the last row of an instance is always looked at
+    const size_t head = group_report_head(X.n);
+    const bool small = group_report_bytes(X.n, chunk) <= PINNED_MOST;
+    const i64 stride = small ? chunk : 0;
+    hipError_t e = G.pinned->reserve(group_report_bytes(X.n, stride));
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_report, dim3(std::min(X.n, 1024)), dim3(256), 0, s, X.insts, X.n, (Ctrl *)G.pinned->p,
+                           (StepStats *)(G.pinned->p + head), stride);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+    memcpy(G.ctrl.data(), G.pinned->p, sizeof(Ctrl) * X.n);
     for (int j = 0; j < X.n; j++) {
         fq_handle *q = G.h[j];
         const Ctrl &c = G.ctrl[j];
@@ -1672,11 +1707,18 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, const ResPlan *
         if (completed > 0) {
             fq_step_stats last;
             const bool all = rows && rows[j];
-            const i64 from = all ? 0 : completed - 1;
-            fq_step_stats *to = all ? rows[j] : &last;
-            e = hipMemcpy(to, q->inst.ring + from, sizeof(StepStats) * (completed - from), hipMemcpyDeviceToHost);
-            if (e != hipSuccess) { err = std::string("group rows: ") + hipGetErrorString(e); return FQ_EHIP; }
-            note_items(q, to[completed - from - 1], plan && c.step < std::min(c.stop_step, stops->step[j]), plan);
+            if (small) {
+                const fq_step_stats *made = (const fq_step_stats *)(G.pinned->p + head) + j * stride;
+                if (all) memcpy(rows[j], made, sizeof(StepStats) * completed);
+                last = made[completed - 1];
+            } else {
+                const i64 from = all ? 0 : completed - 1;
+                fq_step_stats *to = all ? rows[j] : &last;
+                e = hipMemcpy(to, q->inst.ring + from, sizeof(StepStats) * (completed - from), hipMemcpyDeviceToHost);
+                if (e != hipSuccess) { err = std::string("group rows: ") + hipGetErrorString(e); return FQ_EHIP; }
+                if (all) last = rows[j][completed - 1];
+            }
+            note_items(q, last, plan && c.step < std::min(c.stop_step, stops->step[j]), plan);
             if (all) rows[j] += completed;
         }
         q->step = c.step;
@@ -1696,7 +1738,7 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, const ResPlan *
 // step), in as many launches as the growth of the instances takes.  The
 // steps left by an instance whose workgroups did not get onto the GPU
 // together, or outgrew them, are made by its own step kernels.
-int group_resident(Group &G, ResPlan plan, i64 steps, fq_step_stats **rows, hipStream_t s, int *failed,
+int group_resident(Group &G, ResPlan plan, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t s, int *failed,
                    std::string &err, int &rc)
 {
     const Exec &X = G.X;
@@ -1705,10 +1747,11 @@ int group_resident(Group &G, ResPlan plan, i64 steps, fq_step_stats **rows, hipS
     for (;;) {
         std::vector<i64> before(X.n);
         for (int j = 0; j < X.n; j++) before[j] = G.h[j]->step;
-        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 1);
+        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 1, stop);
+        stop = -1;
         hipError_t e = launch_resident(X, plan, stops, s);
         if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
-        int hr = group_collect(G, rows, s, &plan, &stops, failed, err, rc);
+        int hr = group_collect(G, rows, s, steps, &plan, &stops, failed, err, rc);
         if (hr) return hr;
         bool left = false, stuck = false;
         for (int j = 0; j < X.n; j++) {
@@ -1723,21 +1766,22 @@ int group_resident(Group &G, ResPlan plan, i64 steps, fq_step_stats **rows, hipS
             const Ctrl &c = G.ctrl[j];
             const i64 k = c.error ? 0 : std::min(c.stop_step, stops.step[j]) - c.step;
             if (k <= 0) continue;
-            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0);
+            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0, (i64)-1);
             for (i64 i = 0; i < k && e == hipSuccess; i++) e = exec_step(G.h[j]->X, s, nullptr);
             if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
         }
-        return group_collect(G, rows, s, nullptr, nullptr, failed, err, rc);
+        return group_collect(G, rows, s, steps, nullptr, nullptr, failed, err, rc);
     }
 }
 
 // Runs `steps` steps of every instance of G (an instance that has failed or
-// reached its stop step does no work).  When rows is given, the statistics
+// reached its stop step does no work; stop >= 0 sets the stop step of every
+// instance to so many steps from here).  When rows is given, the statistics
 // rows of grid position j are appended at (*rows)[j] (advanced), if not
 // null.  With ov, the replica overlaps of every step are computed and their
 // rows appended at ov->out.  Returns the status of the first failing
 // instance (grid position in *failed) after the chunk in which it failed.
-int group_steps(Group &G, i64 steps, fq_step_stats **rows, hipStream_t s, int *failed, std::string &err,
+int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t s, int *failed, std::string &err,
                 OvRun *ov = nullptr, const GsRun *gs = nullptr)
 {
     const Exec &X = G.X;
@@ -1748,18 +1792,18 @@ int group_steps(Group &G, i64 steps, fq_step_stats **rows, hipStream_t s, int *f
         ResPlan plan;
         int hr;
         if (!ov && !gs && plan_resident(G.h.data(), X.n, plan)) {
-            hr = group_resident(G, plan, chunk, rows, s, failed, err, rc);
+            hr = group_resident(G, plan, chunk, stop, rows, s, failed, err, rc);
         } else {
-            std::vector<i64> before(X.n);
-            for (int j = 0; j < X.n; j++) before[j] = G.h[j]->step;
-            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 0);
+            i64 before[FQ_MAX_REPLICAS];  // (with overlaps only: no allocation there)
+            for (int j = 0; ov && j < X.n; j++) before[j] = G.h[j]->step;
+            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 0, stop);
             hipError_t e = hipGetLastError();
             for (i64 k = 0; k < chunk && e == hipSuccess; k++) {
                 e = exec_step(X, s, nullptr, gs);
                 if (e == hipSuccess && ov) e = launch_overlap(*ov, s);
             }
             if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
-            hr = group_collect(G, rows, s, nullptr, nullptr, failed, err, rc);
+            hr = group_collect(G, rows, s, chunk, nullptr, nullptr, failed, err, rc);
             if (ov && !hr) {
                 i64 done = chunk;
                 for (int j = 0; j < X.n; j++) done = std::min<i64>(done, G.ctrl[j].step - before[j]);
@@ -1771,6 +1815,7 @@ int group_steps(Group &G, i64 steps, fq_step_stats **rows, hipStream_t s, int *f
             }
         }
         if (hr) return hr;
+        stop = -1;
         launched += chunk;
     }
     return rc;
@@ -1867,6 +1912,11 @@ int fq_batch_create(int32_t n, const fq_hamiltonian *h, const fq_params *p, cons
         b->inst.push_back(q);
     }
     rc = group_build(b->G, b->inst, ws, g_err);
+    // replicas report without an allocation in the call, whatever its length
+    if (rc == FQ_OK && n <= FQ_MAX_REPLICAS) {
+        const hipError_t e = b->G.pinned->reserve(group_report_bytes(n, RING));
+        if (e != hipSuccess) { g_err = std::string("batch: pinned memory: ") + hipGetErrorString(e); rc = FQ_EHIP; }
+    }
     if (rc) {
         for (auto x : b->inst) fq_destroy(x);
         delete b;
@@ -1894,13 +1944,12 @@ int fq_batch_run(fq_batch *b, int64_t n_steps, fq_step_stats *stats, void *strea
     for (int i = 0; i < n; i++)
         if (!b->inst[i]->have_state) { b->err = "batch: instance " + std::to_string(i) + " has no state"; return FQ_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_set_stop, dim3(1), dim3(256), 0, s, b->G.X.insts, n, (i64)n_steps);
     std::vector<fq_step_stats *> rows(n, nullptr);
     if (stats)
         for (int i = 0; i < n; i++) rows[b->pos[i]] = stats + (size_t)i * n_steps;
     int failed = -1;
     b->failed = -1;
-    int rc = group_steps(b->G, n_steps, rows.data(), s, &failed, b->err);
+    int rc = group_steps(b->G, n_steps, n_steps, rows.data(), s, &failed, b->err);
     if (failed >= 0)
         for (int i = 0; i < n; i++)
             if (b->pos[i] == failed) b->failed = i;
@@ -1997,13 +2046,12 @@ static int run_replicas(fq_batch *b, int64_t n_steps, fq_step_stats *stats, doub
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { b->err = std::string("replicas: ") + hipGetErrorString(e); return FQ_EHIP; }
-    hipLaunchKernelGGL(k_set_stop, dim3(1), dim3(256), 0, s, b->G.X.insts, R, (i64)n_steps);
     fq_step_stats *rows[FQ_MAX_REPLICAS] = {};
     if (stats)
         for (int i = 0; i < R; i++) rows[b->pos[i]] = stats + (size_t)i * n_steps;
     int failed = -1;
     b->failed = -1;
-    int rc = group_steps(b->G, n_steps, rows, s, &failed, b->err, &ov);
+    int rc = group_steps(b->G, n_steps, n_steps, rows, s, &failed, b->err, &ov);
     if (failed >= 0)
         for (int i = 0; i < R; i++)
             if (b->pos[i] == failed) b->failed = i;
@@ -2170,13 +2218,12 @@ int fq_batch_run_spectral(fq_batch *b, int64_t n_steps, fq_step_stats *stats, vo
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { b->err = std::string("excited states: ") + hipGetErrorString(e); return FQ_EHIP; }
-    hipLaunchKernelGGL(k_set_stop, dim3(1), dim3(256), 0, s, b->G.X.insts, R, (i64)n_steps);
     std::vector<fq_step_stats *> rows(R, nullptr);
     if (stats)
         for (int i = 0; i < R; i++) rows[b->pos[i]] = stats + (size_t)i * n_steps;
     int failed = -1;
     b->failed = -1;
-    rc = group_steps(b->G, n_steps, rows.data(), s, &failed, b->err, nullptr, &g);
+    rc = group_steps(b->G, n_steps, n_steps, rows.data(), s, &failed, b->err, nullptr, &g);
     if (failed >= 0)
         for (int i = 0; i < R; i++)
             if (b->pos[i] == failed) b->failed = i;
@@ -2461,7 +2508,7 @@ int fq_server_tick(fq_server *sv, void *stream, int32_t *n_active, int32_t *n_qu
         for (int j = 0; j < n; j++) rows[j] = sv->rowbuf.data() + (size_t)j * T;
         int failed = -1;
         std::string err;
-        int rc = group_steps(sv->G, T, rows.data(), s, &failed, err);
+        int rc = group_steps(sv->G, T, -1, rows.data(), s, &failed, err);
         if (rc == FQ_EHIP) { sv->err = err; return rc; }
         // account the rows and retire finished or failed solves
         std::unordered_map<const fq_handle *, int> posof;
