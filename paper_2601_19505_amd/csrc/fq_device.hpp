@@ -41,6 +41,10 @@ __device__ __forceinline__ int gatomic_add(int *p, int v)
 {
     return __hip_atomic_fetch_add(gmem(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ u64 gatomic_add(u64 *p, u64 v)
+{
+    return __hip_atomic_fetch_add(gmem(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // ---------------------------------------------------------------- bits
 

@@ -66,7 +66,7 @@ __host__ __device__ __forceinline__ int res_log2_groups(int lg, int log2B)
 }
 template <int W, int MODEL, bool EARLY>
 __global__ __launch_bounds__(fq::RES_BS) void k_resident(const fq::Inst *const *insts, int n, int lg, int lg_grid,
-                                                         int max_items, fq::u64 patience, ResStops stops)
+                                                         fq::i64 max_items, fq::u64 patience, ResStops stops)
 {
     extern __shared__ __align__(16) char smem[];
     const int x = (int)blockIdx.x, y = lg_grid <= 5 ? x >> 3 : x;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident(const fq::Inst *const *
     const fq::Inst &I = fq::const_inst(insts[i]);
     const int own = res_log2_groups(lg, I.log2B);
     if (g >> own) return;
-    fq::resident_steps<W, MODEL, EARLY>(I, I.res, g, own, stops.step[i], (fq::i64)max_items << own, patience, smem);
+    fq::resident_steps<W, MODEL, EARLY>(I, I.res, g, own, stops.step[i], max_items << own, patience, smem);
 }
 
 // explicit instantiations (EXT = extern: declaration only) of the merge and
@@ -94,8 +94,8 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident(const fq::Inst *const *
     EXT template __global__ void k_spawn<W_, M_, 256, true>(const fq::Inst *const *, const fq::u32 *, int); \
     EXT template __global__ void k_spawn<W_, M_, 512, true>(const fq::Inst *const *, const fq::u32 *, int); \
     EXT template __global__ void k_spawn<W_, M_, 1024, true>(const fq::Inst *const *, const fq::u32 *, int); \
-    EXT template __global__ void k_resident<W_, M_, false>(const fq::Inst *const *, int, int, int, int, fq::u64, ResStops); \
-    EXT template __global__ void k_resident<W_, M_, true>(const fq::Inst *const *, int, int, int, int, fq::u64, ResStops);
+    EXT template __global__ void k_resident<W_, M_, false>(const fq::Inst *const *, int, int, int, fq::i64, fq::u64, ResStops); \
+    EXT template __global__ void k_resident<W_, M_, true>(const fq::Inst *const *, int, int, int, fq::i64, fq::u64, ResStops);
 
 #define FQ_EXTERN_STEP_KERNELS                                                                \
     FQ_STEP_KERNEL_SET(extern, 1, 0) FQ_STEP_KERNEL_SET(extern, 1, 1) FQ_STEP_KERNEL_SET(extern, 1, 2)        \

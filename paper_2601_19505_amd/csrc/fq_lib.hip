@@ -95,6 +95,7 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64
         if (resident) {
             ResSync *y = insts[i]->res;
             y->arrived = y->gate = y->xccs = y->count = 0;
+            for (int x = 0; x < RES_XCCS; x++) y->on[x] = y->here[x][0] = 0;
         }
     }
 }
@@ -1280,37 +1281,55 @@ int fq_kernel_time(fq_handle *q, double *ms, int32_t n, int64_t *steps, int32_t 
 namespace {
 
 // Resident steps (fq_resident.hpp) for a set of instances.
+
+// Entries and spawn attempts per workgroup that a plan aims at (the latency
+// of a step's chain bounds it then; fewer items do not shorten it).  A step
+// of the 12/12 ring under early compression at 1e4 walkers (1.7e4 entries
+// and attempts): 11.9 us at 512 a workgroup (G = 32), 12.3 at 1024, 19.8 at
+// 2100, 36 with the step kernels.  The same ring at 1e5 walkers (1.4e5
+// items): 20.0 us with 128 and 256 workgroups, 25.3 with 64, 43 with the
+// step kernels.
+constexpr i64 RES_AIM = 512;
+// Entries and records per workgroup above which the step kernels are taken:
+// the largest measured.  us a step at RES_MAXG workgroups, resident and step
+// kernels: the 16/16 ring at 1.7e6 items 64 and 138, at 3.0e6 110 and 247;
+// 20/20 in two words at 2.0e6 147 and 198; momentum space, initiator rule, at
+// 3.5e6 133 and 178, at 6.5e6 258 and 316; 48 rings of 6e4 items, four
+// workgroups each, 131 and 638.
+constexpr i64 RES_MOST = 24576;
+// items per workgroup at which a launch ends that more workgroups can follow:
+// a population that grows from one determinant soon outruns the first plan
+constexpr i64 RES_MORE = 4 * RES_AIM;
+// the items of a step that a launch of 2^own workgroups goes on after (the
+// kernel's item_limit)
+i64 res_limit(const fq_handle *q, i64 most, int own)
+{
+    const int hash = q->R.W == 1 ? ResSlots<1>::N : ResSlots<2>::N;
+    return q->R.slots > hash ? std::min(most << own, (i64)q->R.B * (hash / 2)) : most << own;
+}
+
 struct ResPlan {
     int lg = 0, lg_grid = 0;  // workgroups of an instance and per instance of the grid (log2)
+    int per = 1;              // instances of a launch
+    i64 most = RES_MOST;      // items per workgroup after which it ends
 };
 
-// Entries and spawn attempts per workgroup that a plan aims at on one XCD;
-// entries and records per workgroup above which a launch ends, so that the
-// next one takes more workgroups.  A step of the 12/12 ring under early
-// compression at 1e4 walkers (1.7e4 entries and attempts): 11.9 us at 512 a
-// workgroup (G = 32), 12.3 at 1024, 19.8 at 2100, 36 with the step kernels.
-// Beyond one XCD the exchange costs more than the work of a workgroup: the
-// same ring at 1e5 walkers (1.4e5 items) takes 27.7 us with 64 workgroups,
-// 35 with 256, 43 with the step kernels.
-constexpr i64 RES_AIM = 512;
-i64 res_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
 // wall-clock ticks (100 MHz) a workgroup waits for the others: 5 ms
 constexpr u64 RES_PATIENCE = 500000;
 // steps of a launch of the step kernels while the size of a step is a guess
 constexpr i64 RES_GUESS_STEPS = 64;
 
-// Whether the instances can be stepped by resident workgroups: all of them
-// on the GPU at once (one per CU, RES_MAXG together), no more items than the
-// hashes of the largest instance's workgroups hold, and no diagnostics (the
-// step kernels record the dumps, the phase clocks and the kernel times).
-// Larger steps keep the step kernels: at RES_MAXG workgroups the barrier
-// takes 9 us and the LDS hashes hold 7.9e5 items, where a step of the four
-// kernels takes about 90 us.
+// Whether the instances can be stepped by resident workgroups: no more items
+// than they are good for, buckets that their LDS counters hold, and no
+// diagnostics (the step kernels record the dumps, the phase clocks and the
+// kernel times).  A launch takes as many instances as get onto the GPU at
+// once (one workgroup per CU, RES_MAXG together); more instances, more
+// launches, each to the end of its steps.
 bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
 {
-    if (n < 1 || n > RES_MAXG) return false;
+    if (n < 1) return false;
     for (int i = 0; i < n; i++)
-        if (h[i]->timing || h[i]->R.B > RES_MAXB ||
+        if (h[i]->timing || h[i]->R.B > RES_MAXB || h[i]->R.cap_s > ((i64)1 << 30) ||
             (h[i]->p.flags & (FQ_FLAG_DUMP_SPAWNS | FQ_FLAG_DUMP_MERGED | FQ_FLAG_PHASE_TIMING)))
             return false;
     bool fits = false;
@@ -1321,27 +1340,37 @@ bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
             const int own = res_log2_groups(lg, h[i]->R.log2B);
             grid = std::max(grid, own);
             aim = aim && h[i]->work <= (RES_AIM << own);
-            most = most && h[i]->items <= (res_most(h[i]->R.W) << own);
+            most = most && h[i]->items <= res_limit(h[i], RES_MOST, own);
         }
         // one XCD holds 32 workgroups, all of them RES_MAXG
-        if (grid <= 5 ? (((n + 7) / 8) << grid) > 32 : (n << grid) > RES_MAXG) break;
+        const int per = grid <= 5 ? 8 * (32 >> grid) : RES_MAXG >> grid;
+        if (fits && n > per) break;
         P.lg = lg;
         P.lg_grid = grid;
+        P.per = std::min(n, per);
         fits = most;
-        if (aim || (most && lg >= 5)) break;
+        P.most = aim ? RES_MORE : RES_MOST;
+        if (aim) break;
     }
     return fits;
 }
 
-hipError_t launch_resident(const Exec &X, const ResPlan &P, const ResStops &stops, hipStream_t s)
+hipError_t launch_resident(const Exec &X, const ResPlan &P, const i64 *stops, hipStream_t s)
 {
-    int n = X.n, lg = P.lg, lg_grid = P.lg_grid, most = (int)res_most(X.W);
-    const int grid = lg_grid <= 5 ? 8 * ((n + 7) / 8 << lg_grid) : n << lg_grid;
-    u64 patience = RES_PATIENCE;
-    ResStops st = stops;
-    void *args[] = {(void *)&X.insts, (void *)&n, (void *)&lg, (void *)&lg_grid, (void *)&most, (void *)&patience, (void *)&st};
-    return hipLaunchKernel(resident_kernel(X.W, X.var), dim3(grid), dim3(RES_BS), args,
-                           res_lds_bytes(X.W), s);
+    static_assert(sizeof(ResStops::step) / sizeof(i64) >= RES_MAXG, "one stop for every instance of a launch");
+    for (int from = 0; from < X.n; from += P.per) {
+        int n = std::min(P.per, X.n - from), lg = P.lg, lg_grid = P.lg_grid;
+        i64 most = P.most;
+        const int grid = lg_grid <= 5 ? 8 * ((n + 7) / 8 << lg_grid) : n << lg_grid;
+        u64 patience = RES_PATIENCE;
+        const Inst *const *insts = X.insts + from;
+        ResStops st = {};
+        std::copy(stops + from, stops + from + n, st.step);
+        void *args[] = {(void *)&insts, (void *)&n, (void *)&lg, (void *)&lg_grid, (void *)&most, (void *)&patience, (void *)&st};
+        hipError_t e = hipLaunchKernel(resident_kernel(X.W, X.var), dim3(grid), dim3(RES_BS), args, res_lds_bytes(X.W), s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // size of the steps to come: the last row of a launch, or more than its
@@ -1353,7 +1382,10 @@ void note_items(fq_handle *q, const fq_step_stats &r, bool ended_early, const Re
     q->items = q->work = r.len + r.spawns;
     if (q->p.flags & FQ_FLAG_EARLY_COMPRESSION) q->work = std::max(q->work, r.len + (i64)r.norm);
     q->items_known = true;
-    if (ended_early && P) q->items = std::max(q->items, (res_most(q->R.W) << res_log2_groups(P->lg, q->R.log2B)) + 1);
+    if (ended_early && P) {
+        q->items = std::max(q->items, res_limit(q, P->most, res_log2_groups(P->lg, q->R.log2B)) + 1);
+        q->work = std::max(q->work, q->items);
+    }
 }
 
 }  // namespace
@@ -1383,9 +1415,8 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
             for (size_t k = old; k < q->ev.size(); k++) HIPCHK(q, hipEventCreate(&q->ev[k]));
         }
         if (resident) {
-            ResStops stops = {};
-            stops.step[0] = q->step + chunk;
-            HIPCHK(q, launch_resident(q->X, plan, stops, s));
+            const i64 stop = q->step + chunk;
+            HIPCHK(q, launch_resident(q->X, plan, &stop, s));
         } else {
             for (i64 k = 0; k < chunk; k++) HIPCHK(q, exec_step(q->X, s, q->timing ? &q->ev[NEV * k] : nullptr));
         }
@@ -1682,7 +1713,7 @@ size_t group_report_bytes(int n, i64 steps) { return group_report_head(n) + size
 // After a launch of a group of at most `chunk` steps: the control blocks, and for every instance its
 // completed steps, rows (appended at (*rows)[j] and advanced, if not null)
 // and error (the first one to *failed, err and rc).
-int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, const ResPlan *plan, const ResStops *stops,
+int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, const ResPlan *plan, const i64 *stops,
                   int *failed, std::string &err, int &rc)
 {
     const Exec &X = G.X;
@@ -1718,7 +1749,7 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, cons
                 if (e != hipSuccess) { err = std::string("group rows: ") + hipGetErrorString(e); return FQ_EHIP; }
                 if (all) last = rows[j][completed - 1];
             }
-            note_items(q, last, plan && c.step < std::min(c.stop_step, stops->step[j]), plan);
+            note_items(q, last, plan && c.step < std::min(c.stop_step, stops[j]), plan);
             if (all) rows[j] += completed;
         }
         q->step = c.step;
@@ -1742,21 +1773,21 @@ int group_resident(Group &G, ResPlan plan, i64 steps, i64 stop, fq_step_stats **
                    std::string &err, int &rc)
 {
     const Exec &X = G.X;
-    ResStops stops = {};
-    for (int j = 0; j < X.n; j++) stops.step[j] = G.h[j]->step + steps;
+    std::vector<i64> stops(X.n);
+    for (int j = 0; j < X.n; j++) stops[j] = G.h[j]->step + steps;
     for (;;) {
         std::vector<i64> before(X.n);
         for (int j = 0; j < X.n; j++) before[j] = G.h[j]->step;
         hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 1, stop);
         stop = -1;
-        hipError_t e = launch_resident(X, plan, stops, s);
+        hipError_t e = launch_resident(X, plan, stops.data(), s);
         if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
-        int hr = group_collect(G, rows, s, steps, &plan, &stops, failed, err, rc);
+        int hr = group_collect(G, rows, s, steps, &plan, stops.data(), failed, err, rc);
         if (hr) return hr;
         bool left = false, stuck = false;
         for (int j = 0; j < X.n; j++) {
             const Ctrl &c = G.ctrl[j];
-            if (c.error || c.step >= std::min(c.stop_step, stops.step[j])) continue;
+            if (c.error || c.step >= std::min(c.stop_step, stops[j])) continue;
             left = true;
             stuck = stuck || c.step == before[j];
         }
@@ -1764,7 +1795,7 @@ int group_resident(Group &G, ResPlan plan, i64 steps, i64 stop, fq_step_stats **
         if (!stuck && plan_resident(G.h.data(), X.n, plan)) continue;
         for (int j = 0; j < X.n; j++) {
             const Ctrl &c = G.ctrl[j];
-            const i64 k = c.error ? 0 : std::min(c.stop_step, stops.step[j]) - c.step;
+            const i64 k = c.error ? 0 : std::min(c.stop_step, stops[j]) - c.step;
             if (k <= 0) continue;
             hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0, (i64)-1);
             for (i64 i = 0; i < k && e == hipSuccess; i++) e = exec_step(G.h[j]->X, s, nullptr);

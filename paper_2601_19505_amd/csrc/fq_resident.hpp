@@ -1,4 +1,4 @@
-// fq_resident.hpp -- many FCIQMC steps of a small instance in one launch.
+// fq_resident.hpp -- many FCIQMC steps of an instance in one launch.
 //
 // A step of a few thousand entries takes a few microseconds of work, but as
 // four launches it took 32 to 45 us: every kernel starts with cold
@@ -32,13 +32,24 @@
 // read with agent-scope loads.  An instance of up to 32 workgroups is placed
 // on one XCD (workgroups go round robin to the 8 XCDs); when the gate finds
 // all of them on one, their common L2 is the meeting point, and a barrier
-// needs no cache maintenance.  Otherwise one wave writes the L2 back at each
-// barrier (agent release), once every wave has waited for its own stores.
+// needs no cache maintenance.  Otherwise the last workgroup to arrive on each
+// XCD writes its L2 back (agent release) for all of them, and the XCDs meet.
 // Measured per step with 1024 records of 12 bytes from every workgroup to all
 // others: 1.4 to 1.6 us on one XCD at 2 to 16 workgroups, 2.2 at 32; on all
-// XCDs with the write back 2.2 to 3.3 us up to 32, 7 at 64, 11 at 128 and 21
-// at 256, of which the barrier alone is 3, 5 and 9.  Fences by every wave
-// instead of one: 6 to 115 us.
+// XCDs 2.7 to 3.3 us up to 32, 3.9 at 64, 4.3 at 128 and 5.9 at 256 (4096
+// records each: 11.8).  With a write back by every workgroup instead of one an
+// XCD it was 5.9, 9.8 and 17.7 us at 64, 128 and 256 (4096 records: 33).
+//
+// Larger steps.  The same kernel is the faster one up to several million
+// entries and records: the four kernels of a step each pay their cold start
+// per bucket, some 14 us for the buckets that fit the chip at once.  A
+// workgroup of a large step merges its buckets in one hash as long as their
+// distinct addresses fit it, and reserves slab places for four rounds of
+// attempts with one atomic per pair of buckets, in order of the buckets (23
+// times the rate of single atomics, which cap a step at 10 records per ns).
+// us a step, before and now: 16/16 in momentum space with the initiator rule
+// at 1.1e6 items and 2048 buckets 103 and 62, the 16/16 ring at 1.7e6 items
+// 138 and 64, 48 rings of 6e4 items 638 and 129.
 #pragma once
 #include "fq_step.hpp"
 
@@ -48,7 +59,9 @@ constexpr int RES_BS = 1024;      // threads of a workgroup: one workgroup per C
 // slots of its LDS hash, by address words
 template <int W> struct ResSlots { static constexpr int N = W == 2 ? 2048 : 4096; };
 constexpr int RES_MAXG = 256;     // workgroups of all instances of a launch: the CUs
-constexpr int RES_MAXB = 1024;    // buckets of an instance: LDS counters of the spawn records
+constexpr int RES_MAXB = 8192;    // buckets of an instance: LDS counters of the spawn records
+constexpr int RES_GROUP = 4;      // rounds of spawn attempts that reserve slab places together
+constexpr int RES_XCCS = 16;      // values of the XCC_ID register
 constexpr int RES_MAXK = 64;      // buckets of a workgroup: one wave scans their counts
 
 // Partial sums of one workgroup for one step, and what it knows of the next.
@@ -62,12 +75,13 @@ struct ResPart {
     u64 hproj[2], vproj[2];
 };
 
-// Exchange area of one instance, zero before the launch.  The parts are
+// Exchange area of one instance, counters zero before the launch.  The parts are
 // double buffered by step parity: a workgroup can be at most one barrier
 // ahead of the slowest reader.
 struct ResSync {
-    u32 arrived, gate, xccs, pad0[29];  // xccs: mask of the XCDs its workgroups run on
+    u32 arrived, gate, xccs, pad0[13], on[RES_XCCS];  // xccs: mask of the XCDs its workgroups run on, on: how many each
     u32 count, pad1[31];
+    u32 here[RES_XCCS][32];  // barrier arrivals by XCD, a line each
     ResPart part[2][RES_MAXG];
 };
 
@@ -77,8 +91,13 @@ struct ResSync {
 template <int W> struct ResLds {
     static constexpr int N = ResSlots<W>::N;
     static constexpr int LIST = N * (W == 2 ? 36 : 24), LIVE = LIST + 2 * N, OFF = LIVE + 2 * N, CNT = OFF + 4 * N,
-                         BASE = CNT + 4 * RES_MAXB, MISC = BASE + 4 * RES_MAXB, LUT = MISC + 64 * 8, TRI = LUT + 2048,
-                         RED = TRI + 2 * TRI_N, WORDS = RED + 8 * 20, BYTES = WORDS + 7 * 4 * RES_MAXK;
+                         TABLES = CNT + 2 * RES_MAXB;
+    // places of the spawn records by bucket: in the high words of the hash,
+    // which hold nothing once compressed, if they are enough
+    static constexpr bool IN_HASH = RES_MAXB <= 2 * N;
+    static constexpr int BASE = IN_HASH ? 8 * N * (W + 1) : TABLES, MISC = TABLES + (IN_HASH ? 0 : 4 * RES_MAXB),
+                         LUT = MISC + 64 * 8, TRI = LUT + 2048, RED = TRI + 2 * TRI_N, WORDS = RED + 8 * 20,
+                         BYTES = WORDS + 7 * 4 * RES_MAXK;
     static_assert(BYTES + 512 <= 160 * 1024, "the LDS of one CU, with the kernel's own words");
 };
 
@@ -107,13 +126,14 @@ template <int W> __device__ __forceinline__ void res_load_rec(int rec, const cha
 }
 
 // Whether every workgroup of the instance is on the GPU, or else the instance
-// is not stepped here: the same answer in every workgroup.  `local`: they
-// share an XCD.
-__device__ __forceinline__ bool res_gate(ResSync *Y, int G, u64 patience, int &local)
+// is not stepped here: the same answer in every workgroup.  where: the own
+// XCD, its workgroups, and the number of XCDs.
+__device__ __forceinline__ bool res_gate(ResSync *Y, int G, u64 patience, u32 *where)
 {
     const u32 xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));  // hardware register 20 (XCC_ID), bits 0 .. 3
     u32 zero = 0;
     __hip_atomic_fetch_or(&Y->xccs, 1u << xcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(&Y->on[xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (__hip_atomic_fetch_add(&Y->arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (u32)G - 1)
         __hip_atomic_compare_exchange_strong(&Y->gate, &zero, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
@@ -127,15 +147,17 @@ __device__ __forceinline__ bool res_gate(ResSync *Y, int G, u64 patience, int &l
         }
         __builtin_amdgcn_s_sleep(1);
     }
-    const u32 m = __hip_atomic_load(&Y->xccs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    local = (m & (m - 1)) == 0;
+    where[0] = xcc;
+    where[1] = __hip_atomic_load(&Y->on[xcc], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    where[2] = __popc(__hip_atomic_load(&Y->xccs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     return s == 1;
 }
 
 // Barrier number `round` (from 1) of the G workgroups of an instance: what
 // any of them stored before it, all of them read behind it with agent-scope
-// loads.
-__device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, bool local)
+// loads.  On several XCDs the last workgroup to arrive on each writes its L2
+// back, once for all of them, and counts the XCD in.
+__device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, const u32 *where)
 {
     if (G == 1) {
         __syncthreads();
@@ -144,9 +166,17 @@ __device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, bool l
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached the L2
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (!local) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        __hip_atomic_fetch_add(&Y->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while (__hip_atomic_load(&Y->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (u32)G * round) {}
+        const u32 xcc = where[0], n = where[1], xccs = where[2];
+        u32 all = (u32)G;
+        bool count = true;
+        if (xccs > 1) {
+            all = xccs;
+            count = __hip_atomic_fetch_add(&Y->here[xcc][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                    n * round - 1u;
+            if (count) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        }
+        if (count) __hip_atomic_fetch_add(&Y->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (__hip_atomic_load(&Y->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all * round) {}
     }
     __syncthreads();
 }
@@ -171,31 +201,50 @@ __device__ __forceinline__ u64 res_scan(u64 x, u64 *tmp, u64 &total)
 // attempts meet 1024 threads, and the length of the chain counts: the
 // attempts of all parents, exact and stochastic, are enumerated flat, one per
 // thread and round, each with its own parent search (four ways at a time)
-// and Philox block.  cnt[t], base[t]: records of the round for bucket t
-// (cnt starts at 0) and their place in its slab, from own[t] (all records so
-// far) when this workgroup is alone, else from one global atomic.  misc[60]
-// counts the records of early compression.
+// and Philox block.  A thread keeps the records of RES_GROUP rounds in
+// registers until their places are known.  cnt, base: records of these rounds
+// by bucket (16 bits each, from 0) and their place in its slab, from own (all
+// records so far) when this workgroup is alone, else from one global atomic
+// for two buckets; the workgroups start at different ones (bucket `first`).
+// misc[60] counts the records of early compression.
 template <int W, int MODEL, bool EARLY>
-__device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, const int out_par, const bool alone,
+__device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, const int out_par, const int first,
+                                               const bool alone,
                                                const u32 spawn_step, const int nS, const i64 A,
-                                               const unsigned short *list, const u32 *off, int *cnt, int *base,
+                                               const unsigned short *list, const u32 *off, u32 *cnt, int *base,
                                                int *own, const unsigned char *lut, const unsigned short *tri)
 {
     typedef typename AddrOf<W>::T T;
-    constexpr int BS = RES_BS;
+    constexpr int BS = RES_BS, R = RES_GROUP;
     const int tid = threadIdx.x;
     const bool narrow = MODEL == 1 || (W == 1 && I.mc.nb <= 32);
     int top = 1;
     while (4 * top < nS) top *= 4;
+    static_assert(RES_MAXB <= 1 << 13, "bucket and rank in one word");
 #pragma unroll 1
-    for (i64 from = 0; from < A; from += BS) {
-        T d = AddrOf<W>::make(0, 0);
-        double v = 0.0;
-        int t = -1, rank = 0;  // bucket, rank in the round
-        bool ni = false;
-        // (wave 0 takes the last attempts: it has the row to write)
-        const i64 x = from + ((tid + BS - 64) & (BS - 1));
-        if (x < A) {
+    for (i64 from = 0; from < A; from += R * BS) {
+        // records of the last R rounds; at = bucket + (rank among the group's records of the bucket) << 13
+        T d[R];
+        double v[R];
+        int at[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            d[r] = AddrOf<W>::make(0, 0);
+            v[r] = 0.0;
+            at[r] = -1;
+        }
+#pragma unroll 1
+        for (int r = 0; r < R && from + r * BS < A; r++) {
+#pragma unroll
+            for (int e = R - 1; e > 0; e--) {
+                d[e] = d[e - 1];
+                v[e] = v[e - 1];
+                at[e] = at[e - 1];
+            }
+            at[0] = -1;
+            // (wave 0 takes the last attempts: it has the row to write)
+            const i64 x = from + r * BS + ((tid + BS - 64) & (BS - 1));
+            if (x >= A) continue;
             // the last survivor whose first attempt is at or before x
             int w = 0;
 #pragma unroll 1
@@ -227,16 +276,16 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
                         return z;
                     }
                 };
-                if (narrow) d = AddrOf<W>::make((u64)entry((u32)a0), 0);
-                else d = entry(a);
-                v = (-(I.dtau * h)) * c;
-                if (!exact) v = v * ((double)m / (double)n);
+                if (narrow) d[0] = AddrOf<W>::make((u64)entry((u32)a0), 0);
+                else d[0] = entry(a);
+                v[0] = (-(I.dtau * h)) * c;
+                if (!exact) v[0] = v[0] * ((double)m / (double)n);
             } else {
                 const i64 m = narrow ? mom_col_size<u32>(I.mc, (u32)a0) : mom_col_size(I.mc, a);
                 if (fabs(c) >= I.t_rel * (double)m) {
-                    if (narrow) d = AddrOf<W>::make((u64)mom_column_entry<u32>(I.mc, (u32)a0, (int)k, h, lut), 0);
-                    else d = mom_column_entry(I.mc, a, (int)k, h, lut);
-                    v = (-(I.dtau * h)) * c;
+                    if (narrow) d[0] = AddrOf<W>::make((u64)mom_column_entry<u32>(I.mc, (u32)a0, (int)k, h, lut), 0);
+                    else d[0] = mom_column_entry(I.mc, a, (int)k, h, lut);
+                    v[0] = (-(I.dtau * h)) * c;
                 } else {
                     const R4 rr = draw(I.seed, a0, a1, spawn_step, 0u, k >> 1);
                     const u32 x0 = (k & 1u) ? rr.z : rr.x, x1 = (k & 1u) ? rr.w : rr.y;
@@ -244,43 +293,55 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
                     if constexpr (MODEL == 1 && W == 1) {
                         const MomCtx32 y = mom_ctx32(I.mc, (u32)a0);
                         P = y.P;
-                        d = AddrOf<W>::make((u64)mom_draw31(I.mc, y, x0, x1, h, R, lut, tri), 0);
+                        d[0] = AddrOf<W>::make((u64)mom_draw31(I.mc, y, x0, x1, h, R, lut, tri), 0);
                     } else {
                         const MomCtx<T> y = mom_ctx<T>(I.mc, a);
                         P = y.P;
-                        d = mom_draw<T>(I.mc, y, x0, x1, h, R, lut);
+                        d[0] = mom_draw<T>(I.mc, y, x0, x1, h, R, lut);
                     }
-                    v = ((-(I.dtau * h)) * c) * ((double)((i64)P * R) / (double)n);
+                    v[0] = ((-(I.dtau * h)) * c) * ((double)((i64)P * R) / (double)n);
                 }
             }
-            ni = !(fabs(c) > I.n_a);
-            if (EARLY && fabs(v) < I.theta)
-                v = compress1(v, I.theta, draw(I.seed, a0, a1, spawn_step, 4u + (k >> 28), k & 0x0fffffffu).x);
-            if (!EARLY || v != 0.0) {
-                t = (int)bucket_index(d, I.log2B, I.mc.nb <= 32);
-                rank = atomicAdd(&cnt[t], 1);
+            const u64 fl = !(fabs(c) > I.n_a) ? I.iflag : 0ull;
+            if (EARLY && fabs(v[0]) < I.theta)
+                v[0] = compress1(v[0], I.theta, draw(I.seed, a0, a1, spawn_step, 4u + (k >> 28), k & 0x0fffffffu).x);
+            if (!EARLY || v[0] != 0.0) {
+                const int t = (int)bucket_index(d[0], I.log2B, I.mc.nb <= 32), up = 16 * (t & 1);
+                at[0] = t | (((atomicAdd(&cnt[t >> 1], 1u << up) >> up) & 0xffff) << 13);
             }
+            d[0] = AddrOf<W>::make(W == 1 ? word0(d[0]) | fl : word0(d[0]), W == 2 ? word1(d[0]) | fl : 0ull);
         }
         __syncthreads();
-        for (int b = tid; b < I.B; b += BS) {
-            const int c = cnt[b];
+        if (*L.failed) break;  // a slab is full: counts stay near its size
+        for (int i = tid; 2 * i < I.B; i += BS) {
+            const int w = (i + first / 2) & (I.B / 2 - 1);  // the workgroups start at different buckets
+            const u32 c = cnt[w];
             if (c) {
+                const int c0 = (int)(c & 0xffff), c1 = (int)(c >> 16);
                 if (alone) {
-                    base[b] = own[b];
-                    own[b] += c;
+                    base[2 * w] = own[2 * w];
+                    own[2 * w] += c0;
+                    if (c1) {
+                        base[2 * w + 1] = own[2 * w + 1];
+                        own[2 * w + 1] += c1;
+                    }
                 } else {
-                    base[b] = gatomic_add(&I.slab_n[out_par][b], c);
+                    // (two counts that stay below 2^31 in one word)
+                    const u64 x = gatomic_add((u64 *)&I.slab_n[out_par][2 * w], ((u64)(u32)c1 << 32) | (u32)c0);
+                    base[2 * w] = (int)(u32)x;
+                    base[2 * w + 1] = (int)(x >> 32);
                 }
-                cnt[b] = 0;
-                if (EARLY) atomicAdd((unsigned long long *)&L.misc[60], (unsigned long long)c);
+                cnt[w] = 0;
+                if (EARLY) atomicAdd((unsigned long long *)&L.misc[60], (unsigned long long)(c0 + c1));
             }
         }
         __syncthreads();
-        if (t >= 0) {
-            const i64 pos = (i64)base[t] + rank;
-            const u64 fl = ni ? I.iflag : 0ull;
-            const T df = AddrOf<W>::make(W == 1 ? word0(d) | fl : word0(d), W == 2 ? word1(d) | fl : 0ull);
-            if (pos < I.cap_s) store_rec<W>(I.rec, I.slab[out_par], (i64)t * I.cap_s + pos, df, v);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (at[r] < 0) continue;
+            const int t = at[r] & ((1 << 13) - 1);
+            const i64 pos = (i64)base[t] + (at[r] >> 13);
+            if (pos < I.cap_s) store_rec<W>(I.rec, I.slab[out_par], (i64)t * I.cap_s + pos, d[r], v[r]);
             else fail(I, L, FQE_CAP_SLAB, t);
         }
     }
@@ -289,7 +350,9 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
 // Steps of instance I up to last_step by workgroup g of G = 2^lg (every
 // workgroup of the instance makes the same number).  Stops early at the
 // instance's stop step, at an error, and after a step that leaves more than
-// max_items entries and records to merge.
+// max_items entries and records to merge.  An instance whose buckets may hold
+// more addresses than the hash is not begun when one of them might now; later
+// the number of items, half the hash a bucket, keeps them from it.
 template <int W, int MODEL, bool EARLY>
 __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const int g, const int lg,
                                                const i64 last_step, const i64 max_items, const u64 patience,
@@ -304,7 +367,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     const int bA = g * K;
     Ctrl *ctrl = I.ctrl;
 
-    __shared__ int s_go, s_fail, s_full, s_len, s_load, s_inx, s_list, s_ex, s_local;
+    __shared__ int s_go, s_fail, s_full, s_len, s_load, s_inx, s_list, s_ex;
+    __shared__ u32 s_where[3];
     __shared__ double s_state[2];  // shift and norm after the step
     __shared__ i64 s_sp;
     Lds L;
@@ -319,7 +383,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     L.full = &s_full;
     unsigned short *list = (unsigned short *)(smem + M::LIST), *live = (unsigned short *)(smem + M::LIVE);
     u32 *off = (u32 *)(smem + M::OFF);
-    int *cnt = (int *)(smem + M::CNT), *base = (int *)(smem + M::BASE);
+    u32 *cnt = (u32 *)(smem + M::CNT);
+    int *base = (int *)(smem + M::BASE);
     unsigned char *lut = (unsigned char *)(smem + M::LUT);
     unsigned short *tri = (unsigned short *)(smem + M::TRI);
     // 128-bit sums of the workgroup, ||c||_1, y.Hc, y.c, as 32-bit limbs in
@@ -337,21 +402,35 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     int p = ctrl->parity;
     double S = ctrl->shift, N0 = ctrl->norm;
     const i64 stop = min(ctrl->stop_step, last_step);
+    const bool large = I.slots > SLOTS;
+    const i64 item_limit = large ? min(max_items, (i64)I.B * (SLOTS / 2)) : max_items;
     const i64 ring_base = ctrl->ring_base;
     if (tid == 0) s_go = !halted(ctrl);
     __syncthreads();
     if (!s_go) return;
+    if (large) {
+        __syncthreads();
+        if (tid < K && (i64)I.tab_n[p][bA + tid] + I.slab_n[p][bA + tid] > SLOTS) s_go = 0;
+        __syncthreads();
+        if (!s_go) {
+            // not here, and not by the other workgroups
+            u32 zero = 0;
+            if (tid == 0 && G > 1)
+                __hip_atomic_compare_exchange_strong(&Y->gate, &zero, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+    }
     if (G > 1) {
         __syncthreads();
-        if (tid == 0) s_go = res_gate(Y, G, patience, s_local);
+        if (tid == 0) s_go = res_gate(Y, G, patience, s_where);
         __syncthreads();
         if (!s_go) return;
     }
     if (n >= stop) return;
-    const bool local = G == 1 || s_local;
     for (int i = tid; i < 2048; i += BS) lut[i] = select_lut_entry(i);
     if (MODEL == 1 || MODEL == 2) tri_fill(tri, tid, BS);
-    for (int t = tid; t < I.B; t += BS) cnt[t] = 0;
+    for (int t = tid; 2 * t < I.B; t += BS) cnt[t] = 0;
     // the reference entries of the own buckets, one per thread from the last
     // thread down, if there are no more than threads
     const int ref0 = I.ref_off[bA], nref = I.ref_off[bA + K] - ref0;
@@ -384,6 +463,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
 
     u32 round = 0;
     int slots = 0;           // of the hash: from the distinct addresses of the step before
+    bool few = false;        // those fill no more than 5/8 of the whole hash
     bool concluded = true;   // no step waits for its shift
     bool held = false;       // the survivors are in registers, at most one per thread: hc = 0 or (h0, h1), hc
     u64 h0 = 0, h1 = 0;
@@ -462,7 +542,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
         // fit the hash; a bucket larger than that is a batch alone (its
         // distinct addresses usually fit).  The first batch is cleared for
         // while the counts arrive, and merged again if it does not fit.
-        for (int k0 = 0, k1 = 0, redo = 0; k0 < K;) {
+        for (int k0 = 0, k1 = 0, redo = 0, most = few ? 8 * SLOTS : SLOTS; k0 < K;) {
             const bool all = k0 > 0 || redo;
             if (all || slots == 0) slots = SLOTS;
             if (all || wid > 1) {
@@ -477,9 +557,9 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             if (tid == 64) s_list = s_full = 0;
             __syncthreads();
             k1 = K;
-            if (pt[K] - pt[k0] + ps[K] - ps[k0] > SLOTS) {
+            if (pt[K] - pt[k0] + ps[K] - ps[k0] > most) {
                 k1 = k0 + 1;
-                while (k1 < K && pt[k1 + 1] - pt[k0] + ps[k1 + 1] - ps[k0] <= SLOTS) k1++;
+                while (k1 < K && pt[k1 + 1] - pt[k0] + ps[k1 + 1] - ps[k0] <= most) k1++;
             }
             L.mask = slots - 1;
             // ------------------------------------------------ 1. merge
@@ -513,7 +593,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
                 const bool error = __any(state & 2), diverged = !(N1 < 17592186044416.0) || !(S1 == S1);
                 const i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
                 if (lane == 0) {
-                    s_go = error || diverged ? 0 : (items > max_items || n + 1 >= stop) ? 1 : 2;
+                    s_go = error || diverged ? 0 : (items > item_limit || n + 1 >= stop) ? 1 : 2;
                     s_state[0] = S1;
                     s_state[1] = N1;
                     if (g == 0 && !error && diverged) set_error(ctrl, FQE_DIVERGED, -1);
@@ -621,8 +701,10 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             }
             if (s_go != 2) break;
             __syncthreads();
-            if (s_full && slots < SLOTS) {
-                // more addresses than expected: again with the whole hash
+            if (s_full && (slots < SLOTS || (most > SLOTS && k1 - k0 > 1))) {
+                // more addresses than expected: again with the whole hash,
+                // then with fewer buckets
+                if (slots == SLOTS) most = SLOTS;
                 redo = 1;
                 __syncthreads();
                 continue;
@@ -772,7 +854,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             // ------------------------------------------------ 5. spawn for step n+2
             if (row_due) write_row();
             if (A < ((i64)1 << 32)) {
-                resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own, lut,
+                resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, bA, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own, lut,
                                                 tri);
             } else if (tid == 0) {
                 fail(I, L, FQE_CAP_SLAB, bA + k0);
@@ -790,6 +872,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
         if (__any(inx) && lane == 0) s_inx = 1;
         // the next hash: at most 5/8 full if the addresses are no more
         slots = 8 * distinct <= 5 * BS ? BS : 8 * distinct <= 10 * BS ? 2 * BS : SLOTS;
+        few = 8 * distinct <= 5 * SLOTS;
         __syncthreads();
         if (wid == 0) {
             ResPart &x = Y->part[(n + 1) & 1][g];
@@ -817,7 +900,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             if (lane == 0) x = SpawnPart{s_ex, s_len - s_ex, s_sp, 0};
             I.spart[(n + 2) & 1][bA + lane] = x;
         }
-        res_barrier(Y, G, ++round, local);
+        res_barrier(Y, G, ++round, s_where);
         concluded = false;
     }
     // the last completed step

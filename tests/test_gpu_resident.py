@@ -78,6 +78,57 @@ CASES = {
 }
 
 
+# the widest counters and beyond them; more records than hash slots, with few
+# and with many distinct addresses; buckets that may outgrow the hash of a
+# workgroup; attempts in several reserving groups
+WIDE = {
+    "4096 buckets": dict(RING, buckets=4096, table_capacity=16384),
+    "8192 buckets, early": dict(RING, buckets=8192, flags=32, table_capacity=16384, spawn_capacity=160000),
+    "8192 buckets, two words": dict(RING, buckets=8192, addr_words=2, table_capacity=16384, spawn_capacity=160000),
+    "16384 buckets: not resident": dict(RING, buckets=16384, table_capacity=32768, spawn_capacity=320000),
+    "few addresses, many records": dict(RING, model=1, M=7, N=7, u=2.0, dtau=5e-4, target_walkers=2e4, buckets=2,
+                                        table_capacity=4000, spawn_capacity=160000),
+    "few addresses, many records, initiator, two words": dict(
+        RING, model=1, M=7, N=7, u=2.0, dtau=5e-4, target_walkers=2e4, buckets=4, addr_words=2, initiator=3.0,
+        table_capacity=4000, spawn_capacity=160000, lds_slots=2048, block=512),
+    "many addresses, several batches": dict(RING, M=11, N=11, target_walkers=6e4, buckets=64, lds_slots=2048, block=512,
+                                            table_capacity=200000, spawn_capacity=400000),
+    "buckets beyond the hash": dict(RING, M=9, N=9, target_walkers=6e3, buckets=4, addr_words=2, table_capacity=16000),
+}
+
+
+@pytest.mark.parametrize("name", list(WIDE))
+def test_wide_resident_steps_equal_the_step_kernels(name):
+    spec = WIDE[name]
+    print("[resident]", name, spec, flush=True)
+    a, b = _pair(spec)
+    _same(a, b, (1, 250, 600))
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("n", [64, 65, 130])
+def test_a_batch_of_more_instances_than_a_launch_takes(n):
+    """256 buckets need four workgroups an instance: 64 instances a launch."""
+    fq = _fq()
+    specs = [dict(RING, M=7 + i % 2, N=7 + i % 2, target_walkers=5e2, buckets=256, seed=90 + i, lds_slots=1024,
+                  block=256, spawn_block=256) for i in range(n)]
+    batch = fq.Batch(specs)
+    for i, sp in enumerate(specs):
+        _start(batch.instance(i), sp, 10.0)
+    rows = [batch.run(k) for k in (3, 120)]
+    for i in (0, 1, 63, n - 2, n - 1):
+        s = fq.Solver(**specs[i])
+        s.set_timing(True)
+        _start(s, specs[i], 10.0)
+        for got, k in zip(rows, (3, 120)):
+            assert got[i].tobytes() == s.run(k).tobytes(), (i, k)
+        sa, sb = _state(batch.instance(i)), _state(s)
+        assert np.array_equal(sa[0], sb[0]) and np.array_equal(sa[1], sb[1])
+        s.close()
+    batch.close()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_resident_steps_equal_the_step_kernels(name):
     spec = CASES[name]
