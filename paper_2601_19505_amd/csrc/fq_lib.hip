@@ -373,6 +373,18 @@ template <int W> const void *resident_kernel_w(int m, bool e)
 
 int res_lds_bytes(int W) { return W == 1 ? ResLds<1>::BYTES : ResLds<2>::BYTES; }
 
+template <int W> const void *replica_kernel_w(int m)
+{
+    switch (m) {
+    case 0: return (const void *)k_resident_replicas<W, 0>;
+    case 1: return (const void *)k_resident_replicas<W, 1>;
+    case 2: return (const void *)k_resident_replicas<W, 2>;
+    default: return (const void *)k_resident_replicas<W, 3>;
+    }
+}
+// (late compression: var < 4)
+const void *replica_kernel(int W, int var) { return W == 1 ? replica_kernel_w<1>(var) : replica_kernel_w<2>(var); }
+
 const void *resident_kernel(int W, int var)
 {
     return W == 1 ? resident_kernel_w<1>(var % 4, var >= 4) : resident_kernel_w<2>(var % 4, var >= 4);
@@ -441,6 +453,7 @@ struct Pinned {
 constexpr size_t REF_TMP_COLUMN = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP;
 constexpr size_t REF_TMP_NOTE = REF_TMP_COLUMN + 16, REF_TMP_BYTES = REF_TMP_COLUMN + 64;
 static_assert(REF_TMP_NOTE + sizeof(InsertNote) <= REF_TMP_BYTES, "the note fits behind the column");
+static_assert(RES_MAXR >= FQ_MAX_REPLICAS, "a parity for every replica");
 static_assert(sizeof(ResSync) <= REF_TMP_BYTES, "the exchange area of resident steps lies in the set-state staging");
 static_assert(sizeof(StepStats) == sizeof(fq_step_stats), "StepStats mirrors fq_step_stats");
 
@@ -1355,6 +1368,34 @@ bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
     return fits;
 }
 
+// The same for n replicas with their overlaps, in one launch (late
+// compression; at most half as many workgroups as buckets, whose sums share
+// O.part).  The hash of a workgroup has to hold its part of the vector until
+// the overlaps are summed, so the items of a step stay below its slots;
+// larger replicas keep the step and overlap kernels.
+i64 replica_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
+bool plan_replicas(fq_handle *const *h, int n, int var, ResPlan &P)
+{
+    if (n > RES_MAXR || var >= 4 || !plan_resident(h, n, P)) return false;
+    const int log2B = h[0]->R.log2B;
+    i64 items = 0, work = 0;
+    for (int i = 0; i < n; i++) {
+        items += h[i]->items;
+        work += h[i]->work;
+    }
+    bool fits = false;
+    for (int lg = res_log2_groups(0, log2B); lg < log2B && n << lg <= RES_MAXG; lg++) {
+        const i64 all = (i64)n << lg;
+        P.lg = P.lg_grid = lg;
+        P.per = n;
+        fits = items <= all * replica_most(h[0]->R.W) && items <= n * res_limit(h[0], RES_MOST, lg);
+        const bool aim = work <= all * RES_AIM;
+        P.most = aim ? std::min(RES_MORE, replica_most(h[0]->R.W)) : replica_most(h[0]->R.W);
+        if (aim) break;
+    }
+    return fits;
+}
+
 hipError_t launch_resident(const Exec &X, const ResPlan &P, const i64 *stops, hipStream_t s)
 {
     static_assert(sizeof(ResStops::step) / sizeof(i64) >= RES_MAXG, "one stop for every instance of a launch");
@@ -1371,6 +1412,16 @@ hipError_t launch_resident(const Exec &X, const ResPlan &P, const i64 *stops, hi
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+hipError_t launch_replicas(const Overlap &O, int W, int var, const ResPlan &P, i64 stop, hipStream_t s)
+{
+    Overlap o = O;
+    int lg = P.lg, spread = o.R << lg <= 32 ? 8 : 1;  // one XCD holds 32 workgroups
+    i64 most = P.most;
+    u64 patience = RES_PATIENCE;
+    void *args[] = {(void *)&o, (void *)&spread, (void *)&lg, (void *)&most, (void *)&patience, (void *)&stop};
+    return hipLaunchKernel(replica_kernel(W, var), dim3((o.R << lg) * spread), dim3(RES_BS), args, res_lds_bytes(W), s);
 }
 
 // size of the steps to come: the last row of a launch, or more than its
@@ -1818,23 +1869,31 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
     const Exec &X = G.X;
     i64 launched = 0;
     int rc = FQ_OK;
+    bool again = true;  // resident steps of replicas are worth another launch
     while (launched < steps && rc == FQ_OK) {
-        const i64 chunk = std::min<i64>(RING, steps - launched);
+        i64 chunk = std::min<i64>(RING, steps - launched);
         ResPlan plan;
         int hr;
         if (!ov && !gs && plan_resident(G.h.data(), X.n, plan)) {
             hr = group_resident(G, plan, chunk, stop, rows, s, failed, err, rc);
         } else {
-            i64 before[FQ_MAX_REPLICAS];  // (with overlaps only: no allocation there)
+            i64 before[FQ_MAX_REPLICAS], stops[FQ_MAX_REPLICAS];  // (with overlaps only: no allocation there)
             for (int j = 0; ov && j < X.n; j++) before[j] = G.h[j]->step;
-            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, 0, stop);
+            const bool resident = ov && again && plan_replicas(G.h.data(), X.n, X.var, plan);
+            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, resident ? 1 : 0, stop);
             hipError_t e = hipGetLastError();
-            for (i64 k = 0; k < chunk && e == hipSuccess; k++) {
+            if (resident) {
+                for (int j = 0; j < X.n; j++) stops[j] = before[j] + chunk;
+                if (e == hipSuccess) e = launch_replicas(ov->O, X.W, X.var, plan, before[0] + chunk, s);
+                // the overlaps of the last step made
+                if (e == hipSuccess) e = launch_overlap(*ov, s);
+            }
+            for (i64 k = 0; k < chunk && !resident && e == hipSuccess; k++) {
                 e = exec_step(X, s, nullptr, gs);
                 if (e == hipSuccess && ov) e = launch_overlap(*ov, s);
             }
             if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
-            hr = group_collect(G, rows, s, chunk, nullptr, nullptr, failed, err, rc);
+            hr = group_collect(G, rows, s, chunk, resident ? &plan : nullptr, resident ? stops : nullptr, failed, err, rc);
             if (ov && !hr) {
                 i64 done = chunk;
                 for (int j = 0; j < X.n; j++) done = std::min<i64>(done, G.ctrl[j].step - before[j]);
@@ -1842,6 +1901,23 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
                     e = hipMemcpy(ov->out, ov->O.ring, sizeof(double) * ov->O.P * done, hipMemcpyDeviceToHost);
                     if (e != hipSuccess) { err = std::string("overlap rows: ") + hipGetErrorString(e); return FQ_EHIP; }
                     ov->out += ov->O.P * done;
+                }
+                if (resident && rc == FQ_OK) {
+                    // what is left of the chunk comes with the next ones
+                    again = done > 0;
+                    chunk = done;
+                } else if (!resident) {
+                    again = true;
+                } else {
+                    // the replicas without an error make the rest of the chunk
+                    for (int j = 0; j < X.n && e == hipSuccess; j++) {
+                        if (G.ctrl[j].error) continue;
+                        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0, (i64)-1);
+                        for (i64 k = G.ctrl[j].step; k < stops[j] && e == hipSuccess; k++)
+                            e = exec_step(G.h[j]->X, s, nullptr);
+                    }
+                    if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+                    hr = group_collect(G, rows, s, chunk, nullptr, nullptr, failed, err, rc);
                 }
             }
         }
@@ -2068,6 +2144,7 @@ static int run_replicas(fq_batch *b, int64_t n_steps, fq_step_stats *stats, doub
     ov.O.ring_cap = RING;
     ov.O.flags = (int *)(sc + lay.flags);
     hipError_t e = ensure_lds(ov.W == 1 ? (const void *)k_overlap<1> : (const void *)k_overlap<2>, ov.lds);
+    if (e == hipSuccess && b->G.X.var < 4) e = ensure_lds(replica_kernel(ov.W, b->G.X.var), res_lds_bytes(ov.W));
     if (e == hipSuccess) e = hipMemcpyAsync((void *)ov.O.rep, rep, sizeof(Inst *) * R, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         // the flags start at zero (a fill kernel: the scratch may hold the

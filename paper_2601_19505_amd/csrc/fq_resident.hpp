@@ -51,6 +51,7 @@
 // at 1.1e6 items and 2048 buckets 103 and 62, the 16/16 ring at 1.7e6 items
 // 138 and 64, 48 rings of 6e4 items 638 and 129.
 #pragma once
+#include "fq_overlap.hpp"
 #include "fq_step.hpp"
 
 namespace fq {
@@ -61,6 +62,7 @@ template <int W> struct ResSlots { static constexpr int N = W == 2 ? 2048 : 4096
 constexpr int RES_MAXG = 256;     // workgroups of all instances of a launch: the CUs
 constexpr int RES_MAXB = 8192;    // buckets of an instance: LDS counters of the spawn records
 constexpr int RES_GROUP = 4;      // rounds of spawn attempts that reserve slab places together
+constexpr int RES_MAXR = 8;       // replicas
 constexpr int RES_XCCS = 16;      // values of the XCC_ID register
 constexpr int RES_MAXK = 64;      // buckets of a workgroup: one wave scans their counts
 
@@ -70,8 +72,8 @@ constexpr int RES_MAXK = 64;      // buckets of a workgroup: one wave scans thei
 struct ResPart {
     u64 norm[2];
     u64 items;    // entries from bit 40; records of the spawn pass for the next step below
-    u64 state;    // bit 0: some sum was rounded first, bit 1: the step failed; from bit 8 the
-                  // most distinct addresses in a bucket; from bit 32 exact parents of the spawn pass
+    u64 state;    // bit 0: some sum was rounded first, bit 1: the step failed, bit 2: the hash did
+                  // not hold the whole vector; from bit 8 the most distinct addresses in a bucket; from bit 32 exact parents of the spawn pass
     u64 hproj[2], vproj[2];
 };
 
@@ -178,6 +180,79 @@ __device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, const 
         if (count) __hip_atomic_fetch_add(&Y->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         while (__hip_atomic_load(&Y->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all * round) {}
     }
+    __syncthreads();
+}
+
+// Replicas (Sec. 4.3) are stepped together, with one gate and one barrier for
+// the workgroups of all of them (in the exchange area of the first), because
+// the overlaps of a step need all vectors of that step.  Workgroup g of
+// replica A still has its part of the vector in the hash when the barrier
+// behind the step opens, and the other replicas' tables hold the same buckets
+// of theirs: they are streamed against the hash before it is cleared.  What
+// the workgroups add up is published at the next barrier, in O.part (twice,
+// by parity of the round; hence at most half as many workgroups as buckets),
+// and the row written behind it.  Two replicas of the 8/8 ring in momentum
+// space at 1e3 walkers take 15.7 us a step so, 43.8 with the step and overlap
+// kernels.
+__device__ __forceinline__ void wave_scan_fx3(Fx3 &x)  // sum in lane 63
+{
+    fx3_add(x, Fx3{dpp0<0x111, 0xf>(x.w0), dpp0<0x111, 0xf>(x.w1), dpp0<0x111, 0xf>(x.w2)});
+    fx3_add(x, Fx3{dpp0<0x112, 0xf>(x.w0), dpp0<0x112, 0xf>(x.w1), dpp0<0x112, 0xf>(x.w2)});
+    fx3_add(x, Fx3{dpp0<0x114, 0xf>(x.w0), dpp0<0x114, 0xf>(x.w1), dpp0<0x114, 0xf>(x.w2)});
+    fx3_add(x, Fx3{dpp0<0x118, 0xf>(x.w0), dpp0<0x118, 0xf>(x.w1), dpp0<0x118, 0xf>(x.w2)});
+    fx3_add(x, Fx3{dpp0<0x142, 0xa>(x.w0), dpp0<0x142, 0xa>(x.w1), dpp0<0x142, 0xa>(x.w2)});
+    fx3_add(x, Fx3{dpp0<0x143, 0xc>(x.w0), dpp0<0x143, 0xc>(x.w1), dpp0<0x143, 0xc>(x.w2)});
+}
+
+// Overlaps of replica A with every later replica on the buckets [bA, bA + K):
+// its amplitudes are in the hash (low word; 0 where compressed away).
+// words: LDS, K + 1 ints and from word 2 RES_MAXK 16 Fx3; to[pair].
+template <int W>
+__device__ __forceinline__ void resident_overlap(const Overlap &O, const Lds &L, const int A, const int *parity,
+                                                 const int bA, const int K, int *words, Fx3 *to)
+{
+    constexpr int BS = RES_BS;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Fx3 *tmp = (Fx3 *)(words + 2 * RES_MAXK);
+    int inexact = 0, ovf = 0;
+#pragma unroll 1
+    for (int B = A + 1; B < O.R; B++) {
+        const Inst &IB = const_inst(O.rep[B]);
+        const int pB = parity[B];
+        if (wid == 0) {
+            int n = lane < K ? res_load(&IB.tab_n[pB][bA + lane]) : 0;
+            n = (int)wave_scan((u64)min((i64)n, IB.cap_t));
+            if (lane < K) words[lane + 1] = n;
+            if (lane == 0) words[0] = 0;
+        }
+        __syncthreads();
+        Fx3 acc = fx3_zero();
+#pragma unroll 1
+        for (int i = tid; i < words[K]; i += BS) {
+            int k = 0;
+            for (int hi = K; hi - k > 1;) {
+                const int mid = (k + hi) >> 1;
+                if (words[mid] <= i) k = mid;
+                else hi = mid;
+            }
+            const i64 e = (i64)(bA + k) * IB.cap_t + (i - words[k]);
+            const u64 a0 = res_load(&IB.tab_a[pB][0][e]), a1 = W == 2 ? res_load(&IB.tab_a[pB][1][e]) : 0;
+            const double v = bitsd(res_load((const u64 *)IB.tab_v[pB] + e));
+            const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
+            const double c = s >= 0 ? bitsd(L.lo[s]) : 0.0;
+            if (c != 0.0) fx3_add(acc, to_fx3(c * v, inexact, ovf));
+        }
+        if (__any((acc.w0 | acc.w1 | acc.w2) != 0)) wave_scan_fx3(acc);
+        if (lane == 63) tmp[wid] = acc;
+        __syncthreads();
+        if (wid == 0) {
+            acc = lane < BS / 64 ? tmp[lane] : fx3_zero();
+            wave_scan_fx3(acc);
+            if (lane == 63) to[pair_index(A, B, O.R)] = acc;
+        }
+    }
+    if (inexact) atomicOr(&O.flags[1], 1);
+    if (ovf) atomicOr(&O.flags[2], 1);
     __syncthreads();
 }
 
@@ -353,9 +428,13 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
 // max_items entries and records to merge.  An instance whose buckets may hold
 // more addresses than the hash is not begun when one of them might now; later
 // the number of items, half the hash a bucket, keeps them from it.
-template <int W, int MODEL, bool EARLY>
-__device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const int g, const int lg,
-                                               const i64 last_step, const i64 max_items, const u64 patience,
+// OV: the instance is replica `me` of O, whose replicas start at one step and
+// stop together: all of them decide from the same sums and flags.  O.ring
+// receives the overlaps of all steps but the last, whose tables the launch
+// leaves.
+template <int W, int MODEL, bool EARLY, bool OV>
+__device__ __forceinline__ void resident_steps(const Inst &I, const int g, const int lg, const i64 last_step,
+                                               const i64 max_items, const u64 patience, const Overlap &O, const int me,
                                                char *smem)
 {
     typedef typename AddrOf<W>::T T;
@@ -366,11 +445,15 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     const int K = I.B >> lg;   // buckets of this workgroup, at most RES_MAXK
     const int bA = g * K;
     Ctrl *ctrl = I.ctrl;
+    // the workgroups that meet at the barrier, and where
+    const int meet = OV ? O.R << lg : G;
+    ResSync *Y = OV ? const_inst(O.rep[0]).res : I.res;
 
     __shared__ int s_go, s_fail, s_full, s_len, s_load, s_inx, s_list, s_ex;
     __shared__ u32 s_where[3];
     __shared__ double s_state[2];  // shift and norm after the step
     __shared__ i64 s_sp;
+    __shared__ int s_par[OV ? RES_MAXR : 1];  // parity of each replica's state
     Lds L;
     L.k0 = (u64 *)smem;
     L.k1 = L.k0 + SLOTS;
@@ -407,6 +490,15 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     const i64 ring_base = ctrl->ring_base;
     if (tid == 0) s_go = !halted(ctrl);
     __syncthreads();
+    if (OV) {
+        // none is stepped when one of them cannot be: the same answer in every workgroup
+        if (tid < O.R) {
+            Ctrl *c = const_inst(O.rep[tid]).ctrl;
+            s_par[tid] = c->parity;
+            if (halted(c) || c->step != n || c->stop_step != ctrl->stop_step) s_go = 0;
+        }
+        __syncthreads();
+    }
     if (!s_go) return;
     if (large) {
         __syncthreads();
@@ -415,15 +507,15 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
         if (!s_go) {
             // not here, and not by the other workgroups
             u32 zero = 0;
-            if (tid == 0 && G > 1)
+            if (tid == 0 && meet > 1)
                 __hip_atomic_compare_exchange_strong(&Y->gate, &zero, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
             return;
         }
     }
-    if (G > 1) {
+    if (meet > 1) {
         __syncthreads();
-        if (tid == 0) s_go = res_gate(Y, G, patience, s_where);
+        if (tid == 0) s_go = res_gate(Y, meet, patience, s_where);
         __syncthreads();
         if (!s_go) return;
     }
@@ -469,6 +561,26 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
     u64 h0 = 0, h1 = 0;
     double hc = 0.0;
     bool row_due = false;    // wave 0 of workgroup 0: the row of step n is to be written
+    bool whole = true;       // the hash holds the whole vector of the step
+    bool dead = false;       // OV: this replica has diverged and waits for the others to hear of it
+    // OV, replica 0: the step whose overlaps have been published and are to be written, and from which half of O.part
+    i64 ov_step = -1;
+    Fx3 *const sums = OV ? O.part + (i64)g * O.P : nullptr;  // this workgroup's overlaps, first half
+    auto write_overlaps = [&]() {
+        const i64 row = ov_step - ring_base;
+#pragma unroll 1
+        for (int k = 0; k < O.P; k++) {
+            Fx3 x = fx3_zero();
+#pragma unroll 1
+            for (int w = lane; w < G; w += 64) {
+                const Fx3 *y = O.part + ((i64)((round & 1) ^ 1) * G + w) * O.P + k;
+                fx3_add(x, Fx3{res_load(&y->w0), res_load(&y->w1), res_load(&y->w2)});
+            }
+            wave_scan_fx3(x);
+            if (lane == 63 && row >= 0 && row < O.ring_cap) O.ring[row * O.P + k] = from_fx3(x);
+        }
+        ov_step = -1;
+    };
     auto write_row = [&]() {
         const bool flagged = red[18] || row_inx;
         // one conversion: y.Hc in lane 0, y.c in the others
@@ -502,7 +614,9 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
         // the workgroups lane, lane + 64, ..
         u64 nl = 0, nh = 0, both = 0, state = 0;
         const bool split = !concluded;
-        const ResPart *part = Y->part[(n + 1) & 1];
+        const ResPart *part = I.res->part[round & 1];
+        if (OV && split && !dead && me < O.R - 1)
+            resident_overlap<W>(O, L, me, s_par, bA, K, (int *)off, sums + (i64)(round & 1) * G * O.P);
         if (split && wid == 0) {
 #pragma unroll 1
             for (int k = lane; k < G; k += 64) {
@@ -511,8 +625,20 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
                 add128(nl, nh, x0, x1);
                 both += x2;
                 // flags joined, largest load, sum of exact parents
-                state = (state & 3) | (x3 & 3) | (max(state & 0xffffff00u, x3 & 0xffffff00u)) |
+                state = (state & 7) | (x3 & 7) | (max(state & 0xffffff00u, x3 & 0xffffff00u)) |
                         (((state >> 32) + (x3 >> 32)) << 32);
+            }
+        }
+        u64 others = 0;  // OV: flags of the other replicas; their entries and records from bit 8
+        if (OV && split && wid == 0) {
+#pragma unroll 1
+            for (int w = lane; w < meet; w += 64) {
+                const int r = w >> lg;
+                if (r == me) continue;
+                const ResPart *x = &const_inst(O.rep[r]).res->part[round & 1][w & (G - 1)];
+                const u64 it = res_load(&x->items), st = res_load(&x->state);
+                others |= st & 6;
+                others += ((it >> 40) + (it & (((u64)1 << 40) - 1))) << 8;
             }
         }
         // wave 1: the counts of the own buckets
@@ -565,7 +691,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             // ------------------------------------------------ 1. merge
             // The records first; meanwhile wave 0, which takes no items,
             // concludes the step before, whose shift scales the survivors:
-            // s_go = 0 that step failed, 1 it was the last, 2 go on.  With
+            // s_go = 0 that step failed, 1 it was the last, 2 go on, 3 it
+            // failed and the other replicas do not know.  With
             // the initiator rule the survivors come first.
             const bool waits = split && !concluded;
             if (waits && wid == 0) {
@@ -591,9 +718,18 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
                 double S1 = S;
                 if (N1 > 0.0) S1 = (S - I.zeta / I.dtau * l0) - I.xi / I.dtau * l1;
                 const bool error = __any(state & 2), diverged = !(N1 < 17592186044416.0) || !(S1 == S1);
-                const i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
+                i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
+                bool end = n + 1 >= stop;
+                if (OV) {
+                    // the same answer in every replica: after each step all go on or none
+                    items += (i64)lane_value(wave_scan(others >> 8), 63);
+                    end = end || items > item_limit * O.R || __any(((others | state) & 6) != 0);
+                } else {
+                    end = end || items > item_limit;
+                }
                 if (lane == 0) {
-                    s_go = error || diverged ? 0 : (items > item_limit || n + 1 >= stop) ? 1 : 2;
+                    // (a replica that has diverged takes part in one more step, for the others to read its flag)
+                    s_go = error ? 0 : diverged ? (OV && !end ? 3 : 0) : end ? 1 : 2;
                     s_state[0] = S1;
                     s_state[1] = N1;
                     if (g == 0 && !error && diverged) set_error(ctrl, FQE_DIVERGED, -1);
@@ -606,13 +742,14 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
                     if (waits) {
                         __syncthreads();
                         concluded = true;
-                        if (s_go) {
+                        dead = OV && s_go == 3;
+                        if (s_go == 1 || s_go == 2) {
                             n++;
                             p = p1;
                             S = lane_value(s_state[0], 0);
                             N0 = lane_value(s_state[1], 0);
                         }
-                        if (s_go && g == 0 && wid == 0) {
+                        if ((s_go == 1 || s_go == 2) && g == 0 && wid == 0) {
                             // the sums of its row, written further down
                             u64 hl = 0, hh = 0, vl = 0, vh = 0;
 #pragma unroll 1
@@ -699,7 +836,10 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
                     have = !regs && i < end;
                 }
             }
-            if (s_go != 2) break;
+            if (s_go != 2) {
+                if (OV && ov_step >= 0) write_overlaps();
+                break;
+            }
             __syncthreads();
             if (s_full && (slots < SLOTS || (most > SLOTS && k1 - k0 > 1))) {
                 // more addresses than expected: again with the whole hash,
@@ -728,7 +868,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             const u32 step1 = (u32)(n + 1);
             const int nU = s_list, kb = k1 - k0;
             distinct += nU;
-            held = k0 == 0 && k1 == K && nU <= BS - 64;
+            whole = k0 == 0 && k1 == K;
+            held = whole && nU <= BS - 64;
             u64 sum = 0;  // survivors from bit 48, attempts below
             u64 nlo = 0, nhi = 0;
             int odd = 0;
@@ -853,6 +994,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             }
             // ------------------------------------------------ 5. spawn for step n+2
             if (row_due) write_row();
+            if (OV && ov_step >= 0) write_overlaps();
             if (A < ((i64)1 << 32)) {
                 resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, bA, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own, lut,
                                                 tri);
@@ -866,7 +1008,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             k0 = k1;
             if (k0 < K) __syncthreads();
         }
-        if (s_go != 2) break;
+        if (s_go != 2 && !dead) break;
 
         // ---------------------------------------------------- 6. partial sums, barrier
         if (__any(inx) && lane == 0) s_inx = 1;
@@ -875,7 +1017,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
         few = 8 * distinct <= 5 * SLOTS;
         __syncthreads();
         if (wid == 0) {
-            ResPart &x = Y->part[(n + 1) & 1][g];
+            ResPart &x = I.res->part[(round + 1) & 1][g];
             if (lane < 3) {
                 const u64 *w = red + 4 * lane;
                 u64 *to = lane == 0 ? x.norm : lane == 1 ? x.hproj : x.vproj;
@@ -889,10 +1031,10 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             }
             if (lane == 63) {
                 x.items = ((u64)s_len << 40) + (u64)s_sp;
-                x.state = (s_inx ? 1 : 0) | (s_fail ? 2 : 0) | ((u64)s_load << 8) | ((u64)s_ex << 32);
+                x.state = (s_inx ? 1 : 0) | (s_fail || dead ? 2 : 0) | (whole ? 0 : 4) | ((u64)s_load << 8) | ((u64)s_ex << 32);
             }
         }
-        if (wid == 1 && lane < K) {
+        if (wid == 1 && lane < K && !dead) {
             __hip_atomic_store(gmem(&I.slab_n[p][bA + lane]), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // consumed
             if (G == 1)
                 __hip_atomic_store(gmem(&I.slab_n[1 - p][lane]), own[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -900,7 +1042,13 @@ __device__ __forceinline__ void resident_steps(const Inst &I, ResSync *Y, const 
             if (lane == 0) x = SpawnPart{s_ex, s_len - s_ex, s_sp, 0};
             I.spart[(n + 2) & 1][bA + lane] = x;
         }
-        res_barrier(Y, G, ++round, s_where);
+        res_barrier(Y, meet, ++round, s_where);
+        if (OV) {
+            // the overlaps of step n are published now; the first barrier of a launch publishes none
+            if (me == 0 && g == 0 && wid == 0 && round > 1 && !dead) ov_step = n;
+            if (tid < O.R) s_par[tid] ^= 1;
+            __syncthreads();
+        }
         concluded = false;
     }
     // the last completed step
