@@ -45,7 +45,9 @@ FQ_EXTERN_STEP_KERNELS
 constexpr int FIN_BS = FQ_FIN_BS;  // threads of the finalize workgroup
 __global__ __launch_bounds__(FIN_BS) void k_finalize(const Inst *const *insts)
 {
-    finalize_instance<FIN_BS>(const_inst(insts[blockIdx.x]));
+    const Inst &I = const_inst(insts[blockIdx.x]);
+    const int n = min((int)gridDim.y, fin_groups(I.B));
+    if ((int)blockIdx.y < n) finalize_instance<FIN_BS>(I, (int)blockIdx.y, n);
 }
 
 // Second partition pass; map entry = instance << 14 | coarse sub-slab.  The
@@ -92,6 +94,7 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64
         Ctrl *c = insts[i]->ctrl;
         c->ring_base = c->step + 1;
         if (stop >= 0) c->stop_step = c->step + stop;
+        insts[i]->fin->done = 0;
         if (resident) {
             ResSync *y = insts[i]->res;
             y->arrived = y->gate = y->xccs = y->count = 0;
@@ -454,6 +457,7 @@ constexpr size_t REF_TMP_COLUMN = (sizeof(u64) * 2 + sizeof(double) + sizeof(int
 constexpr size_t REF_TMP_NOTE = REF_TMP_COLUMN + 16, REF_TMP_BYTES = REF_TMP_COLUMN + 64;
 static_assert(REF_TMP_NOTE + sizeof(InsertNote) <= REF_TMP_BYTES, "the note fits behind the column");
 static_assert(RES_MAXR >= FQ_MAX_REPLICAS, "a parity for every replica");
+static_assert(sizeof(FinScratch) <= REF_TMP_BYTES, "and the sums of the finalize kernel");
 static_assert(sizeof(ResSync) <= REF_TMP_BYTES, "the exchange area of resident steps lies in the set-state staging");
 static_assert(sizeof(StepStats) == sizeof(fq_step_stats), "StepStats mirrors fq_step_stats");
 
@@ -468,6 +472,7 @@ struct Exec {
     const u32 *pmap = nullptr;    // second-pass partition map
     int pgrid = 0;
     bool wide_groups = false;     // coarse groups of more than 256 buckets
+    int fin_groups = 1;           // finalize workgroups of the largest instance
 };
 
 struct Resolved {
@@ -749,7 +754,7 @@ hipError_t exec_step(const Exec &X, hipStream_t s, hipEvent_t *ev, const GsRun *
     if (e == hipSuccess) e = launch_spawn(X, 0, s, ev ? ev[2] : nullptr);
     if (ev && e == hipSuccess) e = hipEventRecord(ev[3], s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_finalize, dim3(X.n), dim3(FIN_BS), 0, s, X.insts);
+        hipLaunchKernelGGL(k_finalize, dim3(X.n, X.fin_groups), dim3(FIN_BS), 0, s, X.insts);
         e = hipGetLastError();
     }
     if (e == hipSuccess && gs) {
@@ -957,6 +962,7 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
     I.coarse = q->ws + R.off_coarse;
     I.coarse_n = (int *)(q->ws + R.off_coarse_n);
     I.res = (ResSync *)(q->ws + R.off_ref_tmp);
+    I.fin = (FinScratch *)(q->ws + R.off_ref_tmp);
     I.spart[0] = (SpawnPart *)(q->ws + R.off_spart[0]);
     I.spart[1] = (SpawnPart *)(q->ws + R.off_spart[1]);
     q->d_inst = (Inst *)(q->ws + R.off_inst);
@@ -1014,6 +1020,7 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
     X.pmap = (const u32 *)(q->ws + R.off_pmap);
     X.pgrid = (int)pm.size();
     X.wide_groups = R.two_pass && R.log2B - R.log2G > 8;
+    X.fin_groups = fin_groups(R.B);
     *out = q;
     return FQ_OK;
 }
@@ -1725,6 +1732,7 @@ int group_build(Group &G, std::vector<fq_handle *> hs, char *hdr, std::string &e
     G.X.pgrid = (int)pmap.size();
     // instances are sorted by bucket count: the first has the widest groups
     G.X.wide_groups = hs[0]->X.wide_groups;
+    G.X.fin_groups = hs[0]->X.fin_groups;
     G.X.lds_s = lds_s;
     G.X.lds_m = lds_m;
     G.ctrl.resize(n);

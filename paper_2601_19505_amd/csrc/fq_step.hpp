@@ -121,6 +121,7 @@ struct Inst {
     double n_a;
     char *coarse;
     int *coarse_n;
+    struct FinScratch *fin;  // sums of the finalize workgroups (shares that memory as well)
     struct ResSync *res;  // exchange area of resident steps (shares the memory of the set-state staging)
 };
 
@@ -1483,14 +1484,28 @@ template <int W, int BS, int RPT, int FMAX> __device__ void partition_coarse(con
 
 // ---------------------------------------------------------------- finalize
 
-// One workgroup: reduce the per-bucket partials of the step that just ran,
+// Workgroup w of n: reduce the per-bucket partials of the step that just ran,
 // update the shift (Eq. shift-update), write the statistics row, release the
 // consumed spawn slab.  Exact integer reductions, so the result does not
-// depend on the number of buckets.
-template <int BS> __device__ void finalize_instance(const Inst &I)
+// depend on the number of buckets or workgroups.  The partials of 16384
+// buckets are 1.6 MB, which one workgroup takes 50 us to read (its loads in
+// flight bound it).  With one workgroup per FIN_BUCKETS buckets each leaves its
+// sums in the scratch, and the last one to do so (they count themselves in Z.done,
+// zero before and after) goes on with all of them: 21 us.  Up to 1024 buckets
+// one workgroup is as fast (6 us).
+constexpr int FIN_BUCKETS = 512, FIN_MOST = 32;
+struct FinScratch {
+    u32 done, pad[31];
+    u64 sums[FIN_MOST][12];
+};
+__host__ __device__ __forceinline__ int fin_groups(int B)
+{
+    return B <= 2 * FIN_BUCKETS ? 1 : B / FIN_BUCKETS < FIN_MOST ? B / FIN_BUCKETS : FIN_MOST;
+}
+template <int BS> __device__ void finalize_instance(const Inst &I, const int w, const int n_groups)
 {
     __shared__ u64 red[BS / 64][12];  // the 12th word: inexact flags
-    __shared__ int s_err;
+    __shared__ int s_err, s_last;
     Ctrl *ctrl = I.ctrl;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     if (tid == 0) s_err = halted(ctrl);
@@ -1502,7 +1517,7 @@ template <int BS> __device__ void finalize_instance(const Inst &I)
     u64 nl = 0, nh = 0, hl = 0, hh = 0, vl = 0, vh = 0;
     i64 len = 0, load = 0, ex = 0, in = 0, sp = 0, inx = 0;
     const SpawnPart *spp = I.spart[(n + 1) & 1];
-    for (int b = tid; b < I.B; b += BS) {
+    for (int b = w * BS + tid; b < I.B; b += n_groups * BS) {
         const Part pt = I.part[b];
         add128(nl, nh, pt.norm[0], pt.norm[1]);
         add128(hl, hh, pt.hproj[0], pt.hproj[1]);
@@ -1536,18 +1551,39 @@ template <int BS> __device__ void finalize_instance(const Inst &I)
         red[wid][8] = (u64)ex; red[wid][9] = (u64)in; red[wid][10] = (u64)sp; red[wid][11] = (u64)inx;
     }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < BS / 64; w++) {
-            add128(nl, nh, red[w][0], red[w][1]);
-            add128(hl, hh, red[w][2], red[w][3]);
-            add128(vl, vh, red[w][4], red[w][5]);
-            len += (i64)red[w][6];
-            load = max(load, (i64)red[w][7]);
-            ex += (i64)red[w][8];
-            in += (i64)red[w][9];
-            sp += (i64)red[w][10];
-            inx |= (i64)red[w][11];
+    auto join = [&](const u64 *x) {
+        add128(nl, nh, x[0], x[1]);
+        add128(hl, hh, x[2], x[3]);
+        add128(vl, vh, x[4], x[5]);
+        len += (i64)x[6];
+        load = max(load, (i64)x[7]);
+        ex += (i64)x[8];
+        in += (i64)x[9];
+        sp += (i64)x[10];
+        inx |= (i64)x[11];
+    };
+    if (tid == 0)
+        for (int k = 1; k < BS / 64; k++) join(red[k]);
+    if (n_groups > 1) {
+        FinScratch &Z = *I.fin;
+        if (tid == 0) {
+            const u64 x[12] = {nl, nh, hl, hh, vl, vh, (u64)len, (u64)load, (u64)ex, (u64)in, (u64)sp, (u64)inx};
+            for (int k = 0; k < 12; k++) __hip_atomic_store(&Z.sums[w][k], x[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_last = __hip_atomic_fetch_add(&Z.done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (u32)n_groups - 1;
         }
+        __syncthreads();
+        if (!s_last) return;
+        __shared__ u64 sums[FIN_MOST][12];
+        for (int k = tid; k < n_groups * 12; k += BS)
+            (&sums[0][0])[k] = __hip_atomic_load(&Z.sums[0][0] + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (tid == 0) {
+            Z.done = 0;
+            for (int k = 0; k < n_groups; k++)
+                if (k != w) join(sums[k]);
+        }
+    }
+    if (tid == 0) {
         const double N1 = from_fixed(nl, nh);
         const double hp = from_fixed(hl, hh);
         const double vp = from_fixed(vl, vh);
