@@ -289,9 +289,9 @@ __global__ void k_ref(const Inst *Ip, u64 r0, u64 r1, u64 *oa, double *oh, int *
     *on = (int)m + 1;
 }
 
-// copy table[parity] into contiguous arrays
+// copy table[parity] into contiguous arrays, ew words per address
 template <int W>
-__global__ __launch_bounds__(256) void k_pack(const Inst *Ip, u64 *oa, double *ov, unsigned long long *cnt)
+__global__ __launch_bounds__(256) void k_pack(const Inst *Ip, u64 *oa, double *ov, int ew, unsigned long long *cnt)
 {
     const Inst &I = *Ip;
     const int p = I.ctrl->parity;
@@ -302,8 +302,8 @@ __global__ __launch_bounds__(256) void k_pack(const Inst *Ip, u64 *oa, double *o
         __syncthreads();
         for (int i = threadIdx.x; i < nb; i += blockDim.x) {
             i64 s = (i64)b * I.cap_t + i, d = (i64)base + i;
-            oa[d * W] = I.tab_a[p][0][s];
-            if (W == 2) oa[d * W + 1] = I.tab_a[p][1][s];
+            oa[d * ew] = I.tab_a[p][0][s];
+            if (ew == 2) oa[d * ew + 1] = W == 2 ? I.tab_a[p][1][s] : 0;
             ov[d] = I.tab_v[p][s];
         }
         __syncthreads();
@@ -476,7 +476,8 @@ struct Exec {
 };
 
 struct Resolved {
-    int W, nb, B, log2B, slots, block, spawn_block, two_pass, log2G, log2SUB;
+    int W, E;  // address words of the kernels, and of the caller
+    int nb, B, log2B, slots, block, spawn_block, two_pass, log2G, log2SUB;
     bool init;  // the initiator rule
     i64 cap_t, cap_s, cap_c, dump_cap;
     size_t rec, slab_bytes;  // bytes per spawn record; bytes of one slab
@@ -543,8 +544,20 @@ int validate(const fq_hamiltonian *h, const fq_params *p, std::string &err)
     return FQ_OK;
 }
 
+// Two-word addresses of at most 62 bits are kept in one word: tables, records
+// and the hash are 16 bytes an entry instead of 24, and the hash needs no
+// slot states.  The 20/20 ring (39 bits) at 1e7 walkers: 628 us a step so, 964
+// in two words (merge 276 and 489, spawn 244 and 340, partition 88 and 114).
+// Not with dumps, which hold the words as the kernels do, and not beside wider
+// instances in a group, whose kernels are compiled for one width (`wide`).
+// Sizes and limits stay those of the caller's words.
+bool narrow(const fq_hamiltonian *h, const fq_params *p)
+{
+    return p->addr_words == 2 && h->N + h->M - 1 <= 62 && !(p->flags & (FQ_FLAG_DUMP_SPAWNS | FQ_FLAG_DUMP_MERGED));
+}
+
 int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, Resolved &R, fq_layout &lout,
-            std::string &err)
+            std::string &err, bool wide = false)
 {
     int rc = validate(h, p, err);
     if (rc) return rc;
@@ -554,7 +567,8 @@ int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, R
     }
     fq_layout L = *lin;
     L.spawn_capacity = std::max(L.spawn_capacity, L.table_capacity);
-    R.W = p->addr_words;
+    R.E = p->addr_words;
+    R.W = !wide && narrow(h, p) ? 1 : R.E;
     R.nb = h->N + h->M - 1;
     R.init = (p->flags & FQ_FLAG_INITIATOR) != 0;
     if (L.lds_slots == 0) L.lds_slots = 4096;
@@ -570,7 +584,7 @@ int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, R
         err = "spawn_block must be 256, 512 or 1024";
         return FQ_EINVAL;
     }
-    if (lds_bytes(R.W, L.lds_slots, R.init) > LDS_MAX) { err = "LDS budget exceeded: lower lds_slots or block"; return FQ_EINVAL; }
+    if (lds_bytes(R.E, L.lds_slots, R.init) > LDS_MAX) { err = "LDS budget exceeded: lower lds_slots or block"; return FQ_EINVAL; }
     if (L.buckets == 0) {
         double uniq = (double)L.table_capacity + 0.25 * (double)L.spawn_capacity;
         i64 b = (i64)std::ceil(uniq / (0.55 * L.lds_slots));
@@ -604,10 +618,11 @@ int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, R
         R.dump_cap = (p->flags & (FQ_FLAG_DUMP_SPAWNS | FQ_FLAG_DUMP_MERGED)) ? (k ? 2 * (all >> k) + 65536 : all) : 0;
     }
     R.nsq = (h->N + 2) * (h->N + 2) + 8;
-    // a slab also stages a whole table (8W + 8 bytes per entry) for
+    // a slab also stages a whole table (8 E + 8 bytes per entry) for
     // set_state, get_state and copy_state
     R.rec = rec_bytes(R.W, R.nb, R.init);
-    R.slab_bytes = std::max(R.rec * (size_t)R.B * R.cap_s, (size_t)(8 * R.W + 8) * (size_t)R.B * R.cap_t + 256);
+    const size_t rec = rec_bytes(R.E, R.nb, R.init);
+    R.slab_bytes = std::max(rec * (size_t)R.B * R.cap_s, (size_t)(8 * R.E + 8) * (size_t)R.B * R.cap_t + 256);
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t r = o; o = align256(o + bytes); return r; };
     R.off_ctrl = take(sizeof(Ctrl));
@@ -630,20 +645,20 @@ int resolve(const fq_hamiltonian *h, const fq_params *p, const fq_layout *lin, R
     const i64 tn = (i64)R.B * R.cap_t;
     for (int q = 0; q < 2; q++) {
         R.off_tab_a[q][0] = take(sizeof(u64) * tn);
-        R.off_tab_a[q][1] = R.W == 2 ? take(sizeof(u64) * tn) : 0;
+        R.off_tab_a[q][1] = R.E == 2 ? take(sizeof(u64) * tn) : 0;
         R.off_tab_v[q] = take(sizeof(double) * tn);
         R.off_tab_n[q] = take(sizeof(int) * R.B);
         R.off_slab[q] = take(R.slab_bytes);
         R.off_slab_n[q] = take(sizeof(int) * R.B);
     }
-    R.off_coarse = take(R.rec * (size_t)R.cap_c << (R.log2G + R.log2SUB));
+    R.off_coarse = take(rec * (size_t)R.cap_c << (R.log2G + R.log2SUB));
     R.off_coarse_n = take(sizeof(int) << (R.log2G + R.log2SUB));
     const i64 dc = std::max<i64>(R.dump_cap, 1);
-    R.off_dsp_parent = take(sizeof(u64) * R.W * dc);
+    R.off_dsp_parent = take(sizeof(u64) * R.E * dc);
     R.off_dsp_attempt = take(sizeof(i64) * dc);
-    R.off_dsp_dest = take(sizeof(u64) * R.W * dc);
+    R.off_dsp_dest = take(sizeof(u64) * R.E * dc);
     R.off_dsp_val = take(sizeof(double) * dc);
-    R.off_dmg_addr = take(sizeof(u64) * R.W * dc);
+    R.off_dmg_addr = take(sizeof(u64) * R.E * dc);
     R.off_dmg_val = take(sizeof(double) * dc);
     R.total = o;
     lout = L;
@@ -808,10 +823,12 @@ static int hip_fail(fq_handle *q, hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_fail(q, e_, #call); \
     } while (0)
 
+static int create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layout, void *workspace, size_t bytes,
+                  bool wide, fq_handle **out);
 static int read_ctrl(fq_handle *q, Ctrl &c, hipStream_t s);
 static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals, i64 n);
 static int next_parity(const fq_handle *q);
-static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, bool check, InsertNote &note,
+static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, int ew, bool check, InsertNote &note,
                           hipStream_t s);
 static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_t *ref_addr, double ref_val,
                       hipStream_t s);
@@ -887,11 +904,17 @@ int fq_workspace_size(const fq_hamiltonian *h, const fq_params *p, const fq_layo
 int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layout, void *workspace, size_t bytes,
               fq_handle **out)
 {
+    return create(h, p, layout, workspace, bytes, false, out);
+}
+
+static int create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layout, void *workspace, size_t bytes,
+                  bool wide, fq_handle **out)
+{
     if (!out) return FQ_EINVAL;
     *out = nullptr;
     fq_handle *q = new (std::nothrow) fq_handle();
     if (!q) return FQ_ENOMEM;
-    int rc = resolve(h, p, layout, q->R, q->L, q->err);
+    int rc = resolve(h, p, layout, q->R, q->L, q->err, wide);
     if (rc) { g_err = q->err; delete q; return rc; }
     if (!workspace || bytes < q->R.total || ((uintptr_t)workspace & 255)) {
         delete q;
@@ -1100,14 +1123,14 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
     }
     hipStream_t s = (hipStream_t)stream;
     const Resolved &R = q->R;
-    const int W = R.W;
-    if (!valid_address(ref_addr, W, q->h.M, q->h.N)) {
+    const int E = R.E;
+    if (!valid_address(ref_addr, E, q->h.M, q->h.N)) {
         // an invalid entry is reported before an invalid reference
         int rc = check_entries(q, addrs, vals, n);
         if (rc == FQ_OK) q->err = "invalid reference address";
         return FQ_EINVAL;
     }
-    if ((size_t)n * (8 * W + 8) > R.slab_bytes || n > (i64)R.B * R.cap_t) {
+    if ((size_t)n * (8 * E + 8) > R.slab_bytes || n > (i64)R.B * R.cap_t) {
         int rc = check_entries(q, addrs, vals, n);
         if (rc) return rc;
         q->err = "state larger than the workspace capacity";
@@ -1117,11 +1140,11 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
     // the state from them
     char *stage = q->inst.slab[next_parity(q)];
     u64 *sa = (u64 *)stage;
-    double *sv = (double *)(stage + sizeof(u64) * W * n);
-    HIPCHK(q, hipMemcpyAsync(sa, addrs, sizeof(u64) * W * n, hipMemcpyHostToDevice, s));
+    double *sv = (double *)(stage + sizeof(u64) * E * n);
+    HIPCHK(q, hipMemcpyAsync(sa, addrs, sizeof(u64) * E * n, hipMemcpyHostToDevice, s));
     HIPCHK(q, hipMemcpyAsync(sv, vals, sizeof(double) * n, hipMemcpyHostToDevice, s));
     InsertNote note;
-    int rc = insert_entries(q, sa, sv, n, true, note, s);
+    int rc = insert_entries(q, sa, sv, n, E, true, note, s);
     if (rc) return rc;
     if (note.refused || note.overflow) {
         // the host names the entry, or finds the entries sound (a bucket is full)
@@ -1137,14 +1160,14 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
 // ms that a checkpoint of 5e5 entries and its continuation took.
 static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals, i64 n)
 {
-    const int W = q->R.W;
+    const int E = q->R.E;
     std::vector<std::pair<uint64_t, uint64_t>> keys((size_t)n);
     for (i64 i = 0; i < n; i++) {
-        if (!valid_address(addrs + i * W, W, q->h.M, q->h.N) || !std::isfinite(vals[i]) || vals[i] == 0.0) {
+        if (!valid_address(addrs + i * E, E, q->h.M, q->h.N) || !std::isfinite(vals[i]) || vals[i] == 0.0) {
             q->err = "invalid address or value at entry " + std::to_string(i);
             return FQ_EINVAL;
         }
-        keys[i] = {W == 2 ? addrs[i * W + 1] : 0, addrs[i * W]};
+        keys[i] = {E == 2 ? addrs[i * E + 1] : 0, addrs[i * E]};
     }
     std::sort(keys.begin(), keys.end());
     for (size_t i = 1; i < keys.size(); i++)
@@ -1156,9 +1179,9 @@ static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals
 // (its table, and its spawns for the next step) does not use.
 static int next_parity(const fq_handle *q) { return q->have_state ? 1 - q->parity : 0; }
 
-// Inserts n staged entries (device arrays) into the table of next_parity; the
-// current state stays as it is.  check: look for addresses that occur twice.
-static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, bool check, InsertNote &note,
+// Inserts n staged entries (device arrays, ew words per address) into the
+// table of next_parity; the current state stays as it is.  check: look for addresses that occur twice.
+static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, int ew, bool check, InsertNote &note,
                           hipStream_t s)
 {
     const Resolved &R = q->R;
@@ -1168,8 +1191,8 @@ static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, 
     HIPCHK(q, hipMemsetAsync(d_note, 0, sizeof(InsertNote), s));
     const int grid = (int)std::min<i64>((n + 255) / 256, 4096);
     const Inst *I = q->d_inst;
-    if (W == 1) hipLaunchKernelGGL(k_insert<1>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, W, d_note);
-    else hipLaunchKernelGGL(k_insert<2>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, W, d_note);
+    if (W == 1) hipLaunchKernelGGL(k_insert<1>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, ew, d_note);
+    else hipLaunchKernelGGL(k_insert<2>, dim3(grid), dim3(256), 0, s, I, par, sa, sv, n, ew, d_note);
     HIPCHK(q, hipGetLastError());
     if (check) {
         // slots for at most cap_t entries of a bucket: the next power of two,
@@ -1271,7 +1294,7 @@ static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_
     q->items = q->work = (i64)std::min(1e15, 2.0 * (double)n + cc.norm);
     q->items_known = false;
     q->ref[0] = ref_addr[0];
-    q->ref[1] = W == 2 ? ref_addr[1] : 0;
+    q->ref[1] = R.E == 2 ? ref_addr[1] : 0;
     q->yref = ref_val;
     return FQ_OK;
 }
@@ -1522,7 +1545,7 @@ int fq_get_state(fq_handle *q, uint64_t *addrs, double *vals, int64_t cap, int64
     if (!q->have_state) { q->err = "no state"; return FQ_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
     const Resolved &R = q->R;
-    const int W = R.W;
+    const int E = R.E;
     Ctrl c;
     int rc = read_ctrl(q, c, s);
     if (rc) return rc;
@@ -1531,15 +1554,15 @@ int fq_get_state(fq_handle *q, uint64_t *addrs, double *vals, int64_t cap, int64
     unsigned long long *cnt = (unsigned long long *)buf;
     u64 *oa = (u64 *)(buf + 256);
     const i64 total_cap = (i64)R.B * R.cap_t;
-    double *ov = (double *)(oa + (size_t)W * total_cap);
-    if (256 + (8 * W + 8) * (size_t)total_cap > R.slab_bytes) {
+    double *ov = (double *)(oa + (size_t)E * total_cap);
+    if (256 + (8 * E + 8) * (size_t)total_cap > R.slab_bytes) {
         q->err = "slab too small to stage the table";
         return FQ_ECAPACITY;
     }
     HIPCHK(q, hipMemsetAsync(cnt, 0, 8, s));
     int grid = std::min(R.B, 4096);
-    if (W == 1) hipLaunchKernelGGL(k_pack<1>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, oa, ov, cnt);
-    else hipLaunchKernelGGL(k_pack<2>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, oa, ov, cnt);
+    if (R.W == 1) hipLaunchKernelGGL(k_pack<1>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, oa, ov, E, cnt);
+    else hipLaunchKernelGGL(k_pack<2>, dim3(grid), dim3(256), 0, s, (const Inst *)q->d_inst, oa, ov, E, cnt);
     HIPCHK(q, hipGetLastError());
     unsigned long long tot = 0;
     HIPCHK(q, hipMemcpyAsync(&tot, cnt, 8, hipMemcpyDeviceToHost, s));
@@ -1549,7 +1572,7 @@ int fq_get_state(fq_handle *q, uint64_t *addrs, double *vals, int64_t cap, int64
     if (step) *step = c.step;
     if ((i64)tot > cap) { q->err = "get_state: capacity too small"; return FQ_ECAPACITY; }
     if (tot) {
-        if (addrs) HIPCHK(q, hipMemcpy(addrs, oa, sizeof(u64) * W * tot, hipMemcpyDeviceToHost));
+        if (addrs) HIPCHK(q, hipMemcpy(addrs, oa, sizeof(u64) * E * tot, hipMemcpyDeviceToHost));
         if (vals) HIPCHK(q, hipMemcpy(vals, ov, sizeof(double) * tot, hipMemcpyDeviceToHost));
     }
     return FQ_OK;
@@ -1609,24 +1632,24 @@ int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream)
         return FQ_EINVAL;
     }
     hipStream_t s = (hipStream_t)stream;
-    const int W = dst->R.W;
+    const int E = dst->R.E;
     Ctrl c;
     int rc = read_ctrl(src, c, s);
     if (rc) return rc;
     if (c.error) { dst->err = "copy_state: source is in an error state"; return FQ_EINVAL; }
     const i64 nmax = (i64)src->R.B * src->R.cap_t;
-    if (256 + (8 * W + 8) * (size_t)nmax > dst->R.slab_bytes) {
+    if (256 + (8 * E + 8) * (size_t)nmax > dst->R.slab_bytes) {
         dst->err = "copy_state: destination slab too small to stage the source table";
         return FQ_ECAPACITY;
     }
     char *buf = dst->inst.slab[next_parity(dst)];
     unsigned long long *cnt = (unsigned long long *)buf;
     u64 *oa = (u64 *)(buf + 256);
-    double *ov = (double *)(oa + (size_t)W * nmax);
+    double *ov = (double *)(oa + (size_t)E * nmax);
     HIPCHK(dst, hipMemsetAsync(cnt, 0, 8, s));
     const int grid = std::min(src->R.B, 4096);
-    if (W == 1) hipLaunchKernelGGL(k_pack<1>, dim3(grid), dim3(256), 0, s, (const Inst *)src->d_inst, oa, ov, cnt);
-    else hipLaunchKernelGGL(k_pack<2>, dim3(grid), dim3(256), 0, s, (const Inst *)src->d_inst, oa, ov, cnt);
+    if (src->R.W == 1) hipLaunchKernelGGL(k_pack<1>, dim3(grid), dim3(256), 0, s, (const Inst *)src->d_inst, oa, ov, E, cnt);
+    else hipLaunchKernelGGL(k_pack<2>, dim3(grid), dim3(256), 0, s, (const Inst *)src->d_inst, oa, ov, E, cnt);
     HIPCHK(dst, hipGetLastError());
     unsigned long long tot = 0;
     HIPCHK(dst, hipMemcpyAsync(&tot, cnt, 8, hipMemcpyDeviceToHost, s));
@@ -1636,7 +1659,7 @@ int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream)
         return FQ_ECAPACITY;
     }
     InsertNote note;
-    rc = insert_entries(dst, oa, ov, (i64)tot, false, note, s);
+    rc = insert_entries(dst, oa, ov, (i64)tot, E, false, note, s);
     if (rc) return rc;
     return load_state(dst, (i64)tot, c.shift, c.step, src->ref, src->yref, s);
 }
@@ -1951,6 +1974,15 @@ struct fq_batch {
 
 namespace {
 
+// whether the kernels of a batch take the caller's two words
+bool batch_wide(int n, const fq_hamiltonian *h, const fq_params *p)
+{
+    auto var = [&](int i) { return variant(h[i].model, h[i].M, h[i].N, 1, h[i].g, p[i].flags); };
+    for (int i = 0; i < n; i++)
+        if (!narrow(&h[i], &p[i]) || var(i) != var(0)) return true;
+    return false;
+}
+
 int batch_plan(int n, const fq_hamiltonian *h, const fq_params *p, const fq_layout *lay, std::vector<size_t> &off,
                size_t &total, std::string &err)
 {
@@ -1958,13 +1990,14 @@ int batch_plan(int n, const fq_hamiltonian *h, const fq_params *p, const fq_layo
     i64 nb = 0, np = 0;
     std::vector<size_t> sz(n);
     Resolved R0;
+    const bool wide = batch_wide(n, h, p);
     for (int i = 0; i < n; i++) {
         Resolved R;
         fq_layout L;
-        int rc = resolve(&h[i], &p[i], &lay[i], R, L, err);
+        int rc = resolve(&h[i], &p[i], &lay[i], R, L, err, wide);
         if (rc) { err = "batch instance " + std::to_string(i) + ": " + err; return rc; }
         if (i == 0) R0 = R;
-        if (R.W != R0.W || variant(h[i].model, h[i].M, h[i].N, p[i].addr_words, h[i].g, p[i].flags) !=
+        if (R.E != R0.E || variant(h[i].model, h[i].M, h[i].N, p[i].addr_words, h[i].g, p[i].flags) !=
                                    variant(h[0].model, h[0].M, h[0].N, p[0].addr_words, h[0].g, p[0].flags) ||
             R.block != R0.block ||
             R.spawn_block != R0.spawn_block || R.slots != R0.slots) {
@@ -2014,10 +2047,11 @@ int fq_batch_create(int32_t n, const fq_hamiltonian *h, const fq_params *p, cons
     if (!b) return FQ_ENOMEM;
     if (hipGetDevice(&b->device) != hipSuccess) b->device = -1;
     char *ws = (char *)workspace;
+    const bool wide = batch_wide(n, h, p);
     for (int i = 0; i < n; i++) {
         fq_handle *q = nullptr;
         size_t sz = (i + 1 < n ? off[i + 1] : total) - off[i];
-        rc = fq_create(&h[i], &p[i], &lay[i], ws + off[i], sz, &q);
+        rc = create(&h[i], &p[i], &lay[i], ws + off[i], sz, wide, &q);
         if (rc) {
             g_err = "batch instance " + std::to_string(i) + ": " + g_err;
             for (auto x : b->inst) fq_destroy(x);
@@ -2271,7 +2305,7 @@ static int spectral_check(fq_batch *b, std::string &err)
     int rc = replica_check(b, err);
     if (rc) return rc;
     const fq_handle *q0 = b->inst[0];
-    if (gs_upd_lds(q0->R.W, q0->R.slots) > LDS_MAX) {
+    if (gs_upd_lds(q0->R.E, q0->R.slots) > LDS_MAX) {
         err = "excited states: lds_slots too large for the orthogonalisation hash (twice lds_slots)";
         return FQ_EINVAL;
     }
@@ -2592,7 +2626,7 @@ int fq_server_tick(fq_server *sv, void *stream, int32_t *n_active, int32_t *n_qu
         Req &r = sv->reqs[rid];
         if (!sv->alloc(r.bytes, r.off)) break;
         sv->queue.pop_front();
-        int rc = fq_create(&r.h, &r.p, &r.L, sv->arena + r.off, r.bytes, &r.q);
+        int rc = create(&r.h, &r.p, &r.L, sv->arena + r.off, r.bytes, true, &r.q);
         if (rc == FQ_OK) rc = fq_set_state(r.q, r.start, &r.start_val, 1, 0.0, 0, r.start, r.start_val, stream);
         if (rc == FQ_OK) {
             hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(1), 0, s, &r.q->d_ctrl->stop_step, (i64)r.n_steps);
