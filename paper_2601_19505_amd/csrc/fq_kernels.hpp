@@ -75,22 +75,22 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident(const fq::Inst *const *
     const fq::Inst &I = fq::const_inst(insts[i]);
     const int own = res_log2_groups(lg, I.log2B);
     if (g >> own) return;
-    fq::resident_steps<W, MODEL, EARLY, false>(I, g, own, stops.step[i], max_items << own, patience, fq::Overlap{}, 0,
-                                               smem);
+    fq::resident_steps<W, MODEL, EARLY, 0>(I, g, own, stops.step[i], max_items << own, patience, fq::Overlap{}, 0, nullptr,
+                                           smem);
 }
 
-// The same for replicas and their overlaps (late compression): replica r is
-// stepped by the workgroups from r 2^lg on of those that blockIdx counts in
+// The same for replicas and their overlaps (KIND 1), or two runs for excited
+// states (KIND 2), with late compression: instance r of O.rep is stepped by the workgroups from r 2^lg on of those that blockIdx counts in
 // steps of `spread`: 8 puts all of them on one XCD.
-template <int W, int MODEL>
-__global__ __launch_bounds__(fq::RES_BS) void k_resident_replicas(fq::Overlap O, int spread, int lg, fq::i64 max_items,
-                                                                  fq::u64 patience, fq::i64 stop)
+template <int W, int MODEL, int KIND>
+__global__ __launch_bounds__(fq::RES_BS) void k_resident_joint(fq::Overlap O, fq::Fx3 *norms, int spread, int lg,
+                                                               fq::i64 max_items, fq::u64 patience, fq::i64 stop)
 {
     extern __shared__ __align__(16) char smem[];
     if ((int)blockIdx.x % spread) return;
     const int y = (int)blockIdx.x / spread, me = y >> lg;
-    fq::resident_steps<W, MODEL, false, true>(fq::const_inst(O.rep[me]), y & ((1 << lg) - 1), lg, stop, max_items << lg,
-                                              patience, O, me, smem);
+    fq::resident_steps<W, MODEL, false, KIND>(fq::const_inst(O.rep[me]), y & ((1 << lg) - 1), lg, stop, max_items << lg,
+                                              patience, O, me, norms, smem);
 }
 
 // explicit instantiations (EXT = extern: declaration only) of the merge and
@@ -111,7 +111,8 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident_replicas(fq::Overlap O,
     EXT template __global__ void k_spawn<W_, M_, 1024, true>(const fq::Inst *const *, const fq::u32 *, int); \
     EXT template __global__ void k_resident<W_, M_, false>(const fq::Inst *const *, int, int, int, fq::i64, fq::u64, ResStops); \
     EXT template __global__ void k_resident<W_, M_, true>(const fq::Inst *const *, int, int, int, fq::i64, fq::u64, ResStops); \
-    EXT template __global__ void k_resident_replicas<W_, M_>(fq::Overlap, int, int, fq::i64, fq::u64, fq::i64);
+    EXT template __global__ void k_resident_joint<W_, M_, 1>(fq::Overlap, fq::Fx3 *, int, int, fq::i64, fq::u64, fq::i64); \
+    EXT template __global__ void k_resident_joint<W_, M_, 2>(fq::Overlap, fq::Fx3 *, int, int, fq::i64, fq::u64, fq::i64);
 
 #define FQ_EXTERN_STEP_KERNELS                                                                \
     FQ_STEP_KERNEL_SET(extern, 1, 0) FQ_STEP_KERNEL_SET(extern, 1, 1) FQ_STEP_KERNEL_SET(extern, 1, 2)        \

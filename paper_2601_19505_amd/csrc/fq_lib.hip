@@ -97,7 +97,7 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64
         insts[i]->fin->done = 0;
         if (resident) {
             ResSync *y = insts[i]->res;
-            y->arrived = y->gate = y->xccs = y->count = 0;
+            y->arrived = y->gate = y->xccs = y->abort = y->count = 0;
             for (int x = 0; x < RES_XCCS; x++) y->on[x] = y->here[x][0] = 0;
         }
     }
@@ -376,17 +376,21 @@ template <int W> const void *resident_kernel_w(int m, bool e)
 
 int res_lds_bytes(int W) { return W == 1 ? ResLds<1>::BYTES : ResLds<2>::BYTES; }
 
-template <int W> const void *replica_kernel_w(int m)
+template <int W, int KIND> const void *joint_kernel_w(int m)
 {
     switch (m) {
-    case 0: return (const void *)k_resident_replicas<W, 0>;
-    case 1: return (const void *)k_resident_replicas<W, 1>;
-    case 2: return (const void *)k_resident_replicas<W, 2>;
-    default: return (const void *)k_resident_replicas<W, 3>;
+    case 0: return (const void *)k_resident_joint<W, 0, KIND>;
+    case 1: return (const void *)k_resident_joint<W, 1, KIND>;
+    case 2: return (const void *)k_resident_joint<W, 2, KIND>;
+    default: return (const void *)k_resident_joint<W, 3, KIND>;
     }
 }
-// (late compression: var < 4)
-const void *replica_kernel(int W, int var) { return W == 1 ? replica_kernel_w<1>(var) : replica_kernel_w<2>(var); }
+// resident replicas, or two runs for excited states (late compression: var < 4)
+const void *joint_kernel(int W, int var, bool excited)
+{
+    if (excited) return W == 1 ? joint_kernel_w<1, 2>(var) : joint_kernel_w<2, 2>(var);
+    return W == 1 ? joint_kernel_w<1, 1>(var) : joint_kernel_w<2, 1>(var);
+}
 
 const void *resident_kernel(int W, int var)
 {
@@ -1398,16 +1402,18 @@ bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
     return fits;
 }
 
-// The same for n replicas with their overlaps, in one launch (late
-// compression; at most half as many workgroups as buckets, whose sums share
-// O.part).  The hash of a workgroup has to hold its part of the vector until
-// the overlaps are summed, so the items of a step stay below its slots;
-// larger replicas keep the step and overlap kernels.
-i64 replica_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
-bool plan_replicas(fq_handle *const *h, int n, int var, ResPlan &P)
+// The same for n replicas with their overlaps, or two runs for excited
+// states, in one launch (late compression; at most half as many workgroups as
+// buckets, whose sums share the scratch).  The hash of a workgroup has to hold
+// its part of the vector until the overlaps are summed (excited states: the
+// parts of both runs), so the items of a step stay below its slots; larger
+// ones keep the step kernels.
+i64 joint_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
+bool plan_joint(fq_handle *const *h, int n, int var, bool excited, ResPlan &P)
 {
-    if (n > RES_MAXR || var >= 4 || !plan_resident(h, n, P)) return false;
+    if (n > (excited ? 2 : RES_MAXR) || var >= 4 || !plan_resident(h, n, P)) return false;
     const int log2B = h[0]->R.log2B;
+    const i64 hashes = excited ? 1 : n;  // one of them holds the items of all
     i64 items = 0, work = 0;
     for (int i = 0; i < n; i++) {
         items += h[i]->items;
@@ -1415,12 +1421,11 @@ bool plan_replicas(fq_handle *const *h, int n, int var, ResPlan &P)
     }
     bool fits = false;
     for (int lg = res_log2_groups(0, log2B); lg < log2B && n << lg <= RES_MAXG; lg++) {
-        const i64 all = (i64)n << lg;
         P.lg = P.lg_grid = lg;
         P.per = n;
-        fits = items <= all * replica_most(h[0]->R.W) && items <= n * res_limit(h[0], RES_MOST, lg);
-        const bool aim = work <= all * RES_AIM;
-        P.most = aim ? std::min(RES_MORE, replica_most(h[0]->R.W)) : replica_most(h[0]->R.W);
+        fits = items <= (hashes * joint_most(h[0]->R.W) << lg) && items <= hashes * res_limit(h[0], RES_MOST, lg);
+        const bool aim = work <= (n * RES_AIM << lg);
+        P.most = aim ? std::min(RES_MORE, joint_most(h[0]->R.W)) : joint_most(h[0]->R.W);
         if (aim) break;
     }
     return fits;
@@ -1444,14 +1449,16 @@ hipError_t launch_resident(const Exec &X, const ResPlan &P, const i64 *stops, hi
     return hipSuccess;
 }
 
-hipError_t launch_replicas(const Overlap &O, int W, int var, const ResPlan &P, i64 stop, hipStream_t s)
+// O: the replicas; excited states: their rep, dots and flags, and norms
+hipError_t launch_joint(const Overlap &O, Fx3 *norms, int W, int var, const ResPlan &P, i64 stop, hipStream_t s)
 {
     Overlap o = O;
     int lg = P.lg, spread = o.R << lg <= 32 ? 8 : 1;  // one XCD holds 32 workgroups
     i64 most = P.most;
     u64 patience = RES_PATIENCE;
-    void *args[] = {(void *)&o, (void *)&spread, (void *)&lg, (void *)&most, (void *)&patience, (void *)&stop};
-    return hipLaunchKernel(replica_kernel(W, var), dim3((o.R << lg) * spread), dim3(RES_BS), args, res_lds_bytes(W), s);
+    void *args[] = {(void *)&o, (void *)&norms, (void *)&spread, (void *)&lg, (void *)&most, (void *)&patience, (void *)&stop};
+    return hipLaunchKernel(joint_kernel(W, var, norms != nullptr), dim3((o.R << lg) * spread), dim3(RES_BS), args,
+                           res_lds_bytes(W), s);
 }
 
 // size of the steps to come: the last row of a launch, or more than its
@@ -1900,7 +1907,7 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
     const Exec &X = G.X;
     i64 launched = 0;
     int rc = FQ_OK;
-    bool again = true;  // resident steps of replicas are worth another launch
+    bool again = true;  // resident steps of replicas or excited states are worth another launch
     while (launched < steps && rc == FQ_OK) {
         i64 chunk = std::min<i64>(RING, steps - launched);
         ResPlan plan;
@@ -1908,16 +1915,28 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
         if (!ov && !gs && plan_resident(G.h.data(), X.n, plan)) {
             hr = group_resident(G, plan, chunk, stop, rows, s, failed, err, rc);
         } else {
-            i64 before[FQ_MAX_REPLICAS], stops[FQ_MAX_REPLICAS];  // (with overlaps only: no allocation there)
-            for (int j = 0; ov && j < X.n; j++) before[j] = G.h[j]->step;
-            const bool resident = ov && again && plan_replicas(G.h.data(), X.n, X.var, plan);
+            i64 before[FQ_MAX_REPLICAS], stops[FQ_MAX_REPLICAS];  // (with overlaps: no allocation there)
+            const bool joint = ov || gs;
+            for (int j = 0; joint && j < X.n; j++) before[j] = G.h[j]->step;
+            const bool resident = joint && again && plan_joint(G.h.data(), X.n, X.var, gs != nullptr, plan);
             hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, X.insts, X.n, resident ? 1 : 0, stop);
             hipError_t e = hipGetLastError();
             if (resident) {
                 for (int j = 0; j < X.n; j++) stops[j] = before[j] + chunk;
-                if (e == hipSuccess) e = launch_replicas(ov->O, X.W, X.var, plan, before[0] + chunk, s);
+                Overlap O = {};
+                if (ov) {
+                    O = ov->O;
+                } else {
+                    O.rep = gs->S.rep;
+                    O.R = gs->S.R;
+                    O.B = gs->S.B;
+                    O.part = gs->S.dots;
+                    O.flags = gs->S.flags;
+                }
+                if (e == hipSuccess)
+                    e = launch_joint(O, gs ? gs->S.norms : nullptr, X.W, X.var, plan, before[0] + chunk, s);
                 // the overlaps of the last step made
-                if (e == hipSuccess) e = launch_overlap(*ov, s);
+                if (e == hipSuccess && ov) e = launch_overlap(*ov, s);
             }
             for (i64 k = 0; k < chunk && !resident && e == hipSuccess; k++) {
                 e = exec_step(X, s, nullptr, gs);
@@ -1925,10 +1944,10 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
             }
             if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
             hr = group_collect(G, rows, s, chunk, resident ? &plan : nullptr, resident ? stops : nullptr, failed, err, rc);
-            if (ov && !hr) {
+            if (joint && !hr) {
                 i64 done = chunk;
                 for (int j = 0; j < X.n; j++) done = std::min<i64>(done, G.ctrl[j].step - before[j]);
-                if (done > 0) {
+                if (ov && done > 0) {
                     e = hipMemcpy(ov->out, ov->O.ring, sizeof(double) * ov->O.P * done, hipMemcpyDeviceToHost);
                     if (e != hipSuccess) { err = std::string("overlap rows: ") + hipGetErrorString(e); return FQ_EHIP; }
                     ov->out += ov->O.P * done;
@@ -2186,7 +2205,7 @@ static int run_replicas(fq_batch *b, int64_t n_steps, fq_step_stats *stats, doub
     ov.O.ring_cap = RING;
     ov.O.flags = (int *)(sc + lay.flags);
     hipError_t e = ensure_lds(ov.W == 1 ? (const void *)k_overlap<1> : (const void *)k_overlap<2>, ov.lds);
-    if (e == hipSuccess && b->G.X.var < 4) e = ensure_lds(replica_kernel(ov.W, b->G.X.var), res_lds_bytes(ov.W));
+    if (e == hipSuccess && b->G.X.var < 4) e = ensure_lds(joint_kernel(ov.W, b->G.X.var, false), res_lds_bytes(ov.W));
     if (e == hipSuccess) e = hipMemcpyAsync((void *)ov.O.rep, rep, sizeof(Inst *) * R, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         // the flags start at zero (a fill kernel: the scratch may hold the
@@ -2357,6 +2376,7 @@ int fq_batch_run_spectral(fq_batch *b, int64_t n_steps, fq_step_stats *stats, vo
     hipError_t e = ensure_lds(g.W == 1 ? (const void *)k_gs_dot<1> : (const void *)k_gs_dot<2>, g.lds_dot);
     if (e == hipSuccess)
         e = ensure_lds(g.W == 1 ? (const void *)k_gs_update<1> : (const void *)k_gs_update<2>, g.lds_upd);
+    if (e == hipSuccess && b->G.X.var < 4) e = ensure_lds(joint_kernel(g.W, b->G.X.var, true), res_lds_bytes(g.W));
     if (e == hipSuccess) e = hipMemcpyAsync((void *)g.S.rep, rep.data(), sizeof(Inst *) * R, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, g.S.updated, R, 0);

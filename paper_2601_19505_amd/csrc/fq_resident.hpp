@@ -76,15 +76,17 @@ struct ResPart {
                   // not hold the whole vector; from bit 8 the most distinct addresses in a bucket; from bit 32 exact parents of the spawn pass
     u64 hproj[2], vproj[2];
 };
+static_assert(sizeof(ResPart) == 64, "two to a cache line");
 
 // Exchange area of one instance, counters zero before the launch.  The parts are
 // double buffered by step parity: a workgroup can be at most one barrier
 // ahead of the slowest reader.
 struct ResSync {
-    u32 arrived, gate, xccs, pad0[13], on[RES_XCCS];  // xccs: mask of the XCDs its workgroups run on, on: how many each
+    u32 arrived, gate, xccs, abort, pad0[12], on[RES_XCCS];  // xccs: mask of the XCDs its workgroups run on, on: how many each
     u32 count, pad1[31];
     u32 here[RES_XCCS][32];  // barrier arrivals by XCD, a line each
     ResPart part[2][RES_MAXG];
+    u64 parents[2][RES_MAXG];  // excited states: survivors after the projection
 };
 
 // LDS: the hash; slot indices of its occupied slots (before them the marks
@@ -204,6 +206,35 @@ __device__ __forceinline__ void wave_scan_fx3(Fx3 &x)  // sum in lane 63
     fx3_add(x, Fx3{dpp0<0x143, 0xc>(x.w0), dpp0<0x143, 0xc>(x.w1), dpp0<0x143, 0xc>(x.w2)});
 }
 
+// Entries [0, words[K]) of the buckets [bA, bA + K) of a table: f(a0, a1, v).
+template <int W, class F>
+__device__ __forceinline__ void resident_stream(const Inst &IJ, const int pj, const int bA, const int K,
+                                                const int *words, F f)
+{
+#pragma unroll 1
+    for (int i = threadIdx.x; i < words[K]; i += RES_BS) {
+        int k = 0;
+        for (int hi = K; hi - k > 1;) {
+            const int mid = (k + hi) >> 1;
+            if (words[mid] <= i) k = mid;
+            else hi = mid;
+        }
+        const i64 e = (i64)(bA + k) * IJ.cap_t + (i - words[k]);
+        f(res_load(&IJ.tab_a[pj][0][e]), W == 2 ? res_load(&IJ.tab_a[pj][1][e]) : (u64)0,
+          bitsd(res_load((const u64 *)IJ.tab_v[pj] + e)));
+    }
+}
+// words[0 .. K]: where the entries of the buckets start
+__device__ __forceinline__ void resident_stream_words(const Inst &IJ, const int pj, const int bA, const int K, int *words)
+{
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x >= 64) return;
+    int n = lane < K ? res_load(&IJ.tab_n[pj][bA + lane]) : 0;
+    n = (int)wave_scan((u64)min((i64)n, IJ.cap_t));
+    if (lane < K) words[lane + 1] = n;
+    if (lane == 0) words[0] = 0;
+}
+
 // Overlaps of replica A with every later replica on the buckets [bA, bA + K):
 // its amplitudes are in the hash (low word; 0 where compressed away).
 // words: LDS, K + 1 ints and from word 2 RES_MAXK 16 Fx3; to[pair].
@@ -219,29 +250,14 @@ __device__ __forceinline__ void resident_overlap(const Overlap &O, const Lds &L,
     for (int B = A + 1; B < O.R; B++) {
         const Inst &IB = const_inst(O.rep[B]);
         const int pB = parity[B];
-        if (wid == 0) {
-            int n = lane < K ? res_load(&IB.tab_n[pB][bA + lane]) : 0;
-            n = (int)wave_scan((u64)min((i64)n, IB.cap_t));
-            if (lane < K) words[lane + 1] = n;
-            if (lane == 0) words[0] = 0;
-        }
+        resident_stream_words(IB, pB, bA, K, words);
         __syncthreads();
         Fx3 acc = fx3_zero();
-#pragma unroll 1
-        for (int i = tid; i < words[K]; i += BS) {
-            int k = 0;
-            for (int hi = K; hi - k > 1;) {
-                const int mid = (k + hi) >> 1;
-                if (words[mid] <= i) k = mid;
-                else hi = mid;
-            }
-            const i64 e = (i64)(bA + k) * IB.cap_t + (i - words[k]);
-            const u64 a0 = res_load(&IB.tab_a[pB][0][e]), a1 = W == 2 ? res_load(&IB.tab_a[pB][1][e]) : 0;
-            const double v = bitsd(res_load((const u64 *)IB.tab_v[pB] + e));
+        resident_stream<W>(IB, pB, bA, K, words, [&](u64 a0, u64 a1, double v) {
             const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
             const double c = s >= 0 ? bitsd(L.lo[s]) : 0.0;
             if (c != 0.0) fx3_add(acc, to_fx3(c * v, inexact, ovf));
-        }
+        });
         if (__any((acc.w0 | acc.w1 | acc.w2) != 0)) wave_scan_fx3(acc);
         if (lane == 63) tmp[wid] = acc;
         __syncthreads();
@@ -254,6 +270,86 @@ __device__ __forceinline__ void resident_overlap(const Overlap &O, const Lds &L,
     if (inexact) atomicOr(&O.flags[1], 1);
     if (ovf) atomicOr(&O.flags[2], 1);
     __syncthreads();
+}
+
+// Excited states (Sec. 2.2): two runs, the second orthogonalised against the
+// first between merge and spawn, step together in the same way, with three
+// barriers a step.  At the first the new table of run 0 is complete; a step in
+// which a hash did not hold its vector or a merge failed ends there, undone
+// (only the tables that the next step overwrites have been written), and the
+// step kernels make it.  Then the workgroups of run 1 stream their buckets of
+// run 0 against their hash for c_0 . c_1 and c_0 . c_0, meet, and stream them
+// once more to subtract.  A step of two runs of the 12/12 ring at 1e5 walkers
+// takes 47 us so, 102 with the step and projection kernels.
+//
+// This workgroup's c_0 . c_1 and c_0 . c_0 (to[0], to[1]); words: as above,
+// the sums of the waves behind them.
+template <int W>
+__device__ __forceinline__ void resident_dot(const Inst &I, const Lds &L, const Inst &IJ, const int pj, const int bA,
+                                             const int K, int *words, int *flags, Fx3 *to)
+{
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Fx3 *tmp = (Fx3 *)(words + 2 * RES_MAXK);
+    resident_stream_words(IJ, pj, bA, K, words);
+    __syncthreads();
+    int inexact = 0, ovf = 0;
+    Fx3 dot = fx3_zero(), sq = fx3_zero();
+    resident_stream<W>(IJ, pj, bA, K, words, [&](u64 a0, u64 a1, double v) {
+        fx3_add(sq, to_fx3(v * v, inexact, ovf));
+        const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
+        const double c = s >= 0 ? bitsd(L.lo[s]) : 0.0;
+        if (c != 0.0) fx3_add(dot, to_fx3(v * c, inexact, ovf));
+    });
+    wave_scan_fx3(dot);
+    wave_scan_fx3(sq);
+    if (lane == 63) {
+        tmp[wid] = dot;
+        tmp[RES_BS / 64 + wid] = sq;
+    }
+    if (inexact) atomicOr(flags, 1);
+    if (ovf) fail(I, L, FQE_DIVERGED, bA);
+    __syncthreads();
+    if (wid < 2) {
+        Fx3 x = lane < RES_BS / 64 ? tmp[wid * (RES_BS / 64) + lane] : fx3_zero();
+        wave_scan_fx3(x);
+        if (lane == 63) to[wid] = x;
+    }
+}
+
+// c_1 <- c_1 - alpha c_0 in the hash; sums: the workgroups' resident_dot
+template <int W>
+__device__ __forceinline__ void resident_project(const Inst &I, const Lds &L, const Inst &IJ, const int pj, const int bA,
+                                                 const int K, const int G, const int *words, const Fx3 *sums,
+                                                 double *s_alpha)
+{
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) {
+        Fx3 d = fx3_zero(), q = fx3_zero();
+#pragma unroll 1
+        for (int w = lane; w < G; w += 64) {
+            const Fx3 *x = sums + 2 * w;
+            fx3_add(d, Fx3{res_load(&x[0].w0), res_load(&x[0].w1), res_load(&x[0].w2)});
+            fx3_add(q, Fx3{res_load(&x[1].w0), res_load(&x[1].w1), res_load(&x[1].w2)});
+        }
+        wave_scan_fx3(d);
+        wave_scan_fx3(q);
+        if (lane == 63) {
+            const double nq = from_fx3(q);
+            *s_alpha = nq > 0.0 ? from_fx3(d) / nq : 0.0;
+        }
+    }
+    __syncthreads();
+    const double alpha = *s_alpha;
+    int np = 0;
+    resident_stream<W>(IJ, pj, bA, K, words, [&](u64 a0, u64 a1, double v) {
+        const int s = lds_slot<W>(L, a0, a1, slot_hash(a0, a1), np);
+        if (s < 0) {
+            fail(I, L, FQE_CAP_LDS, bA);
+        } else {
+            const double p = alpha * v;
+            L.lo[s] = dbits(bitsd(L.lo[s]) - p);
+        }
+    });
 }
 
 // Exclusive scan of x over the workgroup; tmp: 16 words.  One barrier.
@@ -428,32 +524,38 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
 // max_items entries and records to merge.  An instance whose buckets may hold
 // more addresses than the hash is not begun when one of them might now; later
 // the number of items, half the hash a bucket, keeps them from it.
-// OV: the instance is replica `me` of O, whose replicas start at one step and
-// stop together: all of them decide from the same sums and flags.  O.ring
+// KIND 1: the instance is replica `me` of O, whose replicas start at one step
+// and stop together: all of them decide from the same sums and flags.  O.ring
 // receives the overlaps of all steps but the last, whose tables the launch
-// leaves.
-template <int W, int MODEL, bool EARLY, bool OV>
+// leaves.  KIND 2: run `me` of two for excited states, together likewise;
+// O.part takes the dot products (two a workgroup), norms the projected norms,
+// O.flags[0] whether one was rounded.
+template <int W, int MODEL, bool EARLY, int KIND>
 __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const int lg, const i64 last_step,
                                                const i64 max_items, const u64 patience, const Overlap &O, const int me,
-                                               char *smem)
+                                               Fx3 *norms, char *smem)
 {
     typedef typename AddrOf<W>::T T;
     typedef ResLds<W> M;
     constexpr int BS = RES_BS, SLOTS = ResSlots<W>::N;
+    constexpr bool OV = KIND == 1, GS = KIND == 2, JOINT = KIND != 0;
+    const bool second = GS && me == 1;
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = 1 << lg;
     const int K = I.B >> lg;   // buckets of this workgroup, at most RES_MAXK
     const int bA = g * K;
     Ctrl *ctrl = I.ctrl;
     // the workgroups that meet at the barrier, and where
-    const int meet = OV ? O.R << lg : G;
-    ResSync *Y = OV ? const_inst(O.rep[0]).res : I.res;
+    const int meet = JOINT ? O.R << lg : G;
+    ResSync *Y = JOINT ? const_inst(O.rep[0]).res : I.res;
 
     __shared__ int s_go, s_fail, s_full, s_len, s_load, s_inx, s_list, s_ex;
     __shared__ u32 s_where[3];
     __shared__ double s_state[2];  // shift and norm after the step
     __shared__ i64 s_sp;
-    __shared__ int s_par[OV ? RES_MAXR : 1];  // parity of each replica's state
+    __shared__ int s_par[JOINT ? RES_MAXR : 1];  // parity of each replica's state
+    __shared__ int s_live, s_abort;                // excited states: survivors after the projection; the step is undone
+    __shared__ double s_alpha, s_projected;
     Lds L;
     L.k0 = (u64 *)smem;
     L.k1 = L.k0 + SLOTS;
@@ -490,7 +592,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
     const i64 ring_base = ctrl->ring_base;
     if (tid == 0) s_go = !halted(ctrl);
     __syncthreads();
-    if (OV) {
+    if (JOINT) {
         // none is stepped when one of them cannot be: the same answer in every workgroup
         if (tid < O.R) {
             Ctrl *c = const_inst(O.rep[tid]).ctrl;
@@ -553,7 +655,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         first_inx = ctrl->first_inexact;
     }
 
-    u32 round = 0;
+    u32 round = 0, met = 0;  // steps begun and barriers passed in this launch
+    double Nrow = N0;        // norm of the row to be written
     int slots = 0;           // of the hash: from the distinct addresses of the step before
     bool few = false;        // those fill no more than 5/8 of the whole hash
     bool concluded = true;   // no step waits for its shift
@@ -595,7 +698,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             R.inexact_steps = row_st;
             R.spawns = row_sp;
             R.shift = S;
-            R.norm = N0;
+            R.norm = GS ? Nrow : N0;
             R.hproj = hp;
             R.vproj = vp;
             R.flags = flagged ? ROW_INEXACT : 0;
@@ -603,11 +706,12 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         row_inx = 0;
         if (flagged && first_inx == 0) first_inx = n;
         row_ex = (i64)red[16];
-        row_st = len - row_ex;
+        row_st = (GS ? (i64)red[19] : len) - row_ex;
         row_sp = (i64)(red[17] & (((u64)1 << 40) - 1));
         row_due = false;
     };
     s_go = 2;
+    if (GS && tid == 0) s_abort = 0;
     for (;;) {
         // ------------------------------------------------ 0. what the other workgroups left
         // wave 0: the parts of the step that waits for its shift, summed over
@@ -630,7 +734,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             }
         }
         u64 others = 0;  // OV: flags of the other replicas; their entries and records from bit 8
-        if (OV && split && wid == 0) {
+        if (JOINT && split && wid == 0) {
 #pragma unroll 1
             for (int w = lane; w < meet; w += 64) {
                 const int r = w >> lg;
@@ -661,6 +765,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 s_fail = s_full = 0;
                 s_len = s_load = s_inx = s_ex = 0;
                 s_sp = 0;
+                if (GS) s_live = 0;
             }
         }
         int inx = 0, np = 0, distinct = 0;
@@ -668,9 +773,9 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         // fit the hash; a bucket larger than that is a batch alone (its
         // distinct addresses usually fit).  The first batch is cleared for
         // while the counts arrive, and merged again if it does not fit.
-        for (int k0 = 0, k1 = 0, redo = 0, most = few ? 8 * SLOTS : SLOTS; k0 < K;) {
+        for (int k0 = 0, k1 = 0, redo = 0, most = GS ? 1 << 30 : few ? 8 * SLOTS : SLOTS; k0 < K;) {
             const bool all = k0 > 0 || redo;
-            if (all || slots == 0) slots = SLOTS;
+            if (all || slots == 0 || second) slots = SLOTS;
             if (all || wid > 1) {
 #pragma unroll 1
                 for (int s = all ? tid : tid - 128; s < slots; s += all ? BS : BS - 128) {
@@ -720,19 +825,27 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 const bool error = __any(state & 2), diverged = !(N1 < 17592186044416.0) || !(S1 == S1);
                 i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
                 bool end = n + 1 >= stop;
-                if (OV) {
+                if (JOINT) {
                     // the same answer in every replica: after each step all go on or none
                     items += (i64)lane_value(wave_scan(others >> 8), 63);
-                    end = end || items > item_limit * O.R || __any(((others | state) & 6) != 0);
+                    end = end || items > (GS ? item_limit : item_limit * O.R) || __any(((others | state) & 6) != 0);
                 } else {
                     end = end || items > item_limit;
                 }
                 if (lane == 0) {
                     // (a replica that has diverged takes part in one more step, for the others to read its flag)
-                    s_go = error ? 0 : diverged ? (OV && !end ? 3 : 0) : end ? 1 : 2;
+                    s_go = error ? 0 : diverged ? (JOINT && !end ? 3 : 0) : end ? 1 : 2;
                     s_state[0] = S1;
                     s_state[1] = N1;
                     if (g == 0 && !error && diverged) set_error(ctrl, FQE_DIVERGED, -1);
+                }
+                if (second) {
+                    Fx3 x = fx3_zero();
+#pragma unroll 1
+                    for (int w = lane; w < G; w += 64)
+                        fx3_add(x, Fx3{res_load(&norms[w].w0), res_load(&norms[w].w1), res_load(&norms[w].w2)});
+                    wave_scan_fx3(x);
+                    if (lane == 63) s_projected = from_fx3(x);
                 }
             }
 #pragma unroll 1
@@ -742,18 +855,21 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                     if (waits) {
                         __syncthreads();
                         concluded = true;
-                        dead = OV && s_go == 3;
+                        dead = JOINT && s_go == 3;
                         if (s_go == 1 || s_go == 2) {
                             n++;
                             p = p1;
                             S = lane_value(s_state[0], 0);
                             N0 = lane_value(s_state[1], 0);
+                            if (GS) Nrow = N0;
+                            if (second) N0 = lane_value(s_projected, 0);
                         }
                         if ((s_go == 1 || s_go == 2) && g == 0 && wid == 0) {
                             // the sums of its row, written further down
-                            u64 hl = 0, hh = 0, vl = 0, vh = 0;
+                            u64 hl = 0, hh = 0, vl = 0, vh = 0, parents = 0;
 #pragma unroll 1
                             for (int k = lane; k < G; k += 64) {
+                                if (GS) parents += res_load(&I.res->parents[round & 1][k]);
                                 const u64 x0 = res_load(&part[k].hproj[0]), x1 = res_load(&part[k].hproj[1]),
                                           x2 = res_load(&part[k].vproj[0]), x3 = res_load(&part[k].vproj[1]);
                                 add128(hl, hh, x0, x1);
@@ -762,10 +878,12 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                             wave_scan128(hl, hh);
                             wave_scan128(vl, vh);
                             const u64 x = wave_scan(state >> 32);
+                            if (GS) parents = wave_scan(parents);
                             const bool flagged = __any(state & 1);
                             if (lane == 63) {
                                 red[12] = hl; red[13] = hh; red[14] = vl; red[15] = vh;
                                 red[16] = x; red[17] = both; red[18] = flagged;
+                                if (GS) red[19] = parents;
                             }
                             max_load = max(max_load, (int)((state >> 8) & 0xffffff));
                             row_due = true;
@@ -841,7 +959,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 break;
             }
             __syncthreads();
-            if (s_full && (slots < SLOTS || (most > SLOTS && k1 - k0 > 1))) {
+            if (s_full && (slots < SLOTS || (!GS && most > SLOTS && k1 - k0 > 1))) {
                 // more addresses than expected: again with the whole hash,
                 // then with fewer buckets
                 if (slots == SLOTS) most = SLOTS;
@@ -851,147 +969,197 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             }
             redo = 0;
             if (s_full && tid == 0) fail(I, L, FQE_CAP_LDS, bA + k0);
-            // ------------------------------------------------ 2. occupied slots
-            // an index of them, so that the sums, draws and conversions run
-            // on full waves
-#pragma unroll 1
-            for (int s = tid; s < slots; s += BS) {
-                const bool occ = W == 1 ? L.k0[s] != EMPTY : L.state[s] == 2u;
-                const u64 m = __ballot(occ);
-                int at = 0;
-                if (lane == 0 && m) at = atomicAdd(&s_list, __popcll(m));
-                at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
-                if (occ) list[at] = (unsigned short)s;
-            }
-            __syncthreads();
-            // ------------------------------------------------ 3. compress, survivors and their attempts
+            // (the second run of two comes back here after its projection)
+            int nS = 0;
+            i64 A = 0;
             const u32 step1 = (u32)(n + 1);
-            const int nU = s_list, kb = k1 - k0;
-            distinct += nU;
-            whole = k0 == 0 && k1 == K;
-            held = whole && nU <= BS - 64;
-            u64 sum = 0;  // survivors from bit 48, attempts below
-            u64 nlo = 0, nhi = 0;
-            int odd = 0;
-            hc = 0.0;
 #pragma unroll 1
-            for (int j0 = -64; j0 + 64 < nU; j0 += BS - 64, odd ^= 16) {
-                const bool occ = wid > 0 && j0 + tid < nU;
-                int s = 0, bl = 0, pos = 0;
-                u64 a0 = 0, a1 = 0;
-                double c = 0.0;
-                u32 att = 0;
-                if (occ) {
-                    s = list[j0 + tid];
-                    a0 = L.k0[s];
-                    if (W == 2) a1 = L.k1[s];
-                    c = from_fixed(L.lo[s], L.hi[s]);
-                    if (!EARLY && c != 0.0 && fabs(c) < I.theta)
-                        c = compress1(c, I.theta, draw(I.seed, a0, a1, step1, 1u, 0u).x);
-                    L.lo[s] = dbits(c);
-                    if (kb > 1) bl = (int)bucket_index(AddrOf<W>::make(a0, a1), I.log2B, I.mc.nb <= 32) - (bA + k0);
-                }
-                const bool alive = c != 0.0;
-                bool exact = false;
-                if (alive) {
-                    int bad = 0;
-                    spawn_info<W, MODEL>(I, AddrOf<W>::make(a0, a1), c, att, exact, bad);
-                    if (bad) fail(I, L, FQE_ATTEMPTS, bA + k0 + bl);
-                    u64 lo, hi;
-                    int ovf = 0;
-                    to_fixed(fabs(c), lo, hi, ovf, inx);
-                    add128(nlo, nhi, lo, hi);
-                }
-                {
-                    const u64 em = __ballot(exact);
-                    if (lane == 0 && em) atomicAdd(&s_ex, __popcll(em));
-                }
-                // rank inside the bucket: one LDS atomic per wave for a few
-                // buckets, else one per lane
-                if (kb <= 4) {
+            for (int pass = 0;; pass++) {
+                const bool final = !second || pass == 1;
+                // ------------------------------------------------ 2. occupied slots
+                // an index of them, so that the sums, draws and conversions run
+                // on full waves
 #pragma unroll 1
-                    for (int b = 0; b < kb; b++) {
-                        const u64 um = __ballot(occ && bl == b), lm = __ballot(alive && bl == b);
-                        int at = 0;
-                        if (lane == 0) {
-                            if (um) atomicAdd(&used[k0 + b], __popcll(um));
-                            if (lm) at = atomicAdd(&keep[k0 + b], __popcll(lm));
-                        }
-                        at = __builtin_amdgcn_readfirstlane(at);
-                        if (alive && bl == b) pos = at + __popcll(lm & ((1ull << lane) - 1));
+                for (int s = tid; s < slots; s += BS) {
+                    const bool occ = W == 1 ? L.k0[s] != EMPTY : L.state[s] == 2u;
+                    const u64 m = __ballot(occ);
+                    int at = 0;
+                    if (lane == 0 && m) at = atomicAdd(&s_list, __popcll(m));
+                    at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & ((1ull << lane) - 1));
+                    if (occ) list[at] = (unsigned short)s;
+                }
+                __syncthreads();
+                // ------------------------------------------------ 3. compress, survivors and their attempts
+                const int nU = s_list, kb = k1 - k0;
+                distinct += nU;
+                Fx3 pn = fx3_zero();  // norm after the projection
+                int pinx = 0, povf = 0;
+                whole = k0 == 0 && k1 == K;
+                held = whole && nU <= BS - 64;
+                u64 sum = 0;  // survivors from bit 48, attempts below
+                u64 nlo = 0, nhi = 0;
+                int odd = 0;
+                hc = 0.0;
+#pragma unroll 1
+                for (int j0 = -64; j0 + 64 < nU; j0 += BS - 64, odd ^= 16) {
+                    const bool occ = wid > 0 && j0 + tid < nU;
+                    int s = 0, bl = 0, pos = 0;
+                    u64 a0 = 0, a1 = 0;
+                    double c = 0.0;
+                    u32 att = 0;
+                    if (occ) {
+                        s = list[j0 + tid];
+                        a0 = L.k0[s];
+                        if (W == 2) a1 = L.k1[s];
+                        c = GS && pass == 1 ? bitsd(L.lo[s]) : from_fixed(L.lo[s], L.hi[s]);
+                        if (!EARLY && !(GS && pass == 1) && c != 0.0 && fabs(c) < I.theta)
+                            c = compress1(c, I.theta, draw(I.seed, a0, a1, step1, 1u, 0u).x);
+                        L.lo[s] = dbits(c);
+                        if (kb > 1) bl = (int)bucket_index(AddrOf<W>::make(a0, a1), I.log2B, I.mc.nb <= 32) - (bA + k0);
                     }
-                } else {
-                    if (occ) atomicAdd(&used[k0 + bl], 1);
-                    if (alive) pos = atomicAdd(&keep[k0 + bl], 1);
-                }
-                if (alive && pos < I.cap_t) {
-                    const i64 e = (i64)(bA + k0 + bl) * I.cap_t + pos;
-                    gmem(I.tab_a[1 - p][0])[e] = a0;
-                    if (W == 2) gmem(I.tab_a[1 - p][1])[e] = a1;
-                    gmem(I.tab_v[1 - p])[e] = c;
-                }
-                u64 total;
-                const u64 at = sum + res_scan(alive ? ((u64)1 << 48) + att : 0, (u64 *)L.misc + odd, total);
-                sum += total;
-                if (alive) {
-                    live[at >> 48] = (unsigned short)s;
-                    off[at >> 48] = (u32)at;
-                }
-                h0 = a0;
-                h1 = a1;
-                hc = c;
-            }
-            if (tid == 0) L.misc[60] = 0;
-            __syncthreads();
-            const int nS = (int)(sum >> 48);
-            const i64 A = (i64)(sum & (((u64)1 << 48) - 1));
-            // ------------------------------------------------ 4. projected energy
-            u64 hlo = 0, hhi = 0, vlo = 0, vhi = 0;
-            {
-                const int e0 = I.ref_off[bA + k0], e1 = I.ref_off[bA + k1];
-#pragma unroll 1
-                for (int e = ref_held ? ref0 + BS - 1 - tid : e0 + tid; e < e1; e += BS) {
-                    if (e >= e0) {
-                        const u64 a0 = ref_held ? f0 : gmem(I.ref_a[0])[e];
-                        const u64 a1 = W == 1 ? 0 : ref_held ? f1 : gmem(I.ref_a[1])[e];
-                        const double rh = ref_held ? fh : gmem(I.ref_h)[e];
-                        const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
-                        const double cv = s >= 0 ? bitsd(L.lo[s]) : 0.0;
-#pragma unroll 1
-                        for (int r = 0; r < (e == I.ref_self ? 2 : 1); r++) {
+                    const bool alive = c != 0.0;
+                    bool exact = false;
+                    if (alive) {
+                        int bad = 0;
+                        if (final) spawn_info<W, MODEL>(I, AddrOf<W>::make(a0, a1), c, att, exact, bad);
+                        if (bad) fail(I, L, FQE_ATTEMPTS, bA + k0 + bl);
+                        if (GS && pass == 1) {
+                            fx3_add(pn, to_fx3(fabs(c), pinx, povf));
+                        } else {
                             u64 lo, hi;
                             int ovf = 0;
-                            to_fixed(r ? I.yref * cv : I.yref * (rh * cv), lo, hi, ovf, inx);
-                            if (r) add128(vlo, vhi, lo, hi);
-                            else add128(hlo, hhi, lo, hi);
+                            to_fixed(fabs(c), lo, hi, ovf, inx);
+                            add128(nlo, nhi, lo, hi);
                         }
                     }
-                    if (ref_held) break;
+                    {
+                        const u64 em = __ballot(exact);
+                        if (lane == 0 && em) atomicAdd(&s_ex, __popcll(em));
+                    }
+                    // rank inside the bucket: one LDS atomic per wave for a few
+                    // buckets, else one per lane
+                    if (kb <= 4) {
+#pragma unroll 1
+                        for (int b = 0; b < kb; b++) {
+                            const u64 um = __ballot(occ && bl == b), lm = __ballot(alive && bl == b);
+                            int at = 0;
+                            if (lane == 0) {
+                                if (um && pass == 0) atomicAdd(&used[k0 + b], __popcll(um));
+                                if (lm) at = atomicAdd(&keep[k0 + b], __popcll(lm));
+                            }
+                            at = __builtin_amdgcn_readfirstlane(at);
+                            if (alive && bl == b) pos = at + __popcll(lm & ((1ull << lane) - 1));
+                        }
+                    } else {
+                        if (occ && pass == 0) atomicAdd(&used[k0 + bl], 1);
+                        if (alive) pos = atomicAdd(&keep[k0 + bl], 1);
+                    }
+                    if (alive && final && pos < I.cap_t) {
+                        const i64 e = (i64)(bA + k0 + bl) * I.cap_t + pos;
+                        gmem(I.tab_a[1 - p][0])[e] = a0;
+                        if (W == 2) gmem(I.tab_a[1 - p][1])[e] = a1;
+                        gmem(I.tab_v[1 - p])[e] = c;
+                    }
+                    u64 total;
+                    const u64 at = sum + res_scan(alive ? ((u64)1 << 48) + att : 0, (u64 *)L.misc + odd, total);
+                    sum += total;
+                    if (alive) {
+                        live[at >> 48] = (unsigned short)s;
+                        off[at >> 48] = (u32)at;
+                    }
+                    h0 = a0;
+                    h1 = a1;
+                    hc = c;
                 }
-            }
-            // the wave's sums, limb by limb
-            auto limbs = [&](u64 *w, u64 &lo, u64 &hi) {
-                wave_scan128(lo, hi);
-                if (lane == 63) {
-                    atomicAdd(&w[0], lo & 0xffffffffull);
-                    atomicAdd(&w[1], lo >> 32);
-                    atomicAdd(&w[2], hi & 0xffffffffull);
-                    atomicAdd(&w[3], hi >> 32);
+                if (tid == 0) L.misc[60] = 0;
+                __syncthreads();
+                nS = (int)(sum >> 48);
+                A = (i64)(sum & (((u64)1 << 48) - 1));
+                // ------------------------------------------------ 4. projected energy
+                u64 hlo = 0, hhi = 0, vlo = 0, vhi = 0;
+                if (pass == 0) {
+                    const int e0 = I.ref_off[bA + k0], e1 = I.ref_off[bA + k1];
+#pragma unroll 1
+                    for (int e = ref_held ? ref0 + BS - 1 - tid : e0 + tid; e < e1; e += BS) {
+                        if (e >= e0) {
+                            const u64 a0 = ref_held ? f0 : gmem(I.ref_a[0])[e];
+                            const u64 a1 = W == 1 ? 0 : ref_held ? f1 : gmem(I.ref_a[1])[e];
+                            const double rh = ref_held ? fh : gmem(I.ref_h)[e];
+                            const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
+                            const double cv = s >= 0 ? bitsd(L.lo[s]) : 0.0;
+#pragma unroll 1
+                            for (int r = 0; r < (e == I.ref_self ? 2 : 1); r++) {
+                                u64 lo, hi;
+                                int ovf = 0;
+                                to_fixed(r ? I.yref * cv : I.yref * (rh * cv), lo, hi, ovf, inx);
+                                if (r) add128(vlo, vhi, lo, hi);
+                                else add128(hlo, hhi, lo, hi);
+                            }
+                        }
+                        if (ref_held) break;
+                    }
                 }
-            };
-            if (__any((nlo | nhi) != 0)) limbs(red, nlo, nhi);
-            if (__any((hlo | hhi | vlo | vhi) != 0)) {
-                limbs(red + 4, hlo, hhi);
-                limbs(red + 8, vlo, vhi);
+                // the wave's sums, limb by limb
+                auto limbs = [&](u64 *w, u64 &lo, u64 &hi) {
+                    wave_scan128(lo, hi);
+                    if (lane == 63) {
+                        atomicAdd(&w[0], lo & 0xffffffffull);
+                        atomicAdd(&w[1], lo >> 32);
+                        atomicAdd(&w[2], hi & 0xffffffffull);
+                        atomicAdd(&w[3], hi >> 32);
+                    }
+                };
+                if (__any((nlo | nhi) != 0)) limbs(red, nlo, nhi);
+                if (__any((hlo | hhi | vlo | vhi) != 0)) {
+                    limbs(red + 4, hlo, hhi);
+                    limbs(red + 8, vlo, vhi);
+                }
+                // capacities as the step kernels hold them
+                if (tid >= k0 && tid < k1) {
+                    const int u = used[tid];
+                    if (keep[tid] > I.cap_t) fail(I, L, FQE_CAP_TABLE, bA + tid);
+                    if (u > I.slots) fail(I, L, FQE_CAP_LDS, bA + tid);
+                    atomicMax(&s_load, u);
+                    if (final) I.tab_n[1 - p][bA + tid] = keep[tid];
+                }
+                if (!GS) break;
+                // ------------------------------------------------ projection
+                if (pass == 1) {
+                    if (pinx) atomicOr(&O.flags[0], 1);
+                    if (povf) fail(I, L, FQE_DIVERGED, bA);
+                    Fx3 *tmp = (Fx3 *)L.misc;
+                    static_assert(sizeof(Fx3) * (BS / 64) <= 60 * 8, "beside misc[60]");
+                    wave_scan_fx3(pn);
+                    __syncthreads();
+                    if (lane == 63) tmp[wid] = pn;
+                    __syncthreads();
+                    if (wid == 0) {
+                        pn = lane < BS / 64 ? tmp[lane] : fx3_zero();
+                        wave_scan_fx3(pn);
+                        if (lane == 63) norms[g] = pn;
+                    }
+                    break;
+                }
+                if (tid == 0) s_len = nS;
+                __syncthreads();
+                if (tid == 0 && (s_full || s_fail))
+                    __hip_atomic_store(&Y->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                res_barrier(Y, meet, ++met, s_where);
+                if (tid == 0) s_abort = (int)res_load(&Y->abort);
+                __syncthreads();
+                if (s_abort) break;
+                const Inst &IJ = const_inst(O.rep[0]);
+                if (second) resident_dot<W>(I, L, IJ, 1 - s_par[0], bA, K, (int *)off, O.flags, O.part + 2 * g);
+                res_barrier(Y, meet, ++met, s_where);
+                if (!second) break;
+                resident_project<W>(I, L, IJ, 1 - s_par[0], bA, K, G, (const int *)off, O.part, &s_alpha);
+                __syncthreads();
+                if (tid == 0) s_list = 0;
+                if (tid < K) keep[tid] = 0;
+                distinct = 0;
+                __syncthreads();
             }
-            // capacities as the step kernels hold them
-            if (tid >= k0 && tid < k1) {
-                const int u = used[tid];
-                if (keep[tid] > I.cap_t) fail(I, L, FQE_CAP_TABLE, bA + tid);
-                if (u > I.slots) fail(I, L, FQE_CAP_LDS, bA + tid);
-                atomicMax(&s_load, u);
-                I.tab_n[1 - p][bA + tid] = keep[tid];
-            }
+            if (GS && s_abort) break;
             // ------------------------------------------------ 5. spawn for step n+2
             if (row_due) write_row();
             if (OV && ov_step >= 0) write_overlaps();
@@ -1002,13 +1170,28 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 fail(I, L, FQE_CAP_SLAB, bA + k0);
             }
             if (tid == 0) {
-                s_len += nS;
+                if (GS) s_live = nS;
+                else s_len += nS;
                 s_sp += EARLY ? L.misc[60] : A;
             }
             k0 = k1;
             if (k0 < K) __syncthreads();
         }
+        if (GS && dead) {
+            // the others end at the first barrier of their step
+            if (tid == 0) __hip_atomic_store(&Y->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            res_barrier(Y, meet, ++met, s_where);
+            break;
+        }
         if (s_go != 2 && !dead) break;
+        if (GS && s_abort) {
+            // the step is undone, with the errors of this launch
+            if (g == 0 && tid == 0) {
+                __hip_atomic_store(&ctrl->error, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ctrl->err_bucket = 0;
+            }
+            break;
+        }
 
         // ---------------------------------------------------- 6. partial sums, barrier
         if (__any(inx) && lane == 0) s_inx = 1;
@@ -1031,6 +1214,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             }
             if (lane == 63) {
                 x.items = ((u64)s_len << 40) + (u64)s_sp;
+                if (GS) I.res->parents[(round + 1) & 1][g] = (u64)s_live;
                 x.state = (s_inx ? 1 : 0) | (s_fail || dead ? 2 : 0) | (whole ? 0 : 4) | ((u64)s_load << 8) | ((u64)s_ex << 32);
             }
         }
@@ -1039,13 +1223,14 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             if (G == 1)
                 __hip_atomic_store(gmem(&I.slab_n[1 - p][lane]), own[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             SpawnPart x{0, 0, 0, 0};
-            if (lane == 0) x = SpawnPart{s_ex, s_len - s_ex, s_sp, 0};
+            if (lane == 0) x = SpawnPart{s_ex, (GS ? s_live : s_len) - s_ex, s_sp, 0};
             I.spart[(n + 2) & 1][bA + lane] = x;
         }
-        res_barrier(Y, meet, ++round, s_where);
-        if (OV) {
+        round++;
+        res_barrier(Y, meet, ++met, s_where);
+        if (JOINT) {
             // the overlaps of step n are published now; the first barrier of a launch publishes none
-            if (me == 0 && g == 0 && wid == 0 && round > 1 && !dead) ov_step = n;
+            if (OV && me == 0 && g == 0 && wid == 0 && round > 1 && !dead) ov_step = n;
             if (tid < O.R) s_par[tid] ^= 1;
             __syncthreads();
         }
