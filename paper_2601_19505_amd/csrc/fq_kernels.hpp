@@ -50,7 +50,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(FQ_SPAWN_WAV
     fq::spawn_bucket<W, MODEL, BS, EARLY>(I, b, mode, smem);
 }
 
-// Resident steps of small instances, 2^lg_grid workgroups of the grid for
+// Resident steps, 2^lg_grid workgroups of the grid for
 // each.  Up to 32 (the CUs of an XCD) they are placed on XCD i mod 8 for
 // instance i: workgroup 8 ((i / 8) 2^lg_grid + g) + i mod 8 of the grid is
 // its workgroup g.  Above, workgroup i 2^lg_grid + g is.  An instance takes

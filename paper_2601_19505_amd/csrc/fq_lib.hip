@@ -5,9 +5,10 @@
 // annihilation, compression, projected energy, compaction into the other
 // table), k_spawn (one workgroup per bucket: spawn records of the new table
 // for the next step), k_part (second pass of the spawn partition, only when
-// there are more than 64 buckets) and k_finalize (one workgroup: exact
-// reduction of the per-bucket partial sums and the shift update).  Small
-// instances take many steps in one launch instead (k_resident).  The host
+// there are more than 64 buckets) and k_finalize (exact reduction of the
+// per-bucket partial sums and the shift update).  Instances of up to several
+// million entries and records take many steps in one launch instead
+// (k_resident; replicas and excited states k_resident_joint).  The host
 // synchronises only at the end of a chunk of steps, to copy the statistics
 // rows and check the error word.
 #include <hip/hip_runtime.h>
@@ -228,65 +229,108 @@ template <int W> __global__ __launch_bounds__(TWICE_BS) void k_twice(const Inst 
     }
 }
 
-// set_state: the inserted vector becomes the state, its norm ctrl->norm
-__global__ void k_take_norm(const Inst *Ip, const InsertNote *note)
+// set_state: the inserted vector becomes the state, with a fresh control block
+// and no pending spawns
+__global__ __launch_bounds__(256) void k_new_state(const Inst *Ip, Ctrl fresh, const InsertNote *note, int n_coarse)
 {
-    Ctrl *c = Ip->ctrl;
-    c->norm = from_fixed(note->norm[0], note->norm[1]);
-    c->inexact_in = note->inexact;
-    if (note->out_of_range) set_error(c, FQE_DIVERGED, -1);
-    if (note->overflow) set_error(c, FQE_CAP_TABLE, -1);
+    const Inst &I = const_inst(Ip);
+    const int at = blockIdx.x * blockDim.x + threadIdx.x, all = gridDim.x * blockDim.x;
+    for (int i = at; i < I.B; i += all) I.slab_n[0][i] = I.slab_n[1][i] = 0;
+    for (int i = at; i < n_coarse; i += all) I.coarse_n[i] = 0;
+    if (at != 0) return;
+    fresh.norm = from_fixed(note->norm[0], note->norm[1]);
+    fresh.inexact_in = note->inexact;
+    *I.ctrl = fresh;
+    if (note->out_of_range) set_error(I.ctrl, FQE_DIVERGED, -1);
+    if (note->overflow) set_error(I.ctrl, FQE_CAP_TABLE, -1);
 }
 
-// row of the reference address over its column's destinations: entry 0 is
-// the diagonal, then the off-diagonal entries in column order (equal to the
-// column's values unless importance sampling makes H asymmetric); bucket of
-// every destination
+// set_state: the row of the reference address over its column's
+// destinations, in the descriptor, sorted by bucket: entry 0 is the diagonal,
+// then the off-diagonal entries in column order (equal to the column's values
+// unless importance sampling makes H asymmetric).  One workgroup; counts by
+// bucket in LDS (bins: B + 1), then a scan, then the entries go to their
+// places, in any order within a bucket (the sums over them are exact).  One
+// thread took 176 us for the 144 entries of the 6 x 6 lattice, and the host
+// sorted them: twelve copies and waits, a third of a small request's set_state.
+constexpr int REF_BS = 256;
 template <int W, int MODEL>
-__global__ void k_ref(const Inst *Ip, u64 r0, u64 r1, u64 *oa, double *oh, int *ob, int *on, int cap)
+__global__ __launch_bounds__(REF_BS) void k_ref(Inst *Ip, u64 r0, u64 r1, double yref, u64 *oa, double *oh, int *ob,
+                                                int cap)
 {
+    extern __shared__ __align__(16) char smem[];
     const Inst &I = *Ip;
     typedef typename AddrOf<W>::T T;
     __shared__ unsigned char lut[2048];
-    for (int i = threadIdx.x; i < 2048; i += blockDim.x) lut[i] = select_lut_entry(i);
+    __shared__ int sums[REF_BS];
+    int *bins = (int *)smem;
+    const int tid = threadIdx.x, B = I.B;
+    for (int i = tid; i < 2048; i += REF_BS) lut[i] = select_lut_entry(i);
+    for (int b = tid; b <= B; b += REF_BS) bins[b] = 0;
     __syncthreads();
-    if (threadIdx.x != 0) return;
     const T a = AddrOf<W>::make(r0, r1);
     const T st = run_starts(a);
     const int o = popc(st);
-    double hd;
     i64 m;
-    if (MODEL == 0 || MODEL == 3) {
-        hd = real_diag_runs(I.mc, a);
-        m = (MODEL == 0 ? 2 : I.mc.ndir) * o;
-    } else {
-        hd = mom_diag_modes(I.mc, a);
-        m = mom_col_size(I.mc, a);
+    if (MODEL == 0 || MODEL == 3) m = (MODEL == 0 ? 2 : I.mc.ndir) * o;
+    else m = mom_col_size(I.mc, a);
+    if (m + 1 > cap) {
+        if (tid == 0) I.ctrl->ref_len = -1;
+        return;
     }
-    if (m + 1 > cap) { *on = -1; return; }
-    oa[0] = r0;
-    oa[1] = r1;
-    oh[0] = hd;
-    ob[0] = (int)bucket_index(a, I.log2B, I.mc.nb <= 32);
-    for (i64 e = 0; e < m; e++) {
+    for (int e = tid; e <= (int)m; e += REF_BS) {
         double h;
-        T d;
-        if (MODEL == 0) {
-            d = real_entry(I.mc, a, st, o, (int)e, h);
+        T d = a;
+        if (e == 0) {
+            if (MODEL == 0 || MODEL == 3) h = real_diag_runs(I.mc, a);
+            else h = mom_diag_modes(I.mc, a);
+        } else if (MODEL == 0) {
+            d = real_entry(I.mc, a, st, o, e - 1, h);
         } else if (MODEL == 3) {
             // the row of the reference: the inverse importance-sampling factor
             int kd;
-            d = lat_entry(I.mc, a, st, o, (int)e, h, kd, lut);
+            d = lat_entry(I.mc, a, st, o, e - 1, h, kd, lut);
             h = h * I.mc.gz[I.mc.N - kd];
         } else {
-            d = mom_column_entry(I.mc, a, (int)e, h, lut);
+            d = mom_column_entry(I.mc, a, e - 1, h, lut);
         }
-        oa[2 * (e + 1)] = word0(d);
-        oa[2 * (e + 1) + 1] = word1(d);
-        oh[e + 1] = h;
-        ob[e + 1] = (int)bucket_index(d, I.log2B, I.mc.nb <= 32);
+        const int b = (int)bucket_index(d, I.log2B, I.mc.nb <= 32);
+        oa[2 * e] = word0(d);
+        oa[2 * e + 1] = word1(d);
+        oh[e] = h;
+        ob[e] = b;
+        atomicAdd(&bins[b + 1], 1);
     }
-    *on = (int)m + 1;
+    __syncthreads();
+    // bins[b + 1]: where bucket b starts
+    const int per = (B + REF_BS - 1) / REF_BS, b0 = 1 + tid * per, b1 = min(b0 + per, B + 1);
+    int mine = 0;
+    for (int b = b0; b < b1; b++) mine += bins[b];
+    sums[tid] = mine;
+    __syncthreads();
+    int at = 0;
+    for (int t = 0; t < tid; t++) at += sums[t];
+    for (int b = b0; b < b1; b++) {
+        const int n = bins[b];
+        bins[b] = at;
+        at += n;
+    }
+    __syncthreads();
+    for (int e = tid; e <= (int)m; e += REF_BS) {
+        const int to = atomicAdd(&bins[ob[e] + 1], 1);
+        I.ref_a[0][to] = oa[2 * e];
+        I.ref_a[1][to] = oa[2 * e + 1];
+        I.ref_h[to] = oh[e];
+        if (e == 0) Ip->ref_self = to;
+    }
+    __syncthreads();
+    // .. and now where it ends
+    for (int b = tid; b <= B; b += REF_BS) I.ref_off[b] = bins[b];
+    if (tid == 0) {
+        Ip->ref_n = (int)m + 1;
+        Ip->yref = yref;
+        I.ctrl->ref_len = m + 1;
+    }
 }
 
 // copy table[parity] into contiguous arrays, ew words per address
@@ -455,8 +499,8 @@ struct Pinned {
         return e;
     }
 };
-// staging of set_state: a reference column (words, values, buckets), its
-// length, and the note of the insertion
+// staging of set_state: a reference column (words, values, buckets), and the
+// note of the insertion
 constexpr size_t REF_TMP_COLUMN = (sizeof(u64) * 2 + sizeof(double) + sizeof(int)) * REFCAP;
 constexpr size_t REF_TMP_NOTE = REF_TMP_COLUMN + 16, REF_TMP_BYTES = REF_TMP_COLUMN + 64;
 static_assert(REF_TMP_NOTE + sizeof(InsertNote) <= REF_TMP_BYTES, "the note fits behind the column");
@@ -1215,6 +1259,12 @@ static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, 
     return FQ_OK;
 }
 
+static const void *ref_kernel(int W, int var)
+{
+    if (W == 1) return var == 0 ? (const void *)k_ref<1, 0> : var == 3 ? (const void *)k_ref<1, 3> : (const void *)k_ref<1, 1>;
+    return var == 0 ? (const void *)k_ref<2, 0> : var == 3 ? (const void *)k_ref<2, 3> : (const void *)k_ref<2, 1>;
+}
+
 // The n entries inserted into the table of next_parity become the state
 // c^(step): shift, reference column, spawns for step+1.
 static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_t *ref_addr, double ref_val,
@@ -1230,63 +1280,28 @@ static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_
     c.shift = shift;
     c.ring_base = step + 1;
     c.stop_step = INT64_MAX;
-    HIPCHK(q, hipMemcpyAsync(q->d_ctrl, &c, sizeof c, hipMemcpyHostToDevice, s));
-    for (int k = 0; k < 2; k++) HIPCHK(q, hipMemsetAsync(q->inst.slab_n[k], 0, sizeof(int) * R.B, s));
-    HIPCHK(q, hipMemsetAsync(q->inst.coarse_n, 0, sizeof(int) << (R.log2G + R.log2SUB), s));
-    hipLaunchKernelGGL(k_take_norm, dim3(1), dim3(1), 0, s, (const Inst *)q->d_inst,
-                       (const InsertNote *)(q->ws + R.off_ref_tmp + REF_TMP_NOTE));
-    // reference column (on the device), sorted by bucket on the host
+    hipLaunchKernelGGL(k_new_state, dim3(std::min(64, R.B / 256 + 1)), dim3(256), 0, s, (const Inst *)q->d_inst, c,
+                       (const InsertNote *)(q->ws + R.off_ref_tmp + REF_TMP_NOTE), 1 << (R.log2G + R.log2SUB));
+    HIPCHK(q, hipGetLastError());
+    // reference column
     u64 *ra = (u64 *)(q->ws + R.off_ref_tmp);
     double *rh = (double *)(ra + 2 * REFCAP);
-    int *rb = (int *)(rh + REFCAP);
-    int *rn = rb + REFCAP;
+    int *rb = (int *)(rh + REFCAP), cap = REFCAP;
     u64 r0 = ref_addr[0], r1 = W == 2 ? ref_addr[1] : 0;
-#define REFK(W_, M_) hipLaunchKernelGGL((k_ref<W_, M_>), dim3(1), dim3(64), 0, s, (const Inst *)q->d_inst, r0, r1, ra, rh, rb, rn, REFCAP)
-    const int vm = variant(q->h.model, q->h.M, q->h.N, W, q->h.g, 0);
-    if (W == 1) { if (vm == 0) REFK(1, 0); else if (vm == 3) REFK(1, 3); else REFK(1, 1); }
-    else { if (vm == 0) REFK(2, 0); else if (vm == 3) REFK(2, 3); else REFK(2, 1); }
-#undef REFK
-    HIPCHK(q, hipGetLastError());
-    int m = 0;
-    HIPCHK(q, hipMemcpyAsync(&m, rn, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIPCHK(q, hipStreamSynchronize(s));
-    if (m < 1) { q->err = "reference column too long"; return FQ_ECAPACITY; }
-    std::vector<u64> ha(2 * (size_t)m);
-    std::vector<double> hh(m);
-    std::vector<int> hb(m);
-    HIPCHK(q, hipMemcpy(ha.data(), ra, sizeof(u64) * 2 * m, hipMemcpyDeviceToHost));
-    HIPCHK(q, hipMemcpy(hh.data(), rh, sizeof(double) * m, hipMemcpyDeviceToHost));
-    HIPCHK(q, hipMemcpy(hb.data(), rb, sizeof(int) * m, hipMemcpyDeviceToHost));
-    std::vector<int> order(m);
-    for (int i = 0; i < m; i++) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return hb[x] < hb[y]; });
-    std::vector<u64> sa0(m), sa1(m);
-    std::vector<double> sh(m);
-    std::vector<int> off(R.B + 1, 0);
-    int self = -1;
-    for (int k = 0; k < m; k++) {
-        int i = order[k];
-        sa0[k] = ha[2 * i];
-        sa1[k] = ha[2 * i + 1];
-        sh[k] = hh[i];
-        off[hb[i] + 1]++;
-        if (i == 0) self = k;
-    }
-    for (int b = 0; b < R.B; b++) off[b + 1] += off[b];
-    q->inst.ref_n = m;
-    q->inst.ref_self = self;
-    q->inst.yref = ref_val;
-    HIPCHK(q, hipMemcpy(q->inst.ref_a[0], sa0.data(), sizeof(u64) * m, hipMemcpyHostToDevice));
-    HIPCHK(q, hipMemcpy(q->inst.ref_a[1], sa1.data(), sizeof(u64) * m, hipMemcpyHostToDevice));
-    HIPCHK(q, hipMemcpy(q->inst.ref_h, sh.data(), sizeof(double) * m, hipMemcpyHostToDevice));
-    HIPCHK(q, hipMemcpy(q->inst.ref_off, off.data(), sizeof(int) * (R.B + 1), hipMemcpyHostToDevice));
-    HIPCHK(q, hipMemcpy(q->d_inst, &q->inst, sizeof(Inst), hipMemcpyHostToDevice));
+    double yref = ref_val;
+    const void *kr = ref_kernel(W, variant(q->h.model, q->h.M, q->h.N, W, q->h.g, 0));
+    const size_t bins = sizeof(int) * (R.B + 1);
+    HIPCHK(q, ensure_lds(kr, bins));
+    void *args[] = {(void *)&q->d_inst, (void *)&r0, (void *)&r1, (void *)&yref, (void *)&ra, (void *)&rh, (void *)&rb,
+                    (void *)&cap};
+    HIPCHK(q, hipLaunchKernel(kr, dim3(1), dim3(REF_BS), args, bins, s));
     // spawns of c^(step) for step+1
     HIPCHK(q, launch_spawn(q->X, 1, s));
     Ctrl cc;
     int rc;
     rc = read_ctrl(q, cc, s);
     if (rc) return rc;
+    if (cc.ref_len < 1) { q->err = "reference column too long"; return FQ_ECAPACITY; }
     if (cc.error) {
         q->err = std::string("set_state: ") + fqe_name(cc.error);
         return fqe_status(cc.error);

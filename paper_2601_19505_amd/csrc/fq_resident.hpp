@@ -23,10 +23,12 @@
 // host steps it with the step kernels.  Behind an open gate every workgroup
 // is running, so each later barrier ends.
 //
-// The code is kept small (loops are rolled, every building block is inlined
-// once): a step runs through all of it once, and the instruction cache of
-// 64 KiB serves two CUs.  With 67 KB of unrolled code a step of 900 attempts
-// took 14.7 us, most of it instruction fetches.
+// A small step is bound by its chain of dependent latencies (a dozen
+// workgroup barriers of 60 ns, LDS and L2 round trips, Philox blocks, two
+// logarithms, the barrier of the workgroups) and by the VALU issue of 16 waves
+// on 4 SIMDs: 10.8 us a step at 1e3 walkers of the 6/6 ring.  The code is kept
+// small (loops are rolled, every building block is inlined once; 30 KB); 67 KB
+// of unrolled code were no faster.
 //
 // Exchange.  What another workgroup reads (records, counts, partial sums) is
 // read with agent-scope loads.  An instance of up to 32 workgroups is placed
@@ -73,7 +75,8 @@ struct ResPart {
     u64 norm[2];
     u64 items;    // entries from bit 40; records of the spawn pass for the next step below
     u64 state;    // bit 0: some sum was rounded first, bit 1: the step failed, bit 2: the hash did
-                  // not hold the whole vector; from bit 8 the most distinct addresses in a bucket; from bit 32 exact parents of the spawn pass
+                  // not hold the whole vector; from bit 8 the most distinct addresses in a
+                  // bucket; from bit 32 exact parents of the spawn pass
     u64 hproj[2], vproj[2];
 };
 static_assert(sizeof(ResPart) == 64, "two to a cache line");
@@ -82,7 +85,7 @@ static_assert(sizeof(ResPart) == 64, "two to a cache line");
 // double buffered by step parity: a workgroup can be at most one barrier
 // ahead of the slowest reader.
 struct ResSync {
-    u32 arrived, gate, xccs, abort, pad0[12], on[RES_XCCS];  // xccs: mask of the XCDs its workgroups run on, on: how many each
+    u32 arrived, gate, xccs, abort, pad0[12], on[RES_XCCS];  // XCDs the workgroups run on (mask), how many on each
     u32 count, pad1[31];
     u32 here[RES_XCCS][32];  // barrier arrivals by XCD, a line each
     ResPart part[2][RES_MAXG];
@@ -1164,8 +1167,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             if (row_due) write_row();
             if (OV && ov_step >= 0) write_overlaps();
             if (A < ((i64)1 << 32)) {
-                resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, bA, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own, lut,
-                                                tri);
+                resident_spawn<W, MODEL, EARLY>(I, L, 1 - p, bA, G == 1, step1 + 1u, nS, A, live, off, cnt, base, own,
+                                                lut, tri);
             } else if (tid == 0) {
                 fail(I, L, FQE_CAP_SLAB, bA + k0);
             }
@@ -1215,7 +1218,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
             if (lane == 63) {
                 x.items = ((u64)s_len << 40) + (u64)s_sp;
                 if (GS) I.res->parents[(round + 1) & 1][g] = (u64)s_live;
-                x.state = (s_inx ? 1 : 0) | (s_fail || dead ? 2 : 0) | (whole ? 0 : 4) | ((u64)s_load << 8) | ((u64)s_ex << 32);
+                x.state = (s_inx ? 1 : 0) | (s_fail || dead ? 2 : 0) | (whole ? 0 : 4) | ((u64)s_load << 8) |
+                          ((u64)s_ex << 32);
             }
         }
         if (wid == 1 && lane < K && !dead) {

@@ -68,6 +68,7 @@ struct Ctrl {
     u64 probes;        // LDS hash probes summed over all inserts (diagnostics)
     u64 inserts;
     i64 first_inexact; // first step whose row has ROW_INEXACT since the state was set, 0 if none
+    i64 ref_len;       // entries of the reference column, -1 if too long (set_state only)
 };
 
 // per-bucket partial statistics, written with plain stores by the workgroup
