@@ -847,6 +847,7 @@ struct fq_handle {
     int parity;
     i64 items, work;  // of the last step: entries and spawn records; entries and spawn attempts
     bool items_known; // from a statistics row, else an estimate
+    i64 load;         // most distinct addresses in a bucket so far, 0 if not known
     std::string err;
     int timing;
     double time_ms[NEV - 1];
@@ -1312,6 +1313,7 @@ static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_
     // entries and attempts; an exact parent has fewer events than walkers
     q->items = q->work = (i64)std::min(1e15, 2.0 * (double)n + cc.norm);
     q->items_known = false;
+    q->load = 0;
     q->ref[0] = ref_addr[0];
     q->ref[1] = R.E == 2 ? ref_addr[1] : 0;
     q->yref = ref_val;
@@ -1421,27 +1423,38 @@ bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
 // states, in one launch (late compression; at most half as many workgroups as
 // buckets, whose sums share the scratch).  The hash of a workgroup has to hold
 // its part of the vector until the overlaps are summed (excited states: the
-// parts of both runs), so the items of a step stay below its slots; larger
-// ones keep the step kernels.
+// parts of both runs): the most addresses that one of B buckets has had, three
+// standard deviations above the mean or so, say what K buckets have; while
+// that is not known, the items of a step bound it.  A launch that finds its
+// hash too small ends, and its chunk is left to the step kernels.  Two
+// replicas of the 12/12 ring at 1e6 walkers (2.2e6 items): 54 us a step, 254
+// with the step and overlap kernels.
 i64 joint_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
 bool plan_joint(fq_handle *const *h, int n, int var, bool excited, ResPlan &P)
 {
     if (n > (excited ? 2 : RES_MAXR) || var >= 4 || !plan_resident(h, n, P)) return false;
     const int log2B = h[0]->R.log2B;
-    const i64 hashes = excited ? 1 : n;  // one of them holds the items of all
+    const i64 hash = h[0]->R.W == 1 ? ResSlots<1>::N : ResSlots<2>::N;
     i64 items = 0, work = 0;
+    double mean = 0;  // addresses of a bucket
+    bool known = true;
     for (int i = 0; i < n; i++) {
         items += h[i]->items;
         work += h[i]->work;
+        const double m = std::max(0.0, (double)h[i]->load - 3.0 * std::sqrt((double)h[i]->load));
+        mean = excited ? mean + m : std::max(mean, m);
+        known = known && h[i]->load > 0;
     }
     bool fits = false;
     for (int lg = res_log2_groups(0, log2B); lg < log2B && n << lg <= RES_MAXG; lg++) {
+        const double of_group = mean * (double)((i64)1 << (log2B - lg));
+        const i64 most = known ? RES_MOST : joint_most(h[0]->R.W) / (excited ? n : 1);
         P.lg = P.lg_grid = lg;
         P.per = n;
-        fits = items <= (hashes * joint_most(h[0]->R.W) << lg) && items <= hashes * res_limit(h[0], RES_MOST, lg);
+        fits = items <= n * res_limit(h[0], most, lg) && of_group + 4.0 * std::sqrt(of_group) <= (double)(hash - hash / 32);
         const bool aim = work <= (n * RES_AIM << lg);
-        P.most = aim ? std::min(RES_MORE, joint_most(h[0]->R.W)) : joint_most(h[0]->R.W);
-        if (aim) break;
+        P.most = aim ? std::min(RES_MORE, most) : most;
+        if (fits && aim) break;
     }
     return fits;
 }
@@ -1858,6 +1871,7 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, cons
         }
         q->step = c.step;
         q->parity = c.parity;
+        q->load = c.max_load;
         if (c.error && rc == FQ_OK) {
             q->err = std::string(fqe_name(c.error)) + " at step " + std::to_string(c.step + 1) +
                      (c.err_bucket >= 0 ? " (bucket " + std::to_string(c.err_bucket) + ")" : "");
@@ -1969,7 +1983,7 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
                 }
                 if (resident && rc == FQ_OK) {
                     // what is left of the chunk comes with the next ones
-                    again = done > 0;
+                    again = done >= std::min<i64>(chunk, 16);
                     chunk = done;
                 } else if (!resident) {
                     again = true;

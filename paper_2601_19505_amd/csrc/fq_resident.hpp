@@ -776,7 +776,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         // fit the hash; a bucket larger than that is a batch alone (its
         // distinct addresses usually fit).  The first batch is cleared for
         // while the counts arrive, and merged again if it does not fit.
-        for (int k0 = 0, k1 = 0, redo = 0, most = GS ? 1 << 30 : few ? 8 * SLOTS : SLOTS; k0 < K;) {
+        for (int k0 = 0, k1 = 0, redo = 0, most = JOINT ? 1 << 30 : few ? 8 * SLOTS : SLOTS; k0 < K;) {
             const bool all = k0 > 0 || redo;
             if (all || slots == 0 || second) slots = SLOTS;
             if (all || wid > 1) {
@@ -831,7 +831,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 if (JOINT) {
                     // the same answer in every replica: after each step all go on or none
                     items += (i64)lane_value(wave_scan(others >> 8), 63);
-                    end = end || items > (GS ? item_limit : item_limit * O.R) || __any(((others | state) & 6) != 0);
+                    end = end || items > item_limit * O.R || __any(((others | state) & 6) != 0);
                 } else {
                     end = end || items > item_limit;
                 }

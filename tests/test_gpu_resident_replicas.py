@@ -50,6 +50,9 @@ def _same_states(a, b, n):
     (2, dict(BASE, model=2, M=9, N=9, lx=3, t=0.1, u=1.0, g=1.0, dtau=5e-3, buckets=4), (300,)),
     (2, dict(BASE, buckets=4, flags=32), (200,)),                 # early compression: step kernels
     (2, dict(BASE, M=9, N=9, target_walkers=4e3, buckets=2, lds_slots=4096), (500, 200)),  # outgrows two workgroups
+    # few addresses and many records; more addresses than the hashes hold
+    (2, dict(MOM, M=7, N=7, target_walkers=3e4, buckets=4, table_capacity=6000, spawn_capacity=200000), (300, 100)),
+    (2, dict(BASE, M=11, N=11, target_walkers=3e4, buckets=16, table_capacity=60000, spawn_capacity=200000), (400, 100, 50)),
     (2, dict(BASE, M=12, N=12, target_walkers=4e4, buckets=256, lds_slots=2048, block=512, table_capacity=200000,
              spawn_capacity=400000), (500, 300)),
 ])

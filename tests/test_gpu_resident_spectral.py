@@ -51,6 +51,9 @@ def _same_states(a, b, n):
     (2, dict(BASE, model=2, M=9, N=9, lx=3, t=0.1, u=1.0, g=1.0, dtau=5e-3, buckets=4), (300,)),
     (2, dict(BASE, model=1, u=2.0, dtau=5e-4, buckets=8), (200,)),   # equal runs: the second vanishes or not alike
     (2, dict(BASE, M=9, N=9, target_walkers=5e3, buckets=8), (500, 100)),   # outgrows four workgroups a run
+    # few addresses and many records; more addresses than the hashes hold
+    (2, dict(BASE, M=6, N=6, target_walkers=3e4, buckets=2, table_capacity=3000, spawn_capacity=200000), (400, 100)),
+    (2, dict(BASE, M=10, N=10, target_walkers=2e4, buckets=32, table_capacity=60000, spawn_capacity=200000), (400, 100)),
     (2, dict(BASE, M=12, N=12, target_walkers=3e4, buckets=256, table_capacity=200000, spawn_capacity=400000),
      (400, 200)),
 ])
