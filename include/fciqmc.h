@@ -263,8 +263,10 @@ int fq_autotune(fq_handle *src, const fq_layout *candidates, int32_t n, int32_t 
                 size_t scratch_bytes, double *ms, int32_t *best, void *stream);
 
 /* ------------------------------------------------------------------------
- * Batch: n independent instances advanced together, one launch per kernel
- * per step for the whole batch (each workgroup finds its instance and bucket
+ * Batch: n independent instances advanced together, many steps in one launch
+ * for as many of them as get onto the GPU at once, or, when one is too large
+ * for that (or is timed, dumped or phase-timed), one launch per kernel per
+ * step for the whole batch (each workgroup finds its instance and bucket
  * from a map), with per-instance tables, shifts and statistics.  Instances
  * may differ in Hamiltonian (M, N, t, u, g), parameters and capacities;
  * they must share the model kind (the ring without importance sampling; the
