@@ -180,7 +180,13 @@ __device__ __forceinline__ void res_barrier(ResSync *Y, int G, u32 round, const 
             all = xccs;
             count = __hip_atomic_fetch_add(&Y->here[xcc][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                     n * round - 1u;
-            if (count) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (count) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                // The count must not overtake the write back.  The compiler
+                // leaves the fence's own wait out: it does not count the
+                // write back among the operations in flight, and knows of no other.
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
         }
         if (count) __hip_atomic_fetch_add(&Y->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         while (__hip_atomic_load(&Y->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all * round) {}
