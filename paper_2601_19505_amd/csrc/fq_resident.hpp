@@ -908,7 +908,9 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                         __syncthreads();
                     }
                 }
-                const bool table = ph == 1, regs = table && held;
+                // the registers hold the survivors of all buckets: not for a
+                // batch of some of them, which reads its own from the table
+                const bool table = ph == 1, regs = table && held && k0 == 0 && k1 == K;
                 if (wid == 0) continue;
                 const int *pre = table ? pt : ps;
                 const int end = pre[k1];
