@@ -98,7 +98,7 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64
         insts[i]->fin->done = 0;
         if (resident) {
             ResSync *y = insts[i]->res;
-            y->arrived = y->gate = y->xccs = y->abort = y->count = 0;
+            y->arrived = y->gate = y->xccs = y->abort[0] = y->abort[1] = y->count = 0;
             for (int x = 0; x < RES_XCCS; x++) y->on[x] = y->here[x][0] = 0;
         }
     }

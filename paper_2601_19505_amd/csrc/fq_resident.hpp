@@ -85,7 +85,7 @@ static_assert(sizeof(ResPart) == 64, "two to a cache line");
 // double buffered by step parity: a workgroup can be at most one barrier
 // ahead of the slowest reader.
 struct ResSync {
-    u32 arrived, gate, xccs, abort, pad0[12], on[RES_XCCS];  // XCDs the workgroups run on (mask), how many on each
+    u32 arrived, gate, xccs, abort[2], pad0[11], on[RES_XCCS];  // XCDs the workgroups run on (mask), how many on each
     u32 count, pad1[31];
     u32 here[RES_XCCS][32];  // barrier arrivals by XCD, a line each
     ResPart part[2][RES_MAXG];
@@ -287,15 +287,20 @@ __device__ __forceinline__ void resident_overlap(const Overlap &O, const Lds &L,
 // which a hash did not hold its vector or a merge failed ends there, undone
 // (only the tables that the next step overwrites have been written), and the
 // step kernels make it.  Then the workgroups of run 1 stream their buckets of
-// run 0 against their hash for c_0 . c_1 and c_0 . c_0, meet, and stream them
-// once more to subtract.  A step of two runs of the 12/12 ring at 1e5 walkers
-// takes 47 us so, 102 with the step and projection kernels.
+// run 0 against their hash for c_0 . c_1 and c_0 . c_0, counting the addresses
+// of run 0 that it does not hold, meet, and stream them once more to
+// subtract.  The second barrier undoes the step in the same way when some
+// hash does not hold the addresses of both runs: its vote has a word of its
+// own, because the votes of the first barrier are still being read then.  A step of
+// two runs of the 12/12 ring at 1e5 walkers takes 47 us so, 102 with the step
+// and projection kernels.
 //
 // This workgroup's c_0 . c_1 and c_0 . c_0 (to[0], to[1]); words: as above,
-// the sums of the waves behind them.
+// the sums of the waves behind them.  addresses (LDS): those of the hash,
+// plus in the end those of run 0 beyond them.
 template <int W>
 __device__ __forceinline__ void resident_dot(const Inst &I, const Lds &L, const Inst &IJ, const int pj, const int bA,
-                                             const int K, int *words, int *flags, Fx3 *to)
+                                             const int K, int *words, int *flags, Fx3 *to, int *addresses)
 {
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     Fx3 *tmp = (Fx3 *)(words + 2 * RES_MAXK);
@@ -303,14 +308,18 @@ __device__ __forceinline__ void resident_dot(const Inst &I, const Lds &L, const 
     __syncthreads();
     int inexact = 0, ovf = 0;
     Fx3 dot = fx3_zero(), sq = fx3_zero();
+    int fresh = 0;
     resident_stream<W>(IJ, pj, bA, K, words, [&](u64 a0, u64 a1, double v) {
         fx3_add(sq, to_fx3(v * v, inexact, ovf));
         const int s = lds_find<W>(L, a0, a1, slot_hash(a0, a1));
+        fresh += s < 0;
         const double c = s >= 0 ? bitsd(L.lo[s]) : 0.0;
         if (c != 0.0) fx3_add(dot, to_fx3(v * c, inexact, ovf));
     });
     wave_scan_fx3(dot);
     wave_scan_fx3(sq);
+    fresh = (int)wave_scan((u64)fresh);
+    if (lane == 63 && fresh) atomicAdd(addresses, fresh);
     if (lane == 63) {
         tmp[wid] = dot;
         tmp[RES_BS / 64 + wid] = sq;
@@ -325,11 +334,13 @@ __device__ __forceinline__ void resident_dot(const Inst &I, const Lds &L, const 
     }
 }
 
-// c_1 <- c_1 - alpha c_0 in the hash; sums: the workgroups' resident_dot
+// c_1 <- c_1 - alpha c_0 in the hash, which has room for the addresses of
+// both, unless the step is undone (*undone, LDS, read behind a barrier);
+// sums: the workgroups' resident_dot
 template <int W>
 __device__ __forceinline__ void resident_project(const Inst &I, const Lds &L, const Inst &IJ, const int pj, const int bA,
                                                  const int K, const int G, const int *words, const Fx3 *sums,
-                                                 double *s_alpha)
+                                                 double *s_alpha, const int *undone)
 {
     const int lane = threadIdx.x & 63;
     if (threadIdx.x < 64) {
@@ -348,6 +359,7 @@ __device__ __forceinline__ void resident_project(const Inst &I, const Lds &L, co
         }
     }
     __syncthreads();
+    if (*undone) return;
     const double alpha = *s_alpha;
     int np = 0;
     resident_stream<W>(IJ, pj, bA, K, words, [&](u64 a0, u64 a1, double v) {
@@ -1154,17 +1166,25 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 if (tid == 0) s_len = nS;
                 __syncthreads();
                 if (tid == 0 && (s_full || s_fail))
-                    __hip_atomic_store(&Y->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&Y->abort[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 res_barrier(Y, meet, ++met, s_where);
-                if (tid == 0) s_abort = (int)res_load(&Y->abort);
+                if (tid == 0) s_abort = (int)res_load(&Y->abort[0]);
                 __syncthreads();
                 if (s_abort) break;
                 const Inst &IJ = const_inst(O.rep[0]);
-                if (second) resident_dot<W>(I, L, IJ, 1 - s_par[0], bA, K, (int *)off, O.flags, O.part + 2 * g);
+                if (second) {
+                    // (s_list: the addresses of the hash)
+                    resident_dot<W>(I, L, IJ, 1 - s_par[0], bA, K, (int *)off, O.flags, O.part + 2 * g, &s_list);
+                    if (tid == 0 && s_list > SLOTS)
+                        __hip_atomic_store(&Y->abort[1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
                 res_barrier(Y, meet, ++met, s_where);
-                if (!second) break;
-                resident_project<W>(I, L, IJ, 1 - s_par[0], bA, K, G, (const int *)off, O.part, &s_alpha);
+                // (wave 1: resident_project sums the dot products in wave 0)
+                if (tid == 64) s_abort = (int)res_load(&Y->abort[1]);
+                if (second)
+                    resident_project<W>(I, L, IJ, 1 - s_par[0], bA, K, G, (const int *)off, O.part, &s_alpha, &s_abort);
                 __syncthreads();
+                if (s_abort || !second) break;
                 if (tid == 0) s_list = 0;
                 if (tid < K) keep[tid] = 0;
                 distinct = 0;
@@ -1190,7 +1210,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         }
         if (GS && dead) {
             // the others end at the first barrier of their step
-            if (tid == 0) __hip_atomic_store(&Y->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) __hip_atomic_store(&Y->abort[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             res_barrier(Y, meet, ++met, s_where);
             break;
         }
