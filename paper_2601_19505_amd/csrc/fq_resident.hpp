@@ -544,7 +544,9 @@ __device__ __forceinline__ void resident_spawn(const Inst &I, const Lds &L, cons
 // instance's stop step, at an error, and after a step that leaves more than
 // max_items entries and records to merge.  An instance whose buckets may hold
 // more addresses than the hash is not begun when one of them might now; later
-// the number of items, half the hash a bucket, keeps them from it.
+// the number of items, half the hash a bucket, keeps them from it, and a
+// bucket that nevertheless fills three quarters of it (a state may have all
+// its entries in one bucket) ends the launch.
 // KIND 1: the instance is replica `me` of O, whose replicas start at one step
 // and stop together: all of them decide from the same sums and flags.  O.ring
 // receives the overlaps of all steps but the last, whose tables the launch
@@ -738,6 +740,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
         // wave 0: the parts of the step that waits for its shift, summed over
         // the workgroups lane, lane + 64, ..
         u64 nl = 0, nh = 0, both = 0, state = 0;
+        bool full = false;  // a bucket of any instance that meets here comes close to the hash
+        auto load_of = [](u64 st) { return (int)((st >> 8) & 0xffffff); };
         const bool split = !concluded;
         const ResPart *part = I.res->part[round & 1];
         if (OV && split && !dead && me < O.R - 1)
@@ -749,6 +753,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                           x2 = res_load(&part[k].items), x3 = res_load(&part[k].state);
                 add128(nl, nh, x0, x1);
                 both += x2;
+                full = full || (large && load_of(x3) > 3 * SLOTS / 4);
                 // flags joined, largest load, sum of exact parents
                 state = (state & 7) | (x3 & 7) | (max(state & 0xffffff00u, x3 & 0xffffff00u)) |
                         (((state >> 32) + (x3 >> 32)) << 32);
@@ -763,6 +768,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 const ResPart *x = &const_inst(O.rep[r]).res->part[round & 1][w & (G - 1)];
                 const u64 it = res_load(&x->items), st = res_load(&x->state);
                 others |= st & 6;
+                full = full || (large && load_of(st) > 3 * SLOTS / 4);
                 others += ((it >> 40) + (it & (((u64)1 << 40) - 1))) << 8;
             }
         }
@@ -845,7 +851,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 if (N1 > 0.0) S1 = (S - I.zeta / I.dtau * l0) - I.xi / I.dtau * l1;
                 const bool error = __any(state & 2), diverged = !(N1 < 17592186044416.0) || !(S1 == S1);
                 i64 items = (i64)(both >> 40) + (i64)(both & (((u64)1 << 40) - 1));
-                bool end = n + 1 >= stop;
+                bool end = n + 1 >= stop || __any(full);
                 if (JOINT) {
                     // the same answer in every replica: after each step all go on or none
                     items += (i64)lane_value(wave_scan(others >> 8), 63);
@@ -906,7 +912,7 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                                 red[16] = x; red[17] = both; red[18] = flagged;
                                 if (GS) red[19] = parents;
                             }
-                            max_load = max(max_load, (int)((state >> 8) & 0xffffff));
+                            max_load = max(max_load, load_of(state));
                             row_due = true;
                         }
                         if (s_go != 2) break;

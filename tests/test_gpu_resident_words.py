@@ -128,28 +128,39 @@ def test_buckets_larger_than_the_hash(name, more, calls):
     b.close()
 
 
-def test_a_bucket_that_holds_more_than_the_hash_is_not_begun():
-    """2200 addresses, all of one bucket of 8: fewer items than the limit of a
-    launch, and more in that bucket than its hash has slots."""
+def _of_one_bucket(spec, most, n):
+    """n addresses that share one of the 8 buckets of `spec`: a state comes
+    back bucket after bucket, so an entry's neighbours are of its bucket."""
     import paper_2601_19505_amd as fq
     import synthetic
-    spec = dict(LARGE, M=33, N=31, buckets=8, table_capacity=30000, spawn_capacity=60000, target_walkers=2e3)
-    occ = synthetic.random_occupations(np.random.default_rng(7), spec["M"], spec["N"], 24000)
-    all_ = fq.encode_many(occ, 2)
-    one, many = fq.Solver(**spec), [fq.Solver(**spec) for _ in range(2)]
-    # the state comes back bucket after bucket: an entry's neighbours share its bucket
-    one.set_state(all_, np.ones(len(all_)), 0.0, 0, ref=all_[0])
+    occ = synthetic.random_occupations(np.random.default_rng(7), spec["M"], spec["N"], most)
+    a = fq.encode_many(occ, 2)
+    one = fq.Solver(**spec)
+    one.set_state(a, np.ones(len(a)), 0.0, 0, ref=a[0])
     a, _, _, _ = one.get_state()
     one.close()
-    a = a[:2200]
-    v = np.linspace(0.2, 0.4, len(a))
-    many[1].set_timing(True)
-    for s in many:
-        s.set_state(a, v, 0.0, 0, ref=a[0])
-    for n in (2, 100):
-        assert many[0].run(n).tobytes() == many[1].run(n).tobytes(), n
-    # more in one bucket than the hash of a workgroup has slots
-    assert many[1].debug_counters()["max_load"] > 2048
-    assert _same(_state(many[0]), _state(many[1]))
-    for s in many:
-        s.close()
+    return a[:n]
+
+
+@pytest.mark.parametrize("n, value, shift, calls", [
+    (2200, 0.3, 0.0, (2, 100)),    # more than the hash of a workgroup: not begun
+    (1760, 1.0, 100.0, (20, 20)),  # begun; the second step has two attempts an entry, and then it is more
+])
+def test_a_bucket_that_fills_the_hash(n, value, shift, calls):
+    """All addresses in one bucket of 8: fewer items than the limit of a
+    launch, and more in that bucket than its hash has slots."""
+    import paper_2601_19505_amd as fq
+    spec = dict(LARGE, M=33, N=31, buckets=8, table_capacity=30000, spawn_capacity=60000, target_walkers=2e3)
+    print("[words] one bucket", n, flush=True)
+    a = _of_one_bucket(spec, 24000, n)
+    v = np.full(len(a), value)
+    x, y = fq.Solver(**spec), fq.Solver(**spec)
+    y.set_timing(True)
+    for s in (x, y):
+        s.set_state(a, v, shift, 0, ref=a[0])
+    for k in calls:
+        assert x.run(k).tobytes() == y.run(k).tobytes(), k
+    assert y.debug_counters()["max_load"] > 2048
+    assert _same(_state(x), _state(y))
+    x.close()
+    y.close()
