@@ -221,6 +221,10 @@ int fq_read_merged_dump(fq_handle *q, uint64_t *addr, double *value, int64_t cap
 
 /* Kernel timing with HIP events recorded on the run stream around the
  * launches of each step while `enable` is non-zero (five events per step).
+ * A timed run, of a handle or of a batch with a timed instance, takes one
+ * launch per kernel per step.  An untimed run of up to several million
+ * entries and spawn records takes many steps in one launch instead, on other
+ * kernels, so these times do not describe it.  The results are the same.
  * fq_kernel_time fills ms[0..n-1] with the summed milliseconds since the
  * last reset of: [0] the merge kernel (annihilation, compression, projected
  * energy, compaction), [1] the spawn kernel, [2] the second pass of the
@@ -256,7 +260,8 @@ const char *fq_last_error(const fq_handle *q);
  * (caller-owned device memory), copies the state, runs `trial_steps` steps
  * and records the mean milliseconds per step from HIP events in ms[i]
  * (negative when the candidate does not fit `scratch` or fails).  *best is
- * the index of the fastest candidate.  `src` is not modified.
+ * the index of the fastest candidate.  `src` is not modified.  A trial is one
+ * untimed fq_run of trial_steps steps, on the kernels that such a call takes.
  * ------------------------------------------------------------------------ */
 int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream);
 int fq_autotune(fq_handle *src, const fq_layout *candidates, int32_t n, int32_t trial_steps, void *scratch,

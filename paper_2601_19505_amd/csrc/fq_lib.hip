@@ -1703,6 +1703,13 @@ int fq_autotune(fq_handle *src, const fq_layout *cand, int32_t n, int32_t trial_
                 size_t scratch_bytes, double *ms, int32_t *best, void *stream)
 {
     if (!src || !cand || n < 1 || trial_steps < 1 || !scratch || !ms || !best) return FQ_EINVAL;
+    hipStream_t s = (hipStream_t)stream;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
+        src->err = "autotune: hipEventCreate failed";
+        if (e0) (void)hipEventDestroy(e0);
+        return FQ_EHIP;
+    }
     *best = -1;
     double tbest = 0.0;
     for (int i = 0; i < n; i++) {
@@ -1712,17 +1719,22 @@ int fq_autotune(fq_handle *src, const fq_layout *cand, int32_t n, int32_t trial_
         if (fq_workspace_size(&src->h, &src->p, &cand[i], &need, &lo) != FQ_OK || need > scratch_bytes) continue;
         fq_handle *t = nullptr;
         if (fq_create(&src->h, &src->p, &cand[i], scratch, scratch_bytes, &t) != FQ_OK) continue;
+        // the call as a user makes it: with its kernels timed one by one a
+        // handle would take the step kernels, whatever the layout
         bool ok = fq_copy_state(t, src, stream) == FQ_OK && fq_run(t, 1, nullptr, stream) == FQ_OK;
+        float el = 0.0f;
+        ok = ok && hipEventRecord(e0, s) == hipSuccess;
+        ok = ok && fq_run(t, trial_steps, nullptr, stream) == FQ_OK;
+        ok = ok && hipEventRecord(e1, s) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
+             hipEventElapsedTime(&el, e0, e1) == hipSuccess;
         if (ok) {
-            fq_set_timing(t, 1);
-            ok = fq_run(t, trial_steps, nullptr, stream) == FQ_OK;
-        }
-        if (ok) {
-            ms[i] = (t->time_ms[0] + t->time_ms[1] + t->time_ms[2] + t->time_ms[3]) / (double)t->launches;
+            ms[i] = (double)el / (double)trial_steps;
             if (*best < 0 || ms[i] < tbest) { *best = i; tbest = ms[i]; }
         }
         fq_destroy(t);
     }
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
     if (*best < 0) { src->err = "autotune: no candidate ran"; return FQ_EINVAL; }
     return FQ_OK;
 }
