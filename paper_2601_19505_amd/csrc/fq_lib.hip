@@ -104,6 +104,12 @@ __global__ void k_begin_chunk(const Inst *const *insts, int n, int resident, i64
     }
 }
 
+// stop[i]: the step at which instance i halts
+__global__ void k_set_stops(const Inst *const *insts, int n, ResStops stop)
+{
+    for (int i = threadIdx.x; i < n; i += blockDim.x) insts[i]->ctrl->stop_step = stop.step[i];
+}
+
 // End of a chunk: the control blocks of n instances into one array, and the
 // rows of the chunk, at most `stride` of each instance, into another (none:
 // stride 0).  Both lie in pinned host memory: one launch and one wait take
@@ -1895,10 +1901,24 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, cons
     return FQ_OK;
 }
 
+hipError_t set_stops(const Exec &X, const i64 *stops, hipStream_t s)
+{
+    for (int from = 0; from < X.n; from += RES_MAXG) {
+        const int n = std::min(RES_MAXG, X.n - from);
+        ResStops st = {};
+        std::copy(stops + from, stops + from + n, st.step);
+        hipLaunchKernelGGL(k_set_stops, dim3(1), dim3(256), 0, s, X.insts + from, n, st);
+    }
+    return hipGetLastError();
+}
+
 // Resident steps of every instance of G up to `steps` more (or its stop
 // step), in as many launches as the growth of the instances takes.  The
-// steps left by an instance whose workgroups did not get onto the GPU
-// together, or outgrew them, are made by its own step kernels.
+// steps left by instances whose workgroups did not get onto the GPU
+// together, or outgrew them, are made by the step kernels: one instance by
+// its own launches, several by launches they share, in which those that have
+// made their steps halt.  40 rings of 1.2e4 items that have all outgrown their
+// workgroups: 83 us a step so, 2900 with launches of their own.
 int group_resident(Group &G, ResPlan plan, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t s, int *failed,
                    std::string &err, int &rc)
 {
@@ -1923,14 +1943,25 @@ int group_resident(Group &G, ResPlan plan, i64 steps, i64 stop, fq_step_stats **
         }
         if (!left) return FQ_OK;
         if (!stuck && plan_resident(G.h.data(), X.n, plan)) continue;
+        std::vector<i64> until(X.n), after(X.n);
+        i64 most = 0;
+        int more = 0, one = 0;
         for (int j = 0; j < X.n; j++) {
             const Ctrl &c = G.ctrl[j];
-            const i64 k = c.error ? 0 : std::min(c.stop_step, stops[j]) - c.step;
+            after[j] = c.stop_step;
+            until[j] = std::min(c.stop_step, stops[j]);
+            const i64 k = c.error ? 0 : until[j] - c.step;
             if (k <= 0) continue;
-            hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, G.h[j]->X.insts, 1, 0, (i64)-1);
-            for (i64 i = 0; i < k && e == hipSuccess; i++) e = exec_step(G.h[j]->X, s, nullptr);
-            if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
+            most = std::max(most, k);
+            one = j;
+            more++;
         }
+        const Exec &Y = more == 1 ? G.h[one]->X : X;
+        hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(256), 0, s, Y.insts, Y.n, 0, (i64)-1);
+        if (more > 1) e = set_stops(X, until.data(), s);
+        for (i64 i = 0; i < most && e == hipSuccess; i++) e = exec_step(Y, s, nullptr);
+        if (more > 1 && e == hipSuccess) e = set_stops(X, after.data(), s);
+        if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
         return group_collect(G, rows, s, steps, nullptr, nullptr, failed, err, rc);
     }
 }
