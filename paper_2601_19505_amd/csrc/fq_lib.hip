@@ -247,8 +247,6 @@ __global__ __launch_bounds__(256) void k_new_state(const Inst *Ip, Ctrl fresh, c
     fresh.norm = from_fixed(note->norm[0], note->norm[1]);
     fresh.inexact_in = note->inexact;
     *I.ctrl = fresh;
-    if (note->out_of_range) set_error(I.ctrl, FQE_DIVERGED, -1);
-    if (note->overflow) set_error(I.ctrl, FQE_CAP_TABLE, -1);
 }
 
 // set_state: the row of the reference address over its column's
@@ -346,7 +344,7 @@ __global__ __launch_bounds__(256) void k_pack(const Inst *Ip, u64 *oa, double *o
     const Inst &I = *Ip;
     const int p = I.ctrl->parity;
     for (int b = blockIdx.x; b < I.B; b += gridDim.x) {
-        const int nb = I.tab_n[p][b];
+        const int nb = (int)min((i64)I.tab_n[p][b], I.cap_t);
         __shared__ unsigned long long base;
         if (threadIdx.x == 0) base = nb ? atomicAdd(cnt, (unsigned long long)nb) : 0ull;
         __syncthreads();
@@ -885,6 +883,7 @@ static int check_entries(fq_handle *q, const uint64_t *addrs, const double *vals
 static int next_parity(const fq_handle *q);
 static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, int ew, bool check, InsertNote &note,
                           hipStream_t s);
+static int insertion_error(fq_handle *q, const InsertNote &note);
 static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_t *ref_addr, double ref_val,
                       hipStream_t s);
 
@@ -1206,6 +1205,8 @@ int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_
         rc = check_entries(q, addrs, vals, n);
         if (rc) return rc;
     }
+    rc = insertion_error(q, note);
+    if (rc) return rc;
     return load_state(q, n, shift, step, ref_addr, ref_val, s);
 }
 
@@ -1264,6 +1265,15 @@ static int insert_entries(fq_handle *q, const u64 *sa, const double *sv, i64 n, 
     HIPCHK(q, hipMemcpyAsync(&note, d_note, sizeof note, hipMemcpyDeviceToHost, s));
     HIPCHK(q, hipStreamSynchronize(s));
     return FQ_OK;
+}
+
+// Sound entries that cannot become the state: the current one stays.
+static int insertion_error(fq_handle *q, const InsertNote &note)
+{
+    const int code = note.out_of_range ? FQE_DIVERGED : note.overflow ? FQE_CAP_TABLE : 0;
+    if (code == 0) return FQ_OK;
+    q->err = std::string("set_state: ") + fqe_name(code);
+    return fqe_status(code);
 }
 
 static const void *ref_kernel(int W, int var)
@@ -1701,6 +1711,7 @@ int fq_copy_state(fq_handle *dst, fq_handle *src, void *stream)
     }
     InsertNote note;
     rc = insert_entries(dst, oa, ov, (i64)tot, E, false, note, s);
+    if (rc == FQ_OK) rc = insertion_error(dst, note);
     if (rc) return rc;
     return load_state(dst, (i64)tot, c.shift, c.step, src->ref, src->yref, s);
 }
