@@ -198,7 +198,8 @@ int fq_create(const fq_hamiltonian *h, const fq_params *p, const fq_layout *layo
  * S^(step), and the reference vector y = ref_val e_ref for the projected
  * energy (Sec. 4.2; the paper's default is y = c^(0) = 10 e_start).  Entries
  * that are refused, or do not fit their buckets, leave the state that is
- * there as it is. */
+ * there as it is.  When the spawns of the new state do not fit their slab it
+ * is in place, but every step fails until another state is set. */
 int fq_set_state(fq_handle *q, const uint64_t *addrs, const double *vals, int64_t n, double shift,
                  int64_t step, const uint64_t *ref_addr, double ref_val, void *stream);
 

@@ -1300,6 +1300,10 @@ static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_
     hipLaunchKernelGGL(k_new_state, dim3(std::min(64, R.B / 256 + 1)), dim3(256), 0, s, (const Inst *)q->d_inst, c,
                        (const InsertNote *)(q->ws + R.off_ref_tmp + REF_TMP_NOTE), 1 << (R.log2G + R.log2SUB));
     HIPCHK(q, hipGetLastError());
+    // the handle stands where the device does, also when the spawns fail:
+    // a later run counts its rows from here
+    q->step = step;
+    q->parity = par;
     // reference column
     u64 *ra = (u64 *)(q->ws + R.off_ref_tmp);
     double *rh = (double *)(ra + 2 * REFCAP);
@@ -1324,8 +1328,6 @@ static int load_state(fq_handle *q, i64 n, double shift, i64 step, const uint64_
         return fqe_status(cc.error);
     }
     q->have_state = 1;
-    q->step = step;
-    q->parity = par;
     // entries and attempts; an exact parent has fewer events than walkers
     q->items = q->work = (i64)std::min(1e15, 2.0 * (double)n + cc.norm);
     q->items_known = false;
