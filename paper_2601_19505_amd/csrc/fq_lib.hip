@@ -1542,6 +1542,8 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         const bool resident = again && plan_resident(&q, 1, plan);
         i64 chunk = std::min<i64>(RING, n_steps - done);
         if (!resident && !q->items_known) chunk = std::min<i64>(chunk, RES_GUESS_STEPS);
+        // before anything is launched: a failure leaves the handle where it is
+        HIPCHK(q, q->pinned.reserve(256 + sizeof(StepStats) * chunk));
         hipLaunchKernelGGL(k_begin_chunk, dim3(1), dim3(64), 0, s, q->X.insts, 1, resident ? 1 : 0, n_steps - done);
         if (q->timing && (i64)q->ev.size() < NEV * chunk) {
             size_t old = q->ev.size();
@@ -1554,7 +1556,6 @@ int fq_run(fq_handle *q, int64_t n_steps, fq_step_stats *stats_out, void *stream
         } else {
             for (i64 k = 0; k < chunk; k++) HIPCHK(q, exec_step(q->X, s, q->timing ? &q->ev[NEV * k] : nullptr));
         }
-        HIPCHK(q, q->pinned.reserve(256 + sizeof(StepStats) * chunk));
         const Ctrl &c = *(const Ctrl *)q->pinned.p;
         const fq_step_stats *made = (const fq_step_stats *)(q->pinned.p + 256);
         static_assert(sizeof(Ctrl) <= 256, "the rows come behind the control block");
@@ -1857,10 +1858,13 @@ hipError_t launch_overlap(const OvRun &ov, hipStream_t s)
 
 size_t group_report_head(int n) { return (sizeof(Ctrl) * n + 255) & ~(size_t)255; }
 size_t group_report_bytes(int n, i64 steps) { return group_report_head(n) + sizeof(StepStats) * n * steps; }
+// rows of an instance that come through the pinned memory, if all fit it, or none
+i64 group_report_rows(int n, i64 chunk) { return group_report_bytes(n, chunk) <= PINNED_MOST ? chunk : 0; }
 
-// After a launch of a group of at most `chunk` steps: the control blocks, and for every instance its
-// completed steps, rows (appended at (*rows)[j] and advanced, if not null)
-// and error (the first one to *failed, err and rc).
+// After a launch of a group of at most `chunk` steps (whose report fits
+// G.pinned): the control blocks, and for every instance its completed steps,
+// rows (appended at (*rows)[j] and advanced, if not null) and error (the
+// first one to *failed, err and rc).
 int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, const ResPlan *plan, const i64 *stops,
                   int *failed, std::string &err, int &rc)
 {
@@ -1868,14 +1872,11 @@ int group_collect(Group &G, fq_step_stats **rows, hipStream_t s, i64 chunk, cons
     // rows through the pinned memory where they fit it, else a copy for every
     // instance; the last row of an instance is always looked at
     const size_t head = group_report_head(X.n);
-    const bool small = group_report_bytes(X.n, chunk) <= PINNED_MOST;
-    const i64 stride = small ? chunk : 0;
-    hipError_t e = G.pinned->reserve(group_report_bytes(X.n, stride));
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_report, dim3(std::min(X.n, 1024)), dim3(256), 0, s, X.insts, X.n, (Ctrl *)G.pinned->p,
-                           (StepStats *)(G.pinned->p + head), stride);
-        e = hipGetLastError();
-    }
+    const i64 stride = group_report_rows(X.n, chunk);
+    const bool small = stride > 0;
+    hipLaunchKernelGGL(k_report, dim3(std::min(X.n, 1024)), dim3(256), 0, s, X.insts, X.n, (Ctrl *)G.pinned->p,
+                       (StepStats *)(G.pinned->p + head), stride);
+    hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) { err = std::string("group step: ") + hipGetErrorString(e); return FQ_EHIP; }
     memcpy(G.ctrl.data(), G.pinned->p, sizeof(Ctrl) * X.n);
@@ -1997,6 +1998,9 @@ int group_steps(Group &G, i64 steps, i64 stop, fq_step_stats **rows, hipStream_t
         i64 chunk = std::min<i64>(RING, steps - launched);
         ResPlan plan;
         int hr;
+        // before anything is launched: a failure leaves the instances where they are
+        const hipError_t room = G.pinned->reserve(group_report_bytes(X.n, group_report_rows(X.n, chunk)));
+        if (room != hipSuccess) { err = std::string("group report: ") + hipGetErrorString(room); return FQ_EHIP; }
         if (!ov && !gs && plan_resident(G.h.data(), X.n, plan)) {
             hr = group_resident(G, plan, chunk, stop, rows, s, failed, err, rc);
         } else {
