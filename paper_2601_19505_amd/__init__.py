@@ -210,7 +210,11 @@ def _layout(table_capacity=4096, spawn_capacity=16384, buckets=0, lds_slots=0, b
 
 
 class Solver:
-    """One FCIQMC instance on the current GPU (plain per-step launches)."""
+    """One FCIQMC instance on the current GPU."""
+
+    # entries of the state that the last run left (its last row), 0 if not
+    # known: get_state takes arrays of that size
+    _entries = 0
 
     def __init__(self, model, M, N, t=1.0, u=1.0, dtau=1e-3, target_walkers=1000.0, zeta=0.08,
                  xi=None, threshold=1.0, t_rel=1.0, seed=0, addr_words=1, flags=0,
@@ -270,18 +274,22 @@ class Solver:
         a = self._addr(addrs)
         v = np.ascontiguousarray(vals, dtype=np.float64)
         r = self._addr([a[0] if ref is None else ref])[0].copy()
+        self._entries = 0
         self._check(lib().fq_set_state(self.h, _p(a, C.c_uint64), _p(v, C.c_double), len(v),
                                        float(shift), int(step), _p(r, C.c_uint64), float(yref),
                                        _stream()), "fq_set_state")
 
     def run(self, n_steps):
         out = np.zeros(n_steps, STATS_DTYPE)
+        self._entries = 0
         rc = lib().fq_run(self.h, n_steps, C.c_void_p(out.ctypes.data), _stream())
         if rc:
             msg = lib().fq_last_error(self.h)
             err = FqError(rc, f"fq_run: {msg.decode() if msg else ''}")
             err.stats = out
             raise err
+        if n_steps:
+            self._entries = int(out["len"][-1])
         return out
 
     def last_error(self):
@@ -293,7 +301,7 @@ class Solver:
     def get_state(self, cap=None):
         """Current state (addresses, values, shift, step); order unspecified."""
         if cap is None:
-            cap = self.table_capacity + 1024
+            cap = self._entries or self.table_capacity + 1024
         for _ in range(2):
             a = np.empty((cap, self.W), np.uint64)
             v = np.empty(cap, np.float64)
@@ -306,8 +314,11 @@ class Solver:
                 cap = n.value
                 continue
             self._check(rc, "fq_get_state")
-            # pages beyond the entries were never touched: no copy into smaller arrays
-            return a[:n.value], v[:n.value], sh.value, st.value
+            if n.value < cap:
+                # the arrays shrink in place, without a copy
+                a.resize((n.value, self.W), refcheck=False)
+                v.resize(n.value, refcheck=False)
+            return a, v, sh.value, st.value
         raise FqError(-2, "fq_get_state: state changed size")
 
     def spawn_dump(self, cap=None):
@@ -364,6 +375,7 @@ class Solver:
     def copy_state_from(self, other):
         """Copy the state of another solver (same Hamiltonian and parameters,
         any layout) on the device."""
+        self._entries = 0
         self._check(lib().fq_copy_state(self.h, other.h, _stream()), "fq_copy_state")
 
     def autotune(self, candidates, trial_steps=20):
@@ -394,6 +406,8 @@ class Solver:
 
 class _Borrowed(Solver):
     """Handle owned by a batch: same calls as a Solver, no ownership."""
+
+    _entries = property(lambda self: 0, lambda self, n: None)  # the batch steps it too
 
     def __init__(self, h, W, ham, params, table_capacity, spawn_capacity):
         self.h = h
