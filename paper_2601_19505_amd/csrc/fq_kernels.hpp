@@ -93,9 +93,9 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident_joint(fq::Overlap O, fq
                                               patience, O, me, norms, smem);
 }
 
-// explicit instantiations (EXT = extern: declaration only) of the merge and
-// spawn kernels of one (W, model variant) pair, all workgroup sizes and both
-// compression styles
+// explicit instantiations (EXT = extern: declaration only) of the merge,
+// spawn and resident kernels of one (W, model variant) pair, all workgroup
+// sizes and both compression styles (variant 1 is for one word only)
 #define FQ_STEP_KERNEL_SET(EXT, W_, M_)                                                       \
     EXT template __global__ void k_merge<W_, M_, 256, false>(const fq::Inst *const *, const fq::u32 *); \
     EXT template __global__ void k_merge<W_, M_, 512, false>(const fq::Inst *const *, const fq::u32 *); \
@@ -116,5 +116,5 @@ __global__ __launch_bounds__(fq::RES_BS) void k_resident_joint(fq::Overlap O, fq
 
 #define FQ_EXTERN_STEP_KERNELS                                                                \
     FQ_STEP_KERNEL_SET(extern, 1, 0) FQ_STEP_KERNEL_SET(extern, 1, 1) FQ_STEP_KERNEL_SET(extern, 1, 2)        \
-    FQ_STEP_KERNEL_SET(extern, 1, 3) FQ_STEP_KERNEL_SET(extern, 2, 0) FQ_STEP_KERNEL_SET(extern, 2, 1)        \
-    FQ_STEP_KERNEL_SET(extern, 2, 2) FQ_STEP_KERNEL_SET(extern, 2, 3)
+    FQ_STEP_KERNEL_SET(extern, 1, 3) FQ_STEP_KERNEL_SET(extern, 2, 0) FQ_STEP_KERNEL_SET(extern, 2, 2)        \
+    FQ_STEP_KERNEL_SET(extern, 2, 3)

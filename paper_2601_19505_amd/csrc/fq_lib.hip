@@ -39,11 +39,11 @@ using namespace fq;
 
 FQ_EXTERN_STEP_KERNELS
 
-// one workgroup per instance
+// grid: instance, workgroup of the fin_groups(B) of the largest instance
 #ifndef FQ_FIN_BS
 #define FQ_FIN_BS 256
 #endif
-constexpr int FIN_BS = FQ_FIN_BS;  // threads of the finalize workgroup
+constexpr int FIN_BS = FQ_FIN_BS;  // threads of a finalize workgroup
 __global__ __launch_bounds__(FIN_BS) void k_finalize(const Inst *const *insts)
 {
     const Inst &I = const_inst(insts[blockIdx.x]);
@@ -399,7 +399,9 @@ template <int W> const void *step_kernel_w(int m, int bs, bool spawn, bool e)
 {
     switch (m) {
     case 0: return pick_kernel<W, 0>(bs, spawn, e);
-    case 1: return pick_kernel<W, 1>(bs, spawn, e);
+    case 1:  // (one word only)
+        if constexpr (W == 1) return pick_kernel<W, 1>(bs, spawn, e);
+        [[fallthrough]];
     case 2: return pick_kernel<W, 2>(bs, spawn, e);
     default: return pick_kernel<W, 3>(bs, spawn, e);
     }
@@ -416,7 +418,9 @@ template <int W> const void *resident_kernel_w(int m, bool e)
 {
     switch (m) {
     case 0: return e ? (const void *)k_resident<W, 0, true> : (const void *)k_resident<W, 0, false>;
-    case 1: return e ? (const void *)k_resident<W, 1, true> : (const void *)k_resident<W, 1, false>;
+    case 1:  // (one word only)
+        if constexpr (W == 1) return e ? (const void *)k_resident<W, 1, true> : (const void *)k_resident<W, 1, false>;
+        [[fallthrough]];
     case 2: return e ? (const void *)k_resident<W, 2, true> : (const void *)k_resident<W, 2, false>;
     default: return e ? (const void *)k_resident<W, 3, true> : (const void *)k_resident<W, 3, false>;
     }
@@ -428,7 +432,9 @@ template <int W, int KIND> const void *joint_kernel_w(int m)
 {
     switch (m) {
     case 0: return (const void *)k_resident_joint<W, 0, KIND>;
-    case 1: return (const void *)k_resident_joint<W, 1, KIND>;
+    case 1:  // (one word only)
+        if constexpr (W == 1) return (const void *)k_resident_joint<W, 1, KIND>;
+        [[fallthrough]];
     case 2: return (const void *)k_resident_joint<W, 2, KIND>;
     default: return (const void *)k_resident_joint<W, 3, KIND>;
     }
@@ -904,7 +910,6 @@ static const char *fqe_name(int e)
     case FQE_CAP_LDS: return "LDS hash of a bucket is full (use more buckets or lds_slots)";
     case FQE_DIVERGED: return "walker number diverged or became non-finite";
     case FQE_ATTEMPTS: return "too many spawn attempts from one address (more than 2^29 in momentum space, 2^30 otherwise)";
-    case FQE_BARRIER: return "grid barrier timed out";
     default: return "unknown device error";
     }
 }
@@ -914,7 +919,6 @@ static int fqe_status(int e)
     switch (e) {
     case FQE_DIVERGED: return FQ_EDIVERGED;
     case FQE_ATTEMPTS: return FQ_EINVAL;
-    case FQE_BARRIER: return FQ_EHIP;
     default: return FQ_ECAPACITY;
     }
 }

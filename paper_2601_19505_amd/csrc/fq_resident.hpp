@@ -361,7 +361,7 @@ __device__ __forceinline__ void resident_project(const Inst &I, const Lds &L, co
     __syncthreads();
     if (*undone) return;
     const double alpha = *s_alpha;
-    int np = 0;
+    int np = 0;  // (probes, not reported from here)
     resident_stream<W>(IJ, pj, bA, K, words, [&](u64 a0, u64 a1, double v) {
         const int s = lds_slot<W>(L, a0, a1, slot_hash(a0, a1), np);
         if (s < 0) {
@@ -795,7 +795,8 @@ __device__ __forceinline__ void resident_steps(const Inst &I, const int g, const
                 if (GS) s_live = 0;
             }
         }
-        int inx = 0, np = 0, distinct = 0;
+        int inx = 0, distinct = 0;
+        int np = 0;  // (probes, not reported from here)
         // Batches of consecutive buckets whose entries and records together
         // fit the hash; a bucket larger than that is a batch alone (its
         // distinct addresses usually fit).  The first batch is cleared for

@@ -41,8 +41,7 @@
 namespace fq {
 
 constexpr u64 EMPTY = ~0ull;
-enum { FQE_CAP_TABLE = 1, FQE_CAP_SLAB = 2, FQE_CAP_LDS = 3, FQE_DIVERGED = 4, FQE_ATTEMPTS = 5,
-       FQE_BARRIER = 6 };
+enum { FQE_CAP_TABLE = 1, FQE_CAP_SLAB = 2, FQE_CAP_LDS = 3, FQE_DIVERGED = 4, FQE_ATTEMPTS = 5 };
 
 struct StepStats {  // mirrors fq_step_stats
     i64 step, len, exact_steps, inexact_steps, spawns;
