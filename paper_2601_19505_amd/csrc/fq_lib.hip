@@ -1371,17 +1371,17 @@ namespace {
 // Entries and spawn attempts per workgroup that a plan aims at (the latency
 // of a step's chain bounds it then; fewer items do not shorten it).  A step
 // of the 12/12 ring under early compression at 1e4 walkers (1.7e4 entries
-// and attempts): 11.9 us at 512 a workgroup (G = 32), 12.3 at 1024, 19.8 at
-// 2100, 36 with the step kernels.  The same ring at 1e5 walkers (1.4e5
-// items): 20.0 us with 128 and 256 workgroups, 25.3 with 64, 43 with the
-// step kernels.
+// and attempts): 12.1 us with 32 workgroups (512 each), 13.2 with 16, 18.0
+// with 8, 33 with the step kernels.  The same ring at 1e5 walkers (1.6e5
+// items): 18.7 us with 128 workgroups, 19.9 with 256, 45 with the step
+// kernels.
 constexpr i64 RES_AIM = 512;
 // Entries and records per workgroup above which the step kernels are taken:
 // the largest measured.  us a step at RES_MAXG workgroups, resident and step
-// kernels: the 16/16 ring at 1.7e6 items 64 and 138, at 3.0e6 110 and 247;
-// 20/20 in two words at 2.0e6 147 and 198; momentum space, initiator rule, at
-// 3.5e6 133 and 178, at 6.5e6 258 and 316; 48 rings of 6e4 items, four
-// workgroups each, 131 and 638.
+// kernels: the 16/16 ring at 1.8e6 items 64 and 135, at 3.4e6 120 and 240; the
+// 6 x 6 lattice in two words at 2.0e6 137 and 194; momentum space, initiator
+// rule, at 4.0e6 138 and 177, at 6.8e6 277 and 305; 48 rings of 5e4 items,
+// four workgroups each, 130 and 640.
 constexpr i64 RES_MOST = 24576;
 // items per workgroup at which a launch ends that more workgroups can follow:
 // a population that grows from one determinant soon outruns the first plan
@@ -1449,7 +1449,7 @@ bool plan_resident(fq_handle *const *h, int n, ResPlan &P)
 // standard deviations above the mean or so, say what K buckets have; while
 // that is not known, the items of a step bound it.  A launch that finds its
 // hash too small ends, and its chunk is left to the step kernels.  Two
-// replicas of the 12/12 ring at 1e6 walkers (2.2e6 items): 54 us a step, 254
+// replicas of the 12/12 ring at 1e6 walkers (1.7e6 items): 58 us a step, 167
 // with the step and overlap kernels.
 i64 joint_most(int W) { return 3 * (W == 1 ? ResSlots<1>::N : ResSlots<2>::N) / 4; }
 bool plan_joint(fq_handle *const *h, int n, int var, bool excited, ResPlan &P)

@@ -26,7 +26,7 @@
 // A small step is bound by its chain of dependent latencies (a dozen
 // workgroup barriers of 60 ns, LDS and L2 round trips, Philox blocks, two
 // logarithms, the barrier of the workgroups) and by the VALU issue of 16 waves
-// on 4 SIMDs: 10.8 us a step at 1e3 walkers of the 6/6 ring.  The code is kept
+// on 4 SIMDs: 10.9 us a step at 1e3 walkers of the 6/6 ring.  The code is kept
 // small (loops are rolled, every building block is inlined once; 30 KB); 67 KB
 // of unrolled code were no faster.
 //
@@ -35,12 +35,13 @@
 // on one XCD (workgroups go round robin to the 8 XCDs); when the gate finds
 // all of them on one, their common L2 is the meeting point, and a barrier
 // needs no cache maintenance.  Otherwise the last workgroup to arrive on each
-// XCD writes its L2 back (agent release) for all of them, and the XCDs meet.
+// XCD writes its L2 back (agent release) for all of them, waits until that is
+// done, and the XCDs meet.
 // Measured per step with 1024 records of 12 bytes from every workgroup to all
 // others: 1.4 to 1.6 us on one XCD at 2 to 16 workgroups, 2.2 at 32; on all
-// XCDs 2.7 to 3.3 us up to 32, 3.9 at 64, 4.3 at 128 and 5.9 at 256 (4096
-// records each: 11.8).  With a write back by every workgroup instead of one an
-// XCD it was 5.9, 9.8 and 17.7 us at 64, 128 and 256 (4096 records: 33).
+// XCDs 2.7 to 3.6 us up to 32, 4.0 at 64, 4.6 at 128 and 6.0 at 256 (4096
+// records each: 12.0).  With a write back by every workgroup instead of one an
+// XCD it was 6.1, 10.4 and 17.3 us at 64, 128 and 256 (4096 records: 34).
 //
 // Larger steps.  The same kernel is the faster one up to several million
 // entries and records: the four kernels of a step each pay their cold start
@@ -49,9 +50,9 @@
 // distinct addresses fit it, and reserves slab places for four rounds of
 // attempts with one atomic per pair of buckets, in order of the buckets (23
 // times the rate of single atomics, which cap a step at 10 records per ns).
-// us a step, before and now: 16/16 in momentum space with the initiator rule
-// at 1.1e6 items and 2048 buckets 103 and 62, the 16/16 ring at 1.7e6 items
-// 138 and 64, 48 rings of 6e4 items 638 and 129.
+// us a step, step kernels and resident: 16/16 in momentum space with the
+// initiator rule at 1.4e6 items and 2048 buckets 99 and 57, the 16/16 ring at
+// 1.8e6 items 135 and 64, 48 rings of 5e4 items 640 and 130.
 #pragma once
 #include "fq_overlap.hpp"
 #include "fq_step.hpp"
@@ -291,9 +292,9 @@ __device__ __forceinline__ void resident_overlap(const Overlap &O, const Lds &L,
 // of run 0 that it does not hold, meet, and stream them once more to
 // subtract.  The second barrier undoes the step in the same way when some
 // hash does not hold the addresses of both runs: its vote has a word of its
-// own, because the votes of the first barrier are still being read then.  A step of
-// two runs of the 12/12 ring at 1e5 walkers takes 47 us so, 102 with the step
-// and projection kernels.
+// own, because the votes of the first barrier are still being read then.  A
+// step of two runs of the 12/12 ring at 1e5 walkers takes 46 us so, 92 with
+// the step and projection kernels.
 //
 // This workgroup's c_0 . c_1 and c_0 . c_0 (to[0], to[1]); words: as above,
 // the sums of the waves behind them.  addresses (LDS): those of the hash,
