@@ -422,7 +422,7 @@ class _Borrowed(Solver):
 
 
 class Batch:
-    """n instances advanced together (one launch per kernel per step).
+    """n instances advanced together, in launches that they share.
 
     `specs` is a list of dicts with the keyword arguments of Solver (model,
     M, N, t, u, dtau, target_walkers, seed, addr_words, threshold, t_rel,
